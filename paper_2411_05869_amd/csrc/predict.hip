@@ -11,8 +11,8 @@
 // C_core(x*, x_q) inside the sums.  The bump part then no longer factors
 // through c_i: a wave per test point with a group bit sums
 //   sum_q C_core(x*, x_q) sum_{i in M(x*) & M(q)} f_i(x*) f_i(x_q) alpha_q
-// over the masked training points (their data copied when the predictor is
-// created).
+// over the members of its groups (the masked training points' data and the
+// groups' member lists are kept when the predictor is created).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -28,7 +28,9 @@ struct gp_predictor {
   gps::Grid grid{};
   double* alpha_b = nullptr;  // n, binned order
   double* coef = nullptr;     // n1 (at least 1)
-  float* alpha32 = nullptr;   // n, float32 copy for the mixed form
+  // coordinates and alpha of each training point side by side (binned order,
+  // kPackOf(d) doubles a point), or null: read from the data set and alpha_b
+  double* pack = nullptr;
   // core kernel: basis of the nonstationary fields, the fields of the training
   // points (binned order), and the masked training points' data
   gps::CoreBasis cb{};
@@ -38,6 +40,12 @@ struct gp_predictor {
   int32_t* mlist = nullptr;   // nm binned ids of the masked training points
   uint64_t* mmask = nullptr;  // nm group masks
   double* mF = nullptr;       // nm x n1 values f_i
+  // members of each group, one list after another (null: every masked point is tested)
+  int64_t nlist = 0;
+  int32_t* goff = nullptr;    // n1 + 1 offsets
+  int32_t* gk = nullptr;      // nlist masked indices (ascending in a group)
+  int32_t* gq = nullptr;      // nlist binned ids
+  uint64_t* gmask = nullptr;  // nlist group masks
 };
 
 namespace gps {
@@ -62,9 +70,51 @@ __global__ void __launch_bounds__(kThreads) k_group_coef(int64_t nm, int n1, con
   if (threadIdx.x == 0) coef[i] = sh[0];
 }
 
-__global__ void k_to_f32(int64_t n, const double* __restrict__ a, float* __restrict__ b) {
+// Doubles per point of the packed training data: (x, alpha) or (x, y, z or 0, alpha).
+constexpr int kPackOf(int d) { return d == 1 ? 2 : 4; }
+
+__global__ void __launch_bounds__(kThreads) k_pack(int64_t n, int d, const double* __restrict__ xb,
+                                                   const double* __restrict__ alpha, double* __restrict__ pack) {
   const int64_t i = blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x;
-  if (i < n) b[i] = static_cast<float>(a[i]);
+  if (i >= n) return;
+  const int w = kPackOf(d);
+  for (int k = 0; k + 1 < w; ++k) pack[i * w + k] = k < d ? xb[k * n + i] : 0.0;
+  pack[i * w + w - 1] = alpha[i];
+}
+
+// Member lists of the bump groups, one block per group i: the masked points
+// with bit i, ascending.  FILL = false: their number into off[i + 1];
+// FILL = true: the lists, from off[i] on.
+template <bool FILL>
+__global__ void __launch_bounds__(kThreads) k_group_members(int64_t nm, const uint64_t* __restrict__ mmask,
+                                                            const int32_t* __restrict__ mlist,
+                                                            int32_t* __restrict__ off, int32_t* __restrict__ gk,
+                                                            int32_t* __restrict__ gq, uint64_t* __restrict__ gmask) {
+  __shared__ int32_t wcount[kThreads / kWave];
+  const int i = blockIdx.x, w = threadIdx.x / kWave;
+  int32_t running = FILL ? off[i] : 0;
+  for (int64_t b = 0; b < nm; b += kThreads) {
+    const int64_t k = b + threadIdx.x;
+    const uint64_t mk = k < nm ? mmask[k] : 0;
+    const bool hit = (mk >> i) & 1;
+    const uint64_t bal = __ballot(hit);
+    if (lane_id() == 0) wcount[w] = __popcll(bal);
+    __syncthreads();
+    int32_t before = 0, total = 0;
+    for (int j = 0; j < kThreads / kWave; ++j) {
+      if (j < w) before += wcount[j];
+      total += wcount[j];
+    }
+    if (FILL && hit) {
+      const int32_t o = running + before + __popcll(bal & lanes_below());
+      gk[o] = static_cast<int32_t>(k);
+      gq[o] = mlist[k];
+      gmask[o] = mk;
+    }
+    running += total;
+    __syncthreads();
+  }
+  if (!FILL && threadIdx.x == 0) off[i + 1] = running;
 }
 
 struct PredArgs {
@@ -75,19 +125,74 @@ struct PredArgs {
   double lo[3], cell[3];
   int32_t g[3], R[3];
   const double* alpha;
-  const float* alpha32;
+  const double* pack;
   const double* coef;
   // core kernel: masked training points
   int64_t nm;
   const int32_t* mlist;
   const uint64_t* mmask;
   const double* mF;
+  const int32_t* goff;
+  const int32_t* gk;
+  const int32_t* gq;
+  const uint64_t* gmask;
 };
 
+// coordinates and alpha of training point q
+template <int D>
+__device__ __forceinline__ void load_train(const PredArgs& a, int32_t q, double* x, double& alpha) {
+  if (a.pack) {  // uniform over the launch
+    double v[kPackOf(D)];
+    __builtin_memcpy(v, __builtin_assume_aligned(a.pack + static_cast<int64_t>(q) * kPackOf(D), 16), sizeof(v));
+#pragma unroll
+    for (int k = 0; k < D; ++k) x[k] = v[k];
+    alpha = v[kPackOf(D) - 1];
+  } else {
+    x[0] = a.xb[q];
+    if constexpr (D >= 2) x[1] = a.xb[a.n + q];
+    if constexpr (D >= 3) x[2] = a.xb[2 * a.n + q];
+    alpha = a.alpha[q];
+  }
+}
+
+// Lanes per test point.  A test point's window holds 100 - 250 candidates in a
+// few to a few dozen pencils (cell rows along x).  Walked by one thread they
+// are a chain of as many dependent loads, and 1000 points fill four blocks.
+// Sixteen lanes share the point: they read the bounds of up to 32 pencils at
+// once, lay their candidates out as one list in LDS and take its entries in
+// turn, so the loads are independent and no lane idles on a short pencil.
+// About a quarter of the candidates lies within the support; their values
+// (a square root and a degree-11 polynomial, or a core kernel) would be formed
+// with three lanes of four idle, so the hits are gathered first, in place of
+// the list, and evaluated by full groups.  What is left is the gather of the
+// training points from beyond L2 (random sites), which the packed layout
+// halves: one 32-byte read a candidate instead of four 8-byte ones.
+// Calls on the n = 1,095,000 space-time set, thread per point -> this: 1009
+// points (mixed) 244 -> 27 us, 200,003 points in 12 requests (FP64) 1360 -> 300
+// us (384 us before the hits were gathered and the data packed).
+// The split is the same for every m, so a row's value does not depend on the
+// request it arrives in.
+constexpr int kPl = 16;
+constexpr int kPointsPerBlock = kThreads / kPl;
+constexpr int kPencils = 2;     // pencils per lane and round
+constexpr int kCandList = 256;  // candidates listed at a time
+constexpr int kCandUnroll = 4;  // candidates whose loads a lane has in flight
+constexpr int kHitUnroll = 2;
+
+// orders the LDS accesses of a point's lanes (one wave; no block barrier)
+__device__ __forceinline__ void lanes_sync_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // The mean at one test point xp (local part over the cell window, plus the
-// bump groups through c_i when there is no core kernel).
+// bump groups through c_i when there is no core kernel), by the kPl lanes of a
+// point; lane: 0 .. kPl - 1, ids: the point's kCandList words of LDS.  Every lane
+// returns the mean.
 template <int D, bool MIXED, int CK>
-__device__ __forceinline__ double predict_point(const PredArgs& a, const CoreBasis& cb, const double* xp) {
+__device__ __forceinline__ double predict_point(const PredArgs& a, const CoreBasis& cb, const double* xp, int lane,
+                                                int32_t* ids) {
   int c[3] = {0, 0, 0};
   for (int k = 0; k < D; ++k) c[k] = cell_coord(xp[k], a.lo[k], a.cell[k]);
   double sp = 0.0, Sp = 0.0;
@@ -99,35 +204,94 @@ __device__ __forceinline__ double predict_point(const PredArgs& a, const CoreBas
     hi_[k] = min(c[k] + a.R[k], a.g[k] - 1);
     if (lo_[k] > hi_[k]) empty = true;
   }
+  const int shift = lane_id() & ~(kPl - 1);  // the point's first lane of the wave
+  const uint32_t below = (1u << lane) - 1;
   double acc = 0.0;
-  if (!empty) {
-    for (int z = lo_[2]; z <= hi_[2]; ++z)
-      for (int y = lo_[1]; y <= hi_[1]; ++y) {
+  const int ny = hi_[1] - lo_[1] + 1;
+  const int64_t npen = empty ? 0 : static_cast<int64_t>(ny) * (hi_[2] - lo_[2] + 1);
+  for (int64_t p0 = 0; p0 < npen; p0 += kPl * kPencils) {  // the same trips for the point's lanes
+    // this lane's pencils: candidates s[j] .. s[j] + cnt[j] - 1
+    int32_t s[kPencils], cnt[kPencils], own = 0;
+#pragma unroll
+    for (int j = 0; j < kPencils; ++j) {
+      const int64_t pk = p0 + j * kPl + lane;
+      s[j] = cnt[j] = 0;
+      if (pk < npen) {
+        const int y = lo_[1] + static_cast<int>(pk % ny), z = lo_[2] + static_cast<int>(pk / ny);
         const int64_t base = (static_cast<int64_t>(z) * a.g[1] + y) * a.g[0];
-        const int32_t s = a.cell_start[base + lo_[0]];
-        const int32_t e = a.cell_start[base + hi_[0] + 1];
-        for (int32_t q = s; q < e; ++q) {
-          double xq[3];
-          xq[0] = a.xb[q];
-          if constexpr (D >= 2) xq[1] = a.xb[a.n + q];
-          if constexpr (D >= 3) xq[2] = a.xb[2 * a.n + q];
-          const double u2 = scaled_sq<D>(xp, xq, a.kt.inv0);
-          if (u2 < 1.0) {
-            double v = a.kt.s0 * wendland(u2, a.kt.variant);
-            if constexpr (CK == 1) v = core_value<D, 1>(a.kt.core, xp, xq, 0.0, 0.0, 0.0, 0.0) * v;
-            if constexpr (CK == 2)
-              v = core_value<D, 2>(a.kt.core, xp, xq, sp, Sp, a.kt.core.sig[q], a.kt.core.Sig[q]) * v;
-            if constexpr (MIXED)
-              acc += static_cast<double>(static_cast<float>(v) * a.alpha32[q]);
-            else
-              acc += v * a.alpha[q];
-          }
-        }
+        s[j] = a.cell_start[base + lo_[0]];
+        cnt[j] = a.cell_start[base + hi_[0] + 1] - s[j];
       }
+      own += cnt[j];
+    }
+    int32_t end = own;  // inclusive scan over the point's lanes
+#pragma unroll
+    for (int off = 1; off < kPl; off <<= 1) {
+      const int32_t v = __shfl_up(end, off, kPl);
+      if (lane >= off) end += v;
+    }
+    const int32_t total = __shfl(end, kPl - 1, kPl);
+    for (int32_t c0 = 0; c0 < total; c0 += kCandList) {  // dense cells: the list in parts
+      const int32_t len = min(kCandList, total - c0);
+      lanes_sync_lds();  // the previous part has been read
+      int32_t first = end - own - c0;  // list position of the pencil's first candidate
+#pragma unroll
+      for (int j = 0; j < kPencils; ++j) {
+        const int32_t i1 = min(cnt[j], len - first);
+        for (int32_t i = max(0, -first); i < i1; ++i) ids[first + i] = s[j] + i;
+        first += cnt[j];
+      }
+      lanes_sync_lds();
+      // candidates within the support, kept in place (never ahead of what has been read)
+      int32_t nhit = 0;
+      for (int32_t t0 = 0; t0 < len; t0 += kPl * kCandUnroll) {
+        int32_t q[kCandUnroll];
+        double xq[kCandUnroll][3], al;
+#pragma unroll
+        for (int u = 0; u < kCandUnroll; ++u) {
+          const int32_t t = t0 + u * kPl + lane;
+          q[u] = ids[t < len ? t : 0];
+        }
+#pragma unroll
+        for (int u = 0; u < kCandUnroll; ++u) load_train<D>(a, q[u], xq[u], al);
+        lanes_sync_lds();
+#pragma unroll
+        for (int u = 0; u < kCandUnroll; ++u) {
+          const bool hit = t0 + u * kPl + lane < len && scaled_sq<D>(xp, xq[u], a.kt.inv0) < 1.0;
+          const uint32_t bal = static_cast<uint32_t>(__ballot(hit) >> shift) & ((1u << kPl) - 1);
+          if (hit) ids[nhit + __popc(bal & below)] = q[u];
+          nhit += __popc(bal);
+        }
+        lanes_sync_lds();
+      }
+      for (int32_t t0 = 0; t0 < nhit; t0 += kPl * kHitUnroll) {
+        int32_t q[kHitUnroll];
+        double xq[kHitUnroll][3], al[kHitUnroll];
+#pragma unroll
+        for (int u = 0; u < kHitUnroll; ++u) {
+          const int32_t t = t0 + u * kPl + lane;
+          q[u] = ids[t < nhit ? t : 0];
+        }
+#pragma unroll
+        for (int u = 0; u < kHitUnroll; ++u) load_train<D>(a, q[u], xq[u], al[u]);
+#pragma unroll
+        for (int u = 0; u < kHitUnroll; ++u)
+          if (t0 + u * kPl + lane < nhit) {
+            double v = a.kt.s0 * wendland(scaled_sq<D>(xp, xq[u], a.kt.inv0), a.kt.variant);
+            if constexpr (CK == 1) v = core_value<D, 1>(a.kt.core, xp, xq[u], 0.0, 0.0, 0.0, 0.0) * v;
+            if constexpr (CK == 2)
+              v = core_value<D, 2>(a.kt.core, xp, xq[u], sp, Sp, a.kt.core.sig[q[u]], a.kt.core.Sig[q[u]]) * v;
+            // the mixed form: the value and alpha rounded to float32, their product in float32
+            if constexpr (MIXED)
+              acc += static_cast<double>(static_cast<float>(v) * static_cast<float>(al[u]));
+            else
+              acc += v * al[u];
+          }
+      }
+    }
   }
-  // bump groups of the test point (with a core kernel: k_predict_groups)
-  double gsum = 0.0;
-  for (int i = 0; CK == 0 && i < a.kt.n1; ++i) {
+  // bump groups of the test point, a group per lane (with a core kernel: k_predict_groups)
+  for (int i = lane; CK == 0 && i < a.kt.n1; i += kPl) {
     double f = 0.0;
     bool in_group = false;
     for (int j = 0; j < a.kt.n2; ++j) {
@@ -138,19 +302,24 @@ __device__ __forceinline__ double predict_point(const PredArgs& a, const CoreBas
         f = f + bp.a * exp(bp.b * (1.0 - 1.0 / (1.0 - ub2)));
       }
     }
-    if (in_group) gsum += f * a.coef[i];
+    if (in_group) acc += f * a.coef[i];
   }
-  return acc + gsum;
+#pragma unroll
+  for (int off = kPl / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kPl);
+  return acc;
 }
 
 template <int D, bool MIXED, int CK>
 __global__ void __launch_bounds__(kThreads) k_predict(PredArgs a, CoreBasis cb, int64_t m,
                                                       const double* __restrict__ xs, double* __restrict__ out) {
-  const int64_t t = blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x;
+  __shared__ int32_t ids[kPointsPerBlock][kCandList];
+  const int g = threadIdx.x / kPl, lane = threadIdx.x % kPl;
+  const int64_t t = blockIdx.x * static_cast<int64_t>(kPointsPerBlock) + g;
   if (t >= m) return;
   double xp[3];
   for (int k = 0; k < D; ++k) xp[k] = xs[t * D + k];
-  out[t] = predict_point<D, MIXED, CK>(a, cb, xp);
+  const double v = predict_point<D, MIXED, CK>(a, cb, xp, lane, ids[g]);
+  if (lane == 0) out[t] = v;
 }
 
 // Request of row t of a batch: the last r with roff[r] <= t (empty requests
@@ -175,17 +344,21 @@ __global__ void __launch_bounds__(kThreads) k_predict_batch(const PredArgs* __re
                                                             const int32_t* __restrict__ req_pred,
                                                             const int64_t* __restrict__ roff, int nreq, int64_t m,
                                                             const double* __restrict__ xs, double* __restrict__ out) {
-  const int64_t t = blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x;
+  __shared__ int32_t ids[kPointsPerBlock][kCandList];
+  const int g = threadIdx.x / kPl, lane = threadIdx.x % kPl;
+  const int64_t t = blockIdx.x * static_cast<int64_t>(kPointsPerBlock) + g;
   if (t >= m) return;
   const int pi = req_pred[batch_request(roff, nreq, t)];
   double xp[3];
   for (int k = 0; k < D; ++k) xp[k] = xs[t * D + k];
-  out[t] = predict_point<D, MIXED, CK>(args[pi], cbs[pi], xp);
+  const double v = predict_point<D, MIXED, CK>(args[pi], cbs[pi], xp, lane, ids[g]);
+  if (lane == 0) out[t] = v;
 }
 
 // Bump part with a core kernel: one wave per test point.  Lane i < n1 forms
 // f_i(x*) (bumps of group i in j order) into LDS; the lanes then stride over
-// the masked training points and the wave adds its lanes in a fixed order.
+// the members of the point's groups and the wave adds its lanes in a fixed
+// order.
 template <int D, int CK>
 __device__ __forceinline__ void predict_groups_point(const PredArgs& a, const CoreBasis& cb, int64_t t,
                                                      const double* __restrict__ xs, double* __restrict__ out,
@@ -215,26 +388,40 @@ __device__ __forceinline__ void predict_groups_point(const PredArgs& a, const Co
   double sp = 0.0, Sp = 0.0;
   if constexpr (CK == 2) core_point_fields<D>(cb, xp, &sp, &Sp);
   double acc = 0.0;
-  for (int64_t j = lane; j < a.nm; j += kWave) {
-    uint64_t sh = a.mmask[j] & mask;
-    if (!sh) continue;
+  // masked training point k (binned id q) with shared groups sh
+  auto add = [&](int64_t k, int32_t q, uint64_t sh) {
     double bsum = 0.0;
     while (sh) {
       const int i = __builtin_ctzll(sh);
       sh &= sh - 1;
-      bsum += f[i] * a.mF[j * a.kt.n1 + i];
+      bsum += f[i] * a.mF[k * a.kt.n1 + i];
     }
-    const int32_t q = a.mlist[j];
-    double xq[3];
-    xq[0] = a.xb[q];
-    if constexpr (D >= 2) xq[1] = a.xb[a.n + q];
-    if constexpr (D >= 3) xq[2] = a.xb[2 * a.n + q];
+    double xq[3], al;
+    load_train<D>(a, q, xq, al);
     double cv;
     if constexpr (CK == 1)
       cv = core_value<D, 1>(a.kt.core, xp, xq, 0.0, 0.0, 0.0, 0.0);
     else
       cv = core_value<D, 2>(a.kt.core, xp, xq, sp, Sp, a.kt.core.sig[q], a.kt.core.Sig[q]);
-    acc += cv * bsum * a.alpha[q];
+    acc += cv * bsum * al;
+  };
+  if (a.goff) {
+    // the members of the point's groups, each taken in the lowest group it
+    // shares: a few thousand points instead of all masked ones
+    for (uint64_t mm = mask; mm; mm &= mm - 1) {
+      const int i = __builtin_ctzll(mm);
+      const int32_t e = a.goff[i + 1];
+#pragma unroll 2
+      for (int32_t j = a.goff[i] + lane; j < e; j += kWave) {
+        const uint64_t sh = a.gmask[j] & mask;
+        if (__builtin_ctzll(sh) == i) add(a.gk[j], a.gq[j], sh);
+      }
+    }
+  } else {
+    for (int64_t j = lane; j < a.nm; j += kWave) {
+      const uint64_t sh = a.mmask[j] & mask;
+      if (sh) add(j, a.mlist[j], sh);
+    }
   }
 #pragma unroll
   for (int off = kWave / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kWave);
@@ -269,6 +456,57 @@ __global__ void __launch_bounds__(kThreads) k_predict_groups_batch(const PredArg
 
 void destroy_predictor(gp_ctx* c, gp_predictor* p);
 
+// device memory for a copy the predictor can do without: null when there is no room
+template <typename T>
+static T* cache_new(gp_ctx* c, int64_t count) {
+  try {
+    return dev_new<T>(c, static_cast<size_t>(count));
+  } catch (const Error& e) {
+    if (e.st != GP_ENOMEM) throw;
+    return nullptr;
+  }
+}
+
+static void free_member_lists(gp_ctx* c, gp_predictor* p) {
+  if (p->goff) dev_free(c, p->goff, sizeof(int32_t) * (p->kt.n1 + 1));
+  if (p->gk) dev_free(c, p->gk, sizeof(int32_t) * p->nlist);
+  if (p->gq) dev_free(c, p->gq, sizeof(int32_t) * p->nlist);
+  if (p->gmask) dev_free(c, p->gmask, sizeof(uint64_t) * p->nlist);
+  p->goff = p->gk = p->gq = nullptr;
+  p->gmask = nullptr;
+}
+
+// Member lists of the groups from the predictor's masked points (nm > 0).
+static void make_member_lists(gp_ctx* c, gp_predictor* p, int n1) {
+  p->goff = cache_new<int32_t>(c, n1 + 1);
+  if (!p->goff) return;
+  hipLaunchKernelGGL((k_group_members<false>), dim3(n1), dim3(kThreads), 0, c->stream, p->nm, p->mmask, p->mlist,
+                     p->goff, nullptr, nullptr, nullptr);
+  check_launch("group sizes");
+  int32_t* h = static_cast<int32_t*>(pinned_for_write(c, sizeof(int32_t) * (n1 + 1)));
+  GPS_HIP(hipMemcpyAsync(h, p->goff, sizeof(int32_t) * (n1 + 1), hipMemcpyDeviceToHost, c->stream));
+  sync(c);
+  int64_t total = 0;
+  for (int i = 0; i <= n1; ++i) {
+    if (i > 0) total += h[i];
+    h[i] = static_cast<int32_t>(total);
+  }
+  if (total < (int64_t(1) << 31)) {
+    p->nlist = total;  // > 0: every masked point is in a group
+    p->gk = cache_new<int32_t>(c, total);
+    p->gq = cache_new<int32_t>(c, total);
+    p->gmask = cache_new<uint64_t>(c, total);
+  }
+  if (!p->gk || !p->gq || !p->gmask) {
+    free_member_lists(c, p);
+    return;
+  }
+  h2d_async(c, p->goff, h, sizeof(int32_t) * (n1 + 1));
+  hipLaunchKernelGGL((k_group_members<true>), dim3(n1), dim3(kThreads), 0, c->stream, p->nm, p->mmask, p->mlist,
+                     p->goff, p->gk, p->gq, p->gmask);
+  check_launch("group members");
+}
+
 gp_predictor* make_predictor(gp_ctx* c, const gp_dataset* ds, const gp_theta* th, const double* alpha) {
   // a failure part-way releases whatever device memory the predictor holds by then
   auto release = [c](gp_predictor* x) { destroy_predictor(c, x); };
@@ -286,11 +524,8 @@ gp_predictor* make_predictor(gp_ctx* c, const gp_dataset* ds, const gp_theta* th
   p->grid = make_grid(ds, th);
   const int64_t n = ds->n;
   p->alpha_b = dev_new<double>(c, n);
-  p->alpha32 = dev_new<float>(c, n);
   p->coef = dev_new<double>(c, std::max(th->n1, 1));
   permute_to_binned<double>(c, ds, 1, alpha, p->alpha_b);
-  hipLaunchKernelGGL(k_to_f32, dim3(grid_for(n, kThreads)), dim3(kThreads), 0, c->stream, n, p->alpha_b, p->alpha32);
-  check_launch("alpha f32");
   KernelCore kc;
   core_params(th, &kc, &p->cb);
   if (kc.kind == GP_CORE_PACIOREK) {
@@ -318,6 +553,16 @@ gp_predictor* make_predictor(gp_ctx* c, const gp_dataset* ds, const gp_theta* th
       GPS_HIP(hipMemcpyAsync(p->mF, f.F, sizeof(double) * f.nm * th->n1, hipMemcpyDeviceToDevice, c->stream));
     }
   }
+  // Read-only copies of what the predictor holds, made once it is complete: a
+  // context with an HBM budget, or without the room, does without them.
+  if (c->budget == 0) {
+    p->pack = cache_new<double>(c, kPackOf(ds->d) * n);
+    if (p->pack)
+      hipLaunchKernelGGL(k_pack, dim3(grid_for(n, kThreads)), dim3(kThreads), 0, c->stream, n, ds->d, ds->xb,
+                         p->alpha_b, p->pack);
+    check_launch("pack training data");
+    if (p->nm > 0) make_member_lists(c, p.get(), th->n1);
+  }
   sync(c);
   return p.release();
 }
@@ -327,7 +572,8 @@ void destroy_predictor(gp_ctx* c, gp_predictor* p) {
   const int64_t n = p->ds->n;
   dev_free(c, p->bumps, sizeof(Bump) * p->nbumps);
   dev_free(c, p->alpha_b, sizeof(double) * n);
-  dev_free(c, p->alpha32, sizeof(float) * n);
+  dev_free(c, p->pack, sizeof(double) * kPackOf(p->ds->d) * n);
+  free_member_lists(c, p);
   dev_free(c, p->coef, sizeof(double) * std::max(p->kt.n1, 1));
   if (p->sig) dev_free(c, p->sig, sizeof(double) * n);
   if (p->Sig) dev_free(c, p->Sig, sizeof(double) * n);
@@ -351,12 +597,16 @@ static PredArgs pred_args(const gp_predictor* p) {
     a.R[k] = p->grid.R[k];
   }
   a.alpha = p->alpha_b;
-  a.alpha32 = p->alpha32;
+  a.pack = p->pack;
   a.coef = p->coef;
   a.nm = p->nm;
   a.mlist = p->mlist;
   a.mmask = p->mmask;
   a.mF = p->mF;
+  a.goff = p->goff;
+  a.gk = p->gk;
+  a.gq = p->gq;
+  a.gmask = p->gmask;
   return a;
 }
 
@@ -364,7 +614,7 @@ void predict(gp_ctx* c, const gp_predictor* p, int64_t m, const double* xs, int 
   if (m == 0) return;
   const gp_dataset* ds = p->ds;
   const PredArgs a = pred_args(p);
-  const dim3 G(grid_for(m, kThreads)), B(kThreads);
+  const dim3 G(grid_for(m, kPointsPerBlock)), B(kThreads);
   ProfScope ps(c, prec == GP_MIXED ? "predict_f32" : "predict_f64");
   auto go = [&](auto DD) {
     constexpr int D = decltype(DD)::value;
@@ -439,7 +689,7 @@ void predict_batch(gp_ctx* c, int32_t nreq, const gp_predictor* const* preds, co
   const CoreBasis* dc = reinterpret_cast<const CoreBasis*>(dbuf + up(b_args));
   const int32_t* dreq = reinterpret_cast<const int32_t*>(dbuf + up(b_args) + up(b_cb));
   const int64_t* droff = reinterpret_cast<const int64_t*>(dbuf + up(b_args) + up(b_cb) + up(b_req));
-  const dim3 G(grid_for(m, kThreads)), B(kThreads);
+  const dim3 G(grid_for(m, kPointsPerBlock)), B(kThreads);
   ProfScope ps(c, prec == GP_MIXED ? "predict_batch_f32" : "predict_batch_f64");
   auto go = [&](auto DD) {
     constexpr int D = decltype(DD)::value;
