@@ -388,35 +388,30 @@ __global__ void __launch_bounds__(kThreads) k_spmm(int64_t n, unsigned nb_short,
 // and each staged value serves the four rows a wave owns.
 constexpr int kGChunk = 1024;
 
-template <typename VT, typename XT, typename AT, typename YT>
-__global__ void __launch_bounds__(kThreads) k_group_spmv(const int32_t* __restrict__ tiles,
-                                                         const int32_t* __restrict__ grows,
-                                                         const int64_t* __restrict__ uoff,
-                                                         const int32_t* __restrict__ ulist,
-                                                         const int64_t* __restrict__ rp, const VT* __restrict__ val,
-                                                         const XT* __restrict__ x, YT* __restrict__ y,
-                                                         const int* __restrict__ skip) {
-  if (skip && *skip) return;  // uniform over the launch
-  solve_wave_priority();
+constexpr int kWaves = kThreads / kWave;
+constexpr int kWaveRows = kTileRows / kWaves;  // rows of a tile a wave owns: w, w + kWaves, ...
+
+// The sums of the wave's rows of tile t over their leading |U_M| entries, in
+// every lane (0 for rows the tile does not have).
+template <typename VT, typename XT, typename AT>
+__device__ __forceinline__ void tile_gemv(const int4& t, const int32_t* __restrict__ grows,
+                                          const int64_t* __restrict__ uoff, const int32_t* __restrict__ ulist,
+                                          const int64_t* __restrict__ rp, const VT* __restrict__ val,
+                                          const XT* __restrict__ x, AT (&acc)[kWaveRows]) {
   __shared__ AT xs[kGChunk];
-  constexpr int kRows = kTileRows / (kThreads / kWave);
-  // tiles come largest first; block b runs on XCD b % 8, so every XCD gets an
-  // equal share of large and small tiles and the small ones fill the tail
-  const int4 t = reinterpret_cast<const int4*>(tiles)[blockIdx.x];
   const int32_t* U = ulist + uoff[t.x];
   const int64_t nU = uoff[t.x + 1] - uoff[t.x];
   const int w = threadIdx.x / kWave, lane = lane_id();
-  int64_t base[kRows];
-  bool has[kRows];
+  int64_t base[kWaveRows];
+  bool has[kWaveRows];
 #pragma unroll
-  for (int r = 0; r < kRows; ++r) {
-    const int i = w + r * (kThreads / kWave);
+  for (int r = 0; r < kWaveRows; ++r) {
+    const int i = w + r * kWaves;
     has[r] = i < t.z;
     base[r] = has[r] ? rp[grows[t.y + i]] : 0;
   }
-  AT acc[kRows];
 #pragma unroll
-  for (int r = 0; r < kRows; ++r) acc[r] = 0;
+  for (int r = 0; r < kWaveRows; ++r) acc[r] = 0;
   constexpr int kPer = kGChunk / kThreads;
   AT xr[kPer];
   auto load = [&](int64_t c0) {
@@ -440,40 +435,124 @@ __global__ void __launch_bounds__(kThreads) k_group_spmv(const int32_t* __restri
     // those entries get weight 0); one such group per row at a time
     // keeps the kernel at 80 registers (6 waves per SIMD), which measured
     // faster than two groups in flight at 4 waves per SIMD
-    for (int k0 = 4 * lane; k0 < clen; k0 += 4 * kWave) {
-      VT v[1][kRows][4];
+    for (int k = 4 * lane; k < clen; k += 4 * kWave) {
+      VT v[kWaveRows][4];
 #pragma unroll
-      for (int h = 0; h < 1; ++h) {
-        const int k = k0 + h * 4 * kWave;
+      for (int r = 0; r < kWaveRows; ++r) __builtin_memcpy(v[r], val + base[r] + c0 + k, 4 * sizeof(VT));
+      AT xk[4];
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-          if (k < clen) {  // a group past the chunk is not loaded (it could run past the array)
-            __builtin_memcpy(v[h][r], val + base[r] + c0 + k, 4 * sizeof(VT));
-          } else {
+      for (int u = 0; u < 4; ++u) xk[u] = k + u < clen ? xs[min(k + u, kGChunk - 1)] : AT(0);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[h][r][u] = VT(0);
-          }
-        }
-      }
+      for (int r = 0; r < kWaveRows; ++r)
 #pragma unroll
-      for (int h = 0; h < 1; ++h) {
-        const int k = k0 + h * 4 * kWave;
-        AT xk[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) xk[u] = k + u < clen ? xs[min(k + u, kGChunk - 1)] : AT(0);
-#pragma unroll
-        for (int r = 0; r < kRows; ++r)
-#pragma unroll
-          for (int u = 0; u < 4; ++u) acc[r] += (has[r] ? static_cast<AT>(v[h][r][u]) : AT(0)) * xk[u];
-      }
+        for (int u = 0; u < 4; ++u) acc[r] += (has[r] ? static_cast<AT>(v[r][u]) : AT(0)) * xk[u];
     }
   }
 #pragma unroll
-  for (int r = 0; r < kRows; ++r) {
-    AT a = acc[r];
+  for (int r = 0; r < kWaveRows; ++r)
 #pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) a += __shfl_xor(a, off, kWave);
-    if (lane == 0 && has[r]) y[grows[t.y + w + r * (kThreads / kWave)]] = static_cast<YT>(a);
+    for (int off = kWave / 2; off > 0; off >>= 1) acc[r] += __shfl_xor(acc[r], off, kWave);
+}
+
+template <typename VT, typename XT, typename AT, typename YT>
+__global__ void __launch_bounds__(kThreads) k_group_spmv(const int32_t* __restrict__ tiles,
+                                                         const int32_t* __restrict__ grows,
+                                                         const int64_t* __restrict__ uoff,
+                                                         const int32_t* __restrict__ ulist,
+                                                         const int64_t* __restrict__ rp, const VT* __restrict__ val,
+                                                         const XT* __restrict__ x, YT* __restrict__ y,
+                                                         const int* __restrict__ skip) {
+  if (skip && *skip) return;  // uniform over the launch
+  solve_wave_priority();
+  // tiles come largest first; block b runs on XCD b % 8, so every XCD gets an
+  // equal share of large and small tiles and the small ones fill the tail
+  const int4 t = reinterpret_cast<const int4*>(tiles)[blockIdx.x];
+  AT acc[kWaveRows];
+  tile_gemv<VT, XT, AT>(t, grows, uoff, ulist, rp, val, x, acc);
+  const int w = threadIdx.x / kWave;
+#pragma unroll
+  for (int r = 0; r < kWaveRows; ++r)
+    if (lane_id() == 0 && w + r * kWaves < t.z) y[grows[t.y + w + r * kWaves]] = static_cast<YT>(acc[r]);
+}
+
+// Both parts in one launch, for products short enough that the second launch,
+// and not the memory, is what they wait for (kOneLaunchEntries).  A tile's
+// block adds its rows' CSR parts to their group parts; the long rows without a
+// group part take a wave each, the other rows kG lanes.  Every row is summed in
+// the order of the two kernels.  Blocks: tiles, then nb_long, then rows.
+template <typename VT>
+__global__ void __launch_bounds__(kThreads) k_spmv_one(int64_t n, unsigned ntiles, unsigned nb_long, int64_t nlong,
+                                                       const int32_t* __restrict__ tiles,
+                                                       const int32_t* __restrict__ grows,
+                                                       const int64_t* __restrict__ uoff,
+                                                       const int32_t* __restrict__ ulist,
+                                                       const int32_t* __restrict__ long_rows,
+                                                       const int64_t* __restrict__ rp,
+                                                       const int32_t* __restrict__ gskip,
+                                                       const int32_t* __restrict__ col, const VT* __restrict__ val,
+                                                       const double* __restrict__ x, double* __restrict__ y,
+                                                       const int16_t* __restrict__ off16,
+                                                       const int* __restrict__ skip) {
+  if (skip && *skip) return;  // uniform over the launch
+  solve_wave_priority();
+  const int w = threadIdx.x / kWave, lane = lane_id(), sub = threadIdx.x & (kG - 1);
+  auto short_row = [&](int64_t s, int64_t e, int32_t row) {  // by kG lanes
+    double acc = off16 ? spmv_part16<VT, double, double, kG>(s, e, sub, row, off16, val, x)
+                       : spmv_part<VT, double, double, kG>(s, e, sub, row, col, val, x);
+#pragma unroll
+    for (int off = kG / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kG);
+    return acc;
+  };
+  auto long_row = [&](int64_t s, int64_t e, int32_t row) {  // by the wave
+    double acc = spmv_part<VT, double, double, kWave>(s, e, lane, row, col, val, x);
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kWave);
+    return acc;
+  };
+  if (blockIdx.x < ntiles) {
+    const int4 t = reinterpret_cast<const int4*>(tiles)[blockIdx.x];
+    // lanes kG r .. kG r + kG - 1 take the CSR part of the wave's row r
+    const int r8 = lane / kG;
+    const bool own = r8 < kWaveRows && w + r8 * kWaves < t.z;
+    int32_t row = 0;
+    int64_t s = 0, e = 0;
+    if (own) {
+      row = grows[t.y + w + r8 * kWaves];
+      s = rp[row] + gskip[row];
+      e = rp[row + 1];
+    }
+    const bool lng = e - s > kLongRow;
+    double csr = short_row(s, lng ? s : e, row);
+    for (uint64_t todo = __ballot(lng && sub == 0); todo; todo &= todo - 1) {  // uniform
+      const int src = __builtin_ctzll(todo);
+      const double a = long_row(__shfl(s, src, kWave), __shfl(e, src, kWave), __shfl(row, src, kWave));
+      if (lane == src) csr = a;
+    }
+    double acc[kWaveRows], mine = 0.0;
+    tile_gemv<VT, double, double>(t, grows, uoff, ulist, rp, val, x, acc);
+#pragma unroll
+    for (int r = 0; r < kWaveRows; ++r)
+      if (r == r8) mine = acc[r];
+    if (own && sub == 0) y[row] = mine + csr;
+  } else if (blockIdx.x < ntiles + nb_long) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x - ntiles) * kWaves + w;
+    if (i < nlong) {
+      const int32_t row = long_rows[i];
+      if (gskip[row] == 0) {
+        const double a = long_row(rp[row], rp[row + 1], row);
+        if (lane == 0) y[row] = a;
+      }
+    }
+  } else {
+    const unsigned b = xcd_remap(blockIdx.x - ntiles - nb_long, gridDim.x - ntiles - nb_long);
+    const int64_t row = (b * static_cast<int64_t>(kThreads) + threadIdx.x) / kG;
+    if (row < n) {
+      const int64_t s = rp[row], e = rp[row + 1];
+      if (gskip[row] == 0 && e - s <= kLongRow) {  // uniform within the group
+        const double a = short_row(s, e, static_cast<int32_t>(row));
+        if (sub == 0) y[row] = a;
+      }
+    }
   }
 }
 
@@ -495,12 +574,26 @@ __global__ void __launch_bounds__(kThreads) k_col16(int64_t n, const int64_t* __
   }
 }
 
+// Entries up to which the product takes one launch.
+constexpr int64_t kOneLaunchEntries = int64_t(64) << 20;
+
 template <typename VT, typename XT, typename AT, typename YT>
 void spmv_launch(gp_ctx* c, const gp_matrix* m, const XT* x, YT* y, const int* skip = nullptr) {
   const VT* val = static_cast<const VT*>(m->val);
   // long-row blocks padded to a multiple of the XCD count so that both block
   // ranges start on XCD 0 (see xcd_remap)
   const unsigned nb_short = grid_for(m->n * kG, kThreads);
+  if constexpr (std::is_same<XT, double>::value && std::is_same<YT, double>::value) {
+    if (m->ntiles > 0 && m->nnz <= kOneLaunchEntries) {
+      const unsigned nt = static_cast<unsigned>(m->ntiles);
+      const unsigned nl = m->n_long > 0 ? grid_for(m->n_long, kWaves) : 0;
+      hipLaunchKernelGGL((k_spmv_one<VT>), dim3(nt + nl + nb_short), dim3(kThreads), 0, c->stream, m->n, nt, nl,
+                         m->n_long, m->g_tiles, m->g_rows, m->g_uoff, m->g_ulist, m->long_rows, m->row_ptr, m->gskip,
+                         m->col, val, x, y, m->col16, skip);
+      check_launch("spmv");
+      return;
+    }
+  }
   const unsigned nb_long = m->n_long > 0 ? round_up8(grid_for(m->n_long * kWave, kThreads)) : 0;
   if (m->ntiles > 0)
     hipLaunchKernelGGL((k_group_spmv<VT, XT, AT, YT>), dim3(static_cast<unsigned>(m->ntiles)), dim3(kThreads), 0,
