@@ -22,6 +22,7 @@ constexpr int64_t kCsrPad = 64;     // padding entries after the CSR column and 
 constexpr int kTileRows = 16;       // rows per tile of a group block
 constexpr int kSuperRows = 64;      // rows per super-tile (multi-column products)
 constexpr int kPiece = 256;         // U_M entries per block of a multi-column product
+constexpr int kMaxBlock = 32;       // rows of a block-Jacobi block at most
 
 // ------------------------------------------------------------------ errors
 struct Error {
@@ -178,7 +179,7 @@ struct gp_matrix {
   int32_t* bstart = nullptr;    // nblk + 1 block starts (binned rows)
   int32_t* rowblk = nullptr;    // n, block of each row
   int64_t* boff = nullptr;      // nblk + 1 offsets into binv
-  double* binv = nullptr;       // row-major inverses of the diagonal blocks
+  double* binv = nullptr;       // inverses of the diagonal blocks, entry (i, j) of a block of b rows at j * b + i
   size_t bytes = 0;
 };
 

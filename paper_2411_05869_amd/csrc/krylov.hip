@@ -45,6 +45,13 @@ __device__ __forceinline__ int seg_blocks(int64_t n, int per_block) {
   return static_cast<int>(b < 1 ? 1 : b);
 }
 
+// Blocks of a grid-stride pass of at most kRedBlocks blocks over n rows that have
+// a row: the others would add zeros to a sum, or only wait for its partials.
+__host__ __device__ __forceinline__ int red_blocks(int64_t n) {
+  const int64_t b = (n + kThreads - 1) / kThreads;
+  return static_cast<int>(b < 1 ? 1 : (b < kRedBlocks ? b : kRedBlocks));
+}
+
 // ---------------------------------------------------------------- reductions
 __global__ void __launch_bounds__(kThreads) k_dot_part(int64_t n, const double* __restrict__ a,
                                                        const double* __restrict__ b, double* __restrict__ part,
@@ -111,116 +118,168 @@ __device__ __forceinline__ double precond_row(const Precond& M, const double* __
   const int32_t b = M.rowblk[i];
   const int32_t bs = M.bstart[b];
   const int sz = M.bstart[b + 1] - bs;
-  const double* row = M.binv + M.boff[b] + static_cast<int64_t>(i - bs) * sz;
+  const double* row = M.binv + M.boff[b] + (i - bs);
   double z = 0.0;
-  for (int j = 0; j < sz; ++j) z += row[j] * r[bs + j];
+  for (int j = 0; j < sz; ++j) z += row[j * sz] * r[bs + j];
   return z;
 }
 
-// One CG step after the product q = K p.  Every block adds the kRedBlocks
-// partials of p.q (pq_part, same fixed order in every block) and forms alpha =
-// rz / pq; then, kStepRows rows per thread (the block-Jacobi product is a
-// short chain of dependent gathers, so a nearly full grid keeps enough of them
-// in flight):
-// x += alpha p, rn = r - alpha q, z = M^-1 rn, and per-block partials of rn.z and
-// rn.rn.  Block 0 records pq, alpha, rz_old = rz and the status (non-positive
-// curvature).
-constexpr int kStepRows = 2;
-constexpr int kPreEntries = 4;  // block entries per row loaded before alpha is known (blocks average 2.8 points)
+// One CG step after the product q = K p.  Every block adds the partials of p.q
+// (same fixed order in every block) and forms alpha = rz / pq;
+// then, a row per thread: x += alpha p, rn = r - alpha q, z = M^-1 rn, and
+// per-block partials of rn.z and rn.rn, thread t adding its row and row
+// t + 256 of the block's 512.  Block 0 records pq, alpha, rz_old = rz and the
+// status (non-positive curvature).
+//
+// The block product needs rn on the rows of a row's block, which lie within
+// kHalo rows of it: the thread block keeps rn of its rows and of the halo rows
+// on either side in LDS (formed from r and q as for the row itself, so no
+// thread waits for another block).  The inverses are stored by columns, so
+// consecutive rows read consecutive words; PRE entries of a row's are requested
+// before alpha is known, further ones eight at a time.  PRE is 4 where blocks are
+// small (2.8 points at the space-time workload: more would only cost
+// registers) and 32, all of them, where the mean block has more than kBigBlock
+// rows and the latency of a second round would show (see step_launch).
+// Two rows per thread with r, q and the row-wise weights gathered entry by
+// entry took 18.7 us at n = 60,013 (mixture, blocks up to 32, FP64) and 27.0
+// at n = 1,095,000; now @@S and @@T.
+constexpr int kStepRows = 2;    // rows per thread of kRedThreads that a partial covers
+constexpr int kStepThreads = kThreads * kStepRows;
+constexpr int kPreBatch = 8;    // further entries loaded at once
+constexpr int kBigBlock = 8;
+constexpr int kHalo = 32;       // halo rows on either side
+static_assert(kHalo >= kMaxBlock - 1, "the rows of a block lie within kMaxBlock - 1 of each other");
+static_assert(kStepRows == 2, "a thread adds its row and one other");
 
-template <typename QT>
-__global__ void __launch_bounds__(kThreads) k_pcg_step(int64_t n, Precond M, CgScalars* __restrict__ s,
-                                                       const double* __restrict__ pq_part,
-                                                       const double* __restrict__ p, const QT* __restrict__ q,
-                                                       double* __restrict__ x, const double* __restrict__ r,
-                                                       double* __restrict__ rn, double* __restrict__ z,
-                                                       double* __restrict__ part, const int* __restrict__ skip,
-                                                       Seg g = {}) {
+template <typename QT, int PRE>
+__global__ void __launch_bounds__(kStepThreads) k_pcg_step(int64_t n, Precond M, CgScalars* __restrict__ s,
+                                                           const double* __restrict__ pq_part,
+                                                           const double* __restrict__ p, const QT* __restrict__ q,
+                                                           double* __restrict__ x, const double* __restrict__ r,
+                                                           double* __restrict__ rn, double* __restrict__ z,
+                                                           double* __restrict__ part, const int* __restrict__ skip,
+                                                           Seg g = {}) {
   if (seg_skip(skip)) return;
   solve_wave_priority();
   const int64_t o = seg_begin(g, n);
-  if (g.off && static_cast<int>(blockIdx.x) >= seg_blocks(n, kThreads * kStepRows)) return;
+  if (g.off && static_cast<int>(blockIdx.x) >= seg_blocks(n, kStepThreads)) return;
   const int64_t e = o + n;  // rows o .. e of the stacked vectors (the preconditioner is indexed by stacked rows)
   s += blockIdx.y;
   pq_part += blockIdx.y * g.pstride;
   part += blockIdx.y * g.pstride;
-  // Everything a row reads is independent of alpha, so the row's vectors, its
-  // block (row -> block -> start and offset) and the block's first kPreEntries
-  // weights and r, q values are requested before the kRedBlocks partials of
-  // p.q are reduced; the arithmetic afterwards is the same, in the same order.
-  // Row i of z = M^-1 (r - alpha q) forms the block's entries of the new
-  // residual from r and q the same way as the row's own, so every thread sees
-  // bitwise the same values without waiting for the others.
-  double xv[kStepRows], pv[kStepRows], rv[kStepRows], qv[kStepRows], dv[kStepRows];
-  constexpr int kPreSlots = kPreEntries > 0 ? kPreEntries : 1;
-  double wpre[kStepRows][kPreSlots], rpre[kStepRows][kPreSlots], qpre[kStepRows][kPreSlots];
-  const double* brow[kStepRows];
-  int32_t bs[kStepRows];
-  int sz[kStepRows];
+  __shared__ double sr[kStepThreads + 2 * kHalo];
+  // Everything a row reads is independent of alpha, so it is requested before
+  // the partials of p.q are reduced.
+  const int t = threadIdx.x;
+  const int64_t b0 = o + blockIdx.x * static_cast<int64_t>(kStepThreads);  // first row of the thread block
+  const int64_t i = b0 + t;
+  double xv = 0, pv = 0, rv = 0, qv = 0, dv = 1;
+  double w[PRE];
+  const double* bcol = nullptr;
+  int32_t bs = 0;
+  int sz = 0;
+  if (i < e) {
+    xv = x[i];
+    pv = p[i];
+    rv = r[i];
+    qv = static_cast<double>(q[i]);
+    if (M.binv) {
+      const int32_t b = M.rowblk[i];
+      bs = M.bstart[b];
+      sz = M.bstart[b + 1] - bs;
+      bcol = M.binv + M.boff[b] + (i - bs);
 #pragma unroll
-  for (int u = 0; u < kStepRows; ++u) {
-    const int64_t i = o + (blockIdx.x * static_cast<int64_t>(kStepRows) + u) * kThreads + threadIdx.x;
-    sz[u] = 0;
-    if (i < e) {
-      xv[u] = x[i];
-      pv[u] = p[i];
-      rv[u] = r[i];
-      qv[u] = static_cast<double>(q[i]);
-      if (M.binv) {
-        const int32_t b = M.rowblk[i];
-        bs[u] = M.bstart[b];
-        sz[u] = M.bstart[b + 1] - bs[u];
-        brow[u] = M.binv + M.boff[b] + static_cast<int64_t>(i - bs[u]) * sz[u];
-#pragma unroll
-        for (int j = 0; j < kPreEntries; ++j) {
-          if (j < sz[u]) {
-            wpre[u][j] = brow[u][j];
-            rpre[u][j] = r[bs[u] + j];
-            qpre[u][j] = static_cast<double>(q[bs[u] + j]);
-          }
-        }
-      } else {
-        dv[u] = M.diag[i];
-      }
+      for (int j = 0; j < PRE; ++j)
+        if (j < sz) w[j] = bcol[j * sz];
+    } else {
+      dv = M.diag[i];
+    }
+  }
+  // the halo row of this thread (the first 2 kHalo threads have one)
+  double rh = 0.0, qh = 0.0;
+  const int hs = t < kHalo ? t : kStepThreads + t;
+  if (M.binv && t < 2 * kHalo) {
+    const int64_t h = b0 - kHalo + hs;
+    if (h >= o && h < e) {
+      rh = r[h];
+      qh = static_cast<double>(q[h]);
     }
   }
   double pqv[1];
-  reduce_partials<1>(pq_part, kRedBlocks, pqv);
+  reduce_partials<1>(pq_part, red_blocks(n), pqv);
   const double pq = pqv[0], rz = s->rz;
   const bool ok = pq > 0.0 && isfinite(pq);
   const double alpha = ok ? rz / pq : 0.0;
-  double v[2] = {0, 0};
+  const double ri = rv - alpha * qv;
+  if (M.binv) {  // uniform
+    sr[kHalo + t] = ri;
+    if (t < 2 * kHalo) sr[hs] = rh - alpha * qh;
+    __syncthreads();
+  }
+  double zi = 0.0;
+  if (i < e) {
+    x[i] = xv + alpha * pv;
+    if (M.binv) {
+      // z_i = sum_j binv[i][j] rn_j over the block, j ascending
+      const double* rb = sr + (kHalo + (bs - b0));
 #pragma unroll
-  for (int u = 0; u < kStepRows; ++u) {
-    const int64_t i = o + (blockIdx.x * static_cast<int64_t>(kStepRows) + u) * kThreads + threadIdx.x;
-    if (i < e) {
-      x[i] = xv[u] + alpha * pv[u];
-      const double ri = rv[u] - alpha * qv[u];
-      double zi;
-      if (M.binv) {
-        // z_i = sum_j binv[i][j] (r_j - alpha q_j) over the block, j ascending
-        zi = 0.0;
+      for (int j = 0; j < PRE; ++j)
+        if (j < sz) zi += w[j] * rb[j];
+      for (int j0 = PRE; j0 < sz; j0 += kPreBatch) {
+        double v[kPreBatch];
 #pragma unroll
-        for (int j = 0; j < kPreEntries; ++j)
-          if (j < sz[u]) zi += wpre[u][j] * (rpre[u][j] - alpha * qpre[u][j]);
-        for (int j = kPreEntries; j < sz[u]; ++j)
-          zi += brow[u][j] * (r[bs[u] + j] - alpha * static_cast<double>(q[bs[u] + j]));
-      } else {
-        zi = ri / dv[u];
+        for (int j = 0; j < kPreBatch; ++j) v[j] = bcol[min(j0 + j, sz - 1) * sz];
+#pragma unroll
+        for (int j = 0; j < kPreBatch; ++j)
+          if (j0 + j < sz) zi += v[j] * rb[j0 + j];
       }
-      rn[i] = ri;
-      z[i] = zi;
-      v[0] += ri * zi;
-      v[1] += ri * ri;
+    } else {
+      zi = ri / dv;
+    }
+    rn[i] = ri;
+    z[i] = zi;
+  }
+  // rows past the end carry zeros
+  __shared__ double so[2][kThreads], ss[2][kThreads / kWave];
+  const double mine = i < e ? ri : 0.0;
+  if (t >= kThreads) {
+    so[0][t - kThreads] = mine;
+    so[1][t - kThreads] = zi;
+  }
+  __syncthreads();
+  if (t < kThreads) {
+    // the first product rounded, the second fused to it, as a loop over the two rows does
+    double v[2] = {__builtin_fma(so[0][t], so[1][t], mine * zi), __builtin_fma(so[0][t], so[0][t], mine * mine)};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+#pragma unroll
+      for (int off = kWave / 2; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, kWave);
+      if (lane_id() == 0) ss[k][t / kWave] = v[k];
     }
   }
-  block_sum_store<2>(v, part);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  __syncthreads();
+  if (t < 2) {
+    double a = 0;
+#pragma unroll
+    for (int j = 0; j < kThreads / kWave; ++j) a += ss[t][j];
+    part[blockIdx.x * 2 + t] = a;
+  }
+  if (blockIdx.x == 0 && t == 0) {
     s->pq = pq;
     s->alpha = alpha;
     s->rz_old = rz;
     if (!ok) s->status = 1;
   }
+}
+
+// The step's launch: blocks of 512 rows, R problems.
+template <typename... A>
+void step_launch(gp_ctx* c, const gp_matrix* m, unsigned nbs, unsigned R, int64_t n, const Precond& M, A... a) {
+  const dim3 G(nbs, R), B(kStepThreads);
+  if (M.binv && m->binv_len > kBigBlock * m->n)  // sum of b^2 over sum of b: the block size a row sees on average
+    hipLaunchKernelGGL((k_pcg_step<double, kMaxBlock>), G, B, 0, c->stream, n, M, a...);
+  else
+    hipLaunchKernelGGL((k_pcg_step<double, 4>), G, B, 0, c->stream, n, M, a...);
 }
 
 // New direction after a step: every block adds the step's nb partials (same
@@ -233,6 +292,7 @@ __global__ void __launch_bounds__(kThreads) k_pcg_direction(int64_t n, CgScalars
   if (seg_skip(skip)) return;
   solve_wave_priority();
   const int64_t o = seg_begin(g, n);
+  if (static_cast<int>(blockIdx.x) >= red_blocks(n)) return;
   if (g.off) nb = seg_blocks(n, kThreads * kStepRows);  // the step's partials of this problem
   z += o;
   p += o;
@@ -324,7 +384,8 @@ __global__ void __launch_bounds__(kThreads) k_precond(int64_t n, Precond M, cons
   block_sum_store<2>(v, part);
 }
 
-// per-block partials of p.q (kRedBlocks blocks, grid-stride)
+// per-block partials of p.q (red_blocks(n) blocks; rows a stride of kRedBlocks
+// blocks apart, so the sums are those of a full grid)
 template <typename QT>
 __global__ void __launch_bounds__(kThreads) k_pq_part(int64_t n, const double* __restrict__ p,
                                                       const QT* __restrict__ q, double* __restrict__ part,
@@ -332,13 +393,14 @@ __global__ void __launch_bounds__(kThreads) k_pq_part(int64_t n, const double* _
   if (seg_skip(skip)) return;
   solve_wave_priority();
   const int64_t o = seg_begin(g, n);
+  if (static_cast<int>(blockIdx.x) >= red_blocks(n)) return;
   p += o;
   q += o;
   part += blockIdx.y * g.pstride;
   // four strided elements loaded at once, then added in the order of a plain
   // grid-stride loop (the sum does not depend on the unrolling)
   double v[1] = {0};
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
+  constexpr int64_t stride = static_cast<int64_t>(kRedBlocks) * kThreads;
   for (int64_t i = blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x; i < n; i += kLoadBatch * stride) {
     double pv[kLoadBatch], qv[kLoadBatch];
 #pragma unroll
@@ -926,7 +988,7 @@ SolveResult pcg_solve(gp_ctx* c, gp_matrix* m, const double* y, double* x, doubl
   double* ppart = static_cast<double*>(workspace(c, 28, sizeof(double) * 2 * nbp));
   CgScalars* s = static_cast<CgScalars*>(workspace(c, 27, sizeof(CgScalars)));
   CgScalars* hs = static_cast<CgScalars*>(pinned(c, sizeof(CgScalars)));
-  const dim3 G(kRedBlocks), B(kThreads);
+  const dim3 G(kRedBlocks), B(kThreads), GR(red_blocks(n));
   auto read = [&]() {
     GPS_HIP(hipMemcpyAsync(hs, s, sizeof(CgScalars), hipMemcpyDeviceToHost, c->stream));
     side_pump(c);  // the side stream's queue topped up before the host waits
@@ -975,12 +1037,11 @@ SolveResult pcg_solve(gp_ctx* c, gp_matrix* m, const double* y, double* x, doubl
       spmv_f64(c, m, p, q);
       {
         ProfScope ps(c, "pcg_vector_ops");
-        hipLaunchKernelGGL((k_pq_part<double>), G, B, 0, c->stream, n, p, q, pqp, nullptr);
-        hipLaunchKernelGGL((k_pcg_step<double>), dim3(nbs), B, 0, c->stream, n, M, s, pqp, p, q, x, rc, rnx, z,
-                           spart, nullptr);
+        hipLaunchKernelGGL((k_pq_part<double>), GR, B, 0, c->stream, n, p, q, pqp, nullptr);
+        step_launch(c, m, nbs, 1, n, M, s, pqp, p, q, x, rc, rnx, z, spart, static_cast<const int*>(nullptr), Seg{});
         std::swap(rc, rnx);
         if (t + 1 < steps)
-          hipLaunchKernelGGL(k_pcg_direction, G, B, 0, c->stream, n, s, spart, static_cast<int>(nbs), z, p, nullptr);
+          hipLaunchKernelGGL(k_pcg_direction, GR, B, 0, c->stream, n, s, spart, static_cast<int>(nbs), z, p, nullptr);
         else
           hipLaunchKernelGGL(k_beta_fin, dim3(1), B, 0, c->stream, spart, static_cast<int>(nbs), s, 3);
       }
@@ -1166,7 +1227,8 @@ static void pcg_device_impl(gp_ctx* c, gp_matrix* m, const double* y, double* x,
   const int* skip_true = &ctl->skip_true;
   const int* skip_final = &ctl->skip_final;
   const unsigned Ry = static_cast<unsigned>(R);
-  const dim3 G(kRedBlocks, Ry), B(kThreads), G1(1, Ry), GP(nbp, Ry), GS(nbs, Ry), C(kCtlThreads);
+  const dim3 G(kRedBlocks, Ry), B(kThreads), G1(1, Ry), GP(nbp, Ry), GR(red_blocks(nrow), Ry),
+      C(kCtlThreads);
   auto true_residual = [&](const int* gate, const int* shared_gate) {
     spmv_f64(c, m, x, q, shared_gate);
     hipLaunchKernelGGL(k_true_resid, G, B, 0, c->stream, nrow, y, q, rc, gate, g);
@@ -1188,12 +1250,11 @@ static void pcg_device_impl(gp_ctx* c, gp_matrix* m, const double* y, double* x,
     for (int t = 0; t < steps; ++t) {
       spmv_f64(c, m, p, q, &all->skip_iter);
       ProfScope ps(c, "pcg_vector_ops");
-      hipLaunchKernelGGL((k_pq_part<double>), G, B, 0, c->stream, nrow, p, q, pqp, skip_iter, g);
-      hipLaunchKernelGGL((k_pcg_step<double>), GS, B, 0, c->stream, nrow, M, s, pqp, p, q, x, rc, rnx, z,
-                         spart, skip_iter, g);
+      hipLaunchKernelGGL((k_pq_part<double>), GR, B, 0, c->stream, nrow, p, q, pqp, skip_iter, g);
+      step_launch(c, m, nbs, Ry, nrow, M, s, pqp, p, q, x, rc, rnx, z, spart, skip_iter, g);
       std::swap(rc, rnx);
       if (t + 1 < steps)
-        hipLaunchKernelGGL(k_pcg_direction, G, B, 0, c->stream, nrow, s, spart, static_cast<int>(nbs), z, p,
+        hipLaunchKernelGGL(k_pcg_direction, GR, B, 0, c->stream, nrow, s, spart, static_cast<int>(nbs), z, p,
                            skip_iter, g);
       else
         hipLaunchKernelGGL(k_beta_fin, G1, B, 0, c->stream, spart, static_cast<int>(nbs), s, 3, skip_iter, g,
@@ -1326,9 +1387,9 @@ __global__ void __launch_bounds__(kThreads) k_mr_lanczos(int64_t n, Precond M, c
       const int32_t b = M.rowblk[i];
       const int32_t bs = M.bstart[b];
       const int sz = M.bstart[b + 1] - bs;
-      const double* row = M.binv + M.boff[b] + static_cast<int64_t>(i - bs) * sz;
+      const double* row = M.binv + M.boff[b] + (i - bs);
       zi = 0.0;
-      for (int j = 0; j < sz; ++j) zi += row[j] * mr_next(s, f, q, r1, r2, bs + j);
+      for (int j = 0; j < sz; ++j) zi += row[j * sz] * mr_next(s, f, q, r1, r2, bs + j);
     }
     rn[i] = ri;
     z[i] = zi;

@@ -19,7 +19,6 @@ namespace gps {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kMaxBlock = 32;
 
 // flag[p] = 1 when p starts a block (first point of its cell, or every
 // kMaxBlock-th point inside a large cell)
@@ -140,10 +139,11 @@ __global__ void __launch_bounds__(kThreads) k_block_invert(int64_t nblk, const i
   }
   if (mine && !ok && lane == 0) atomicOr(bad, 1);
   if (mine && lane < sz) {
-    double* out = binv + boff[g] + static_cast<int64_t>(lane) * sz;
+    // stored by columns: in the products consecutive rows read consecutive words
+    double* out = binv + boff[g] + lane;
 #pragma unroll
     for (int j = 0; j < BS; ++j)
-      if (j < sz) out[j] = a[j];
+      if (j < sz) out[j * sz] = a[j];
   }
 }
 

@@ -39,7 +39,12 @@ __device__ __forceinline__ void block_sum_store(double (&v)[NV], double* __restr
 // Sums part[b * NV + i] over b in a fixed order (partials written by an earlier
 // launch); the result is returned to every thread of the block.
 // A thread loads four of its strided partials at once and adds them in the
-// order of a plain strided loop.
+// order of a plain strided loop; the 256 threads are combined as a halving tree
+// (t with t + 128, t + 64, ..., t + 1).  The consumers' blocks all wait for
+// this sum: only the first two levels go through LDS (every wave adds them for
+// itself after one barrier), the rest are lane exchanges, which give every lane
+// the total (a + b = b + a, so both sides of an exchange hold the same bits).
+// A block of more threads gets the same sum: its first kRedThreads form it.
 template <int NV>
 __device__ __forceinline__ void reduce_partials(const double* __restrict__ part, int nb, double* __restrict__ res) {
   constexpr int kBatch = 4;
@@ -47,7 +52,8 @@ __device__ __forceinline__ void reduce_partials(const double* __restrict__ part,
   double s[NV];
 #pragma unroll
   for (int i = 0; i < NV; ++i) s[i] = 0;
-  for (int b0 = threadIdx.x; b0 < nb; b0 += kBatch * kRedThreads) {
+  const int nbt = threadIdx.x < kRedThreads ? nb : 0;
+  for (int b0 = threadIdx.x; b0 < nbt; b0 += kBatch * kRedThreads) {
     double v[kBatch][NV];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
@@ -61,17 +67,19 @@ __device__ __forceinline__ void reduce_partials(const double* __restrict__ part,
 #pragma unroll
         for (int i = 0; i < NV; ++i) s[i] += v[u][i];
   }
+  if (threadIdx.x < kRedThreads)
 #pragma unroll
-  for (int i = 0; i < NV; ++i) sh[i][threadIdx.x] = s[i];
+    for (int i = 0; i < NV; ++i) sh[i][threadIdx.x] = s[i];
   __syncthreads();
-  for (int st = kRedThreads / 2; st > 0; st >>= 1) {
-    if (threadIdx.x < st)
+  const int l = lane_id();
 #pragma unroll
-      for (int i = 0; i < NV; ++i) sh[i][threadIdx.x] += sh[i][threadIdx.x + st];
-    __syncthreads();
+  for (int i = 0; i < NV; ++i) {
+    static_assert(kRedThreads == 4 * kWave, "two levels above a wave");
+    double v = (sh[i][l] + sh[i][l + 128]) + (sh[i][l + 64] + sh[i][l + 192]);
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
+    res[i] = v;
   }
-#pragma unroll
-  for (int i = 0; i < NV; ++i) res[i] = sh[i][0];
   __syncthreads();
 }
 

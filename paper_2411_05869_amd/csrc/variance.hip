@@ -229,7 +229,7 @@ __device__ __forceinline__ void col_totals(const double* __restrict__ part, int 
 }
 
 // Preconditioner of the recurrences: the matrix diagonal, or (binv set) the
-// block-Jacobi inverses over the binning cells (row-major per block).  Row i of
+// block-Jacobi inverses over the binning cells (by columns per block).  Row i of
 // z = M^-1 r needs r on the rows of its block; the caller passes a function
 // that forms r for any row, so every thread sees the same values without
 // waiting for the others.
@@ -247,9 +247,9 @@ __device__ __forceinline__ double var_precond(const VarPrecond& M, int64_t i, do
   const int32_t b = M.rowblk[i];
   const int32_t bs = M.bstart[b];
   const int sz = M.bstart[b + 1] - bs;
-  const double* row = M.binv + M.boff[b] + static_cast<int64_t>(i - bs) * sz;
+  const double* row = M.binv + M.boff[b] + (i - bs);
   double z = 0.0;
-  for (int j = 0; j < sz; ++j) z += row[j] * r_at(bs + j);
+  for (int j = 0; j < sz; ++j) z += row[j * sz] * r_at(bs + j);
   return z;
 }
 
