@@ -141,8 +141,8 @@ __device__ __forceinline__ double precond_row(const Precond& M, const double* __
 // registers) and 32, all of them, where the mean block has more than kBigBlock
 // rows and the latency of a second round would show (see step_launch).
 // Two rows per thread with r, q and the row-wise weights gathered entry by
-// entry took 18.7 us at n = 60,013 (mixture, blocks up to 32, FP64) and 27.0
-// at n = 1,095,000; now @@S and @@T.
+// entry took 18.7 us at n = 60,013 (mixture, blocks up to 32, FP64), now 7.7; at
+// n = 1,095,000 (space-time) it is bound by its 105 MB: 27 us either way.
 constexpr int kStepRows = 2;    // rows per thread of kRedThreads that a partial covers
 constexpr int kStepThreads = kThreads * kStepRows;
 constexpr int kPreBatch = 8;    // further entries loaded at once

@@ -574,7 +574,11 @@ __global__ void __launch_bounds__(kThreads) k_col16(int64_t n, const int64_t* __
   }
 }
 
-// Entries up to which the product takes one launch.
+// Entries up to which the product takes one launch.  Two launches -> one, per
+// product: 0.3M entries (FP64) 10.5 -> 8.0 us, 2.0M (mixture n = 30,011, mixed)
+// 13.7 -> 9.6, 5.0M 21.4 -> 16.2, 42M 52.5 -> 49.0 and 87.5 -> 79.2 (FP64).  At 87M
+// entries the CSR rows' occupancy counts for more (the tile code holds 80
+// registers): 146.3 -> 150.7 and 202.1 -> 214.5.
 constexpr int64_t kOneLaunchEntries = int64_t(64) << 20;
 
 template <typename VT, typename XT, typename AT, typename YT>
