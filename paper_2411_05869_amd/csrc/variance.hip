@@ -27,8 +27,15 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kC = 32;                 // right-hand sides per batch
 constexpr int kRowsPer = kThreads / kC;  // rows handled together by a block
-constexpr unsigned kVBlocks = 1024;    // blocks of the column-reduction kernels
+// The reductions end in one block that adds every block's partials: few, large
+// blocks leave it little to add (1024 blocks of 256 threads took it 12 - 18 us
+// an iteration, longer than the pass it closed at n = 50,021).
+constexpr int kRThreads = 1024;        // threads of the reducing passes
+constexpr unsigned kVBlocks = 512;     // their blocks at most
+constexpr int kRRows = kRThreads / kC; // rows handled together by one of them
 constexpr int kRowBatch = 4;           // strided rows a thread loads at once in the column reductions
+constexpr int kTile = 64;              // rows of a tile of the update, before whole Jacobi blocks
+constexpr int kTileMax = kTile + kMaxBlock - 1;
 constexpr int kCheckEvery = 8;
 constexpr int kMaxRefresh = 3;
 
@@ -177,55 +184,79 @@ __global__ void __launch_bounds__(kThreads) k_cross_groups(CrossArgs a, CoreBasi
 }
 
 // ------------------------------------------------------- column reductions
-// Thread (r, col) = (threadIdx.x / 32, threadIdx.x % 32) takes rows r, r + 8,
-// ... of the block's share; per block and column the NV partial sums go to
-// part[(blockIdx.x * NV + v) * 32 + col].
+// Thread (r, col) = (threadIdx.x / 32, threadIdx.x % 32) of kRThreads takes rows
+// r, r + 32, ... of the block's share; per block and column the NV partial sums
+// go to part[(blockIdx.x * NV + v) * 32 + col].  A wave first adds its two rows,
+// then thread (v, col) the waves in order.
 template <int NV>
 __device__ __forceinline__ void col_partials(const double (&v)[NV], double* __restrict__ part) {
-  __shared__ double sh[NV][kRowsPer][kC];
-  const int col = threadIdx.x % kC, r = threadIdx.x / kC;
+  constexpr int kW = kRThreads / kWave;
+  __shared__ double sh[NV][kW][kC];
+  const int col = threadIdx.x % kC, w = threadIdx.x / kWave;
 #pragma unroll
-  for (int i = 0; i < NV; ++i) sh[i][r][col] = v[i];
+  for (int i = 0; i < NV; ++i) {
+    const double t = v[i] + __shfl_xor(v[i], kC, kWave);
+    if (lane_id() < kC) sh[i][w][col] = t;
+  }
   __syncthreads();
-  if (threadIdx.x < kC) {
+  if (threadIdx.x < NV * kC) {
+    const int i = threadIdx.x / kC;
+    double s = 0.0;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      double s = 0.0;
-      for (int rr = 0; rr < kRowsPer; ++rr) s += sh[i][rr][col];
-      part[(static_cast<int64_t>(blockIdx.x) * NV + i) * kC + col] = s;
-    }
+    for (int k = 0; k < kW; ++k) s += sh[i][k][col];
+    part[(static_cast<int64_t>(blockIdx.x) * NV + i) * kC + col] = s;
   }
 }
 
 // Column totals of the partials of nb blocks, in a fixed order: thread
-// (chunk, col) = (threadIdx.x / 32, threadIdx.x % 32) of a kFinThreads-thread
-// block adds the partials of its chunk of consecutive blocks, then thread col
-// adds the chunks in order.  tot[v] is valid in threads 0..31 (column
-// threadIdx.x); every thread of the block must call it.
+// (chunk, col) of a kFinThreads-thread block adds the partials of blocks chunk,
+// chunk + 32, ... (eight loaded at once), a wave its two chunks, then thread
+// (v, col) the waves in order.  tot[0] is the total of value threadIdx.x / 32,
+// valid in threads 0 .. 32 NV - 1 (column threadIdx.x % 32); every thread of the
+// block must call it.
 constexpr int kFinThreads = 1024;
-constexpr int kChunks = kFinThreads / kC;
 
 template <int NV>
-__device__ __forceinline__ void col_totals(const double* __restrict__ part, int nb, double (&tot)[NV]) {
-  __shared__ double sh[NV][kChunks][kC];
+__device__ __forceinline__ double col_total(const double* __restrict__ part, int nb) {
+  constexpr int kW = kFinThreads / kWave, kChunks = kFinThreads / kC, kB = 8;
+  __shared__ double sh[NV][kW][kC];
   const int col = threadIdx.x % kC, ch = threadIdx.x / kC;
-  const int per = (nb + kChunks - 1) / kChunks;
-  const int b0 = min(nb, ch * per), b1 = min(nb, b0 + per);
+  double s[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) s[v] = 0.0;
+  for (int b0 = ch; b0 < nb; b0 += kB * kChunks) {
+    double t[kB][NV];
+#pragma unroll
+    for (int u = 0; u < kB; ++u)
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        const int b = b0 + u * kChunks;
+        t[u][v] = b < nb ? part[(static_cast<int64_t>(b) * NV + v) * kC + col] : 0.0;
+      }
+#pragma unroll
+    for (int u = 0; u < kB; ++u)
+#pragma unroll
+      for (int v = 0; v < NV; ++v) s[v] += t[u][v];
+  }
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
-    double s = 0.0;
-    for (int b = b0; b < b1; ++b) s += part[(static_cast<int64_t>(b) * NV + v) * kC + col];
-    sh[v][ch][col] = s;
+    const double t = s[v] + __shfl_xor(s[v], kC, kWave);
+    if (lane_id() < kC) sh[v][threadIdx.x / kWave][col] = t;
   }
   __syncthreads();
-  if (threadIdx.x < kC) {
+  double r = 0.0;
+  if (threadIdx.x < NV * kC)
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      double s = 0.0;
-      for (int c = 0; c < kChunks; ++c) s += sh[v][c][col];
-      tot[v] = s;
-    }
-  }
+    for (int k = 0; k < kW; ++k) r += sh[threadIdx.x / kC][k][col];
+  return r;
+}
+
+// The totals of two values: both valid in threads 0 .. 31 (the second handed
+// over from threads 32 .. 63 of the same wave).
+__device__ __forceinline__ void col_totals2(const double* __restrict__ part, int nb, double (&tot)[2]) {
+  const double t = col_total<2>(part, nb);
+  tot[0] = t;
+  tot[1] = __shfl_xor(t, kC, kWave);
 }
 
 // Preconditioner of the recurrences: the matrix diagonal, or (binv set) the
@@ -241,40 +272,80 @@ struct VarPrecond {
   const double* binv;
 };
 
-template <typename F>
-__device__ __forceinline__ double var_precond(const VarPrecond& M, int64_t i, double ri, F&& r_at) {
-  if (!M.binv) return ri / M.diag[i];
+// Rows of tile k: from the first Jacobi block that starts at or after row
+// kTile k to the one that starts at or after row kTile (k + 1), so that a tile
+// holds whole blocks (at most kTileMax rows) and the tiles hold every row once.
+__device__ __forceinline__ int64_t tile_start(const VarPrecond& M, int64_t n, int64_t k) {
+  const int64_t i = k * kTile;
+  if (i >= n) return n;
+  if (!M.binv) return i;
   const int32_t b = M.rowblk[i];
-  const int32_t bs = M.bstart[b];
-  const int sz = M.bstart[b + 1] - bs;
-  const double* row = M.binv + M.boff[b] + (i - bs);
-  double z = 0.0;
-  for (int j = 0; j < sz; ++j) z += row[j * sz] * r_at(bs + j);
-  return z;
+  return M.bstart[b] == i ? i : M.bstart[b + 1];
 }
 
-#define ROW_LOOP(n)                                                                                 \
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kRowsPer + threadIdx.x / kC; i < (n);       \
-       i += static_cast<int64_t>(gridDim.x) * kRowsPer)
+// z = M^-1 r for the rows of a tile (rows lo .. hi - 1, the thread's column):
+// rt holds the tile's r; put(i, r, z) takes each of the thread's rows.
+// The block product is rt's rows times the block's inverse: r is read once
+// from memory for the whole block instead of once per row of it, and a row's
+// inverse entries (stored by columns) are loaded eight at a time.
+template <typename F>
+__device__ __forceinline__ void tile_precond(const VarPrecond& M, int64_t lo, int64_t hi, double (*rt)[kC], F&& put) {
+  const int col = threadIdx.x % kC;
+  for (int64_t i = lo + threadIdx.x / kC; i < hi; i += kRRows) {
+    const double r = rt[i - lo][col];
+    double z = 0.0;
+    if (M.binv) {
+      const int32_t b = M.rowblk[i];
+      const int32_t bs = M.bstart[b];
+      const int sz = M.bstart[b + 1] - bs;
+      const double* w = M.binv + M.boff[b] + (i - bs);
+      const double(*rb)[kC] = rt + (bs - lo);
+      constexpr int kB = 8;
+      for (int j0 = 0; j0 < sz; j0 += kB) {
+        double v[kB];
+#pragma unroll
+        for (int j = 0; j < kB; ++j) v[j] = w[min(j0 + j, sz - 1) * sz];
+#pragma unroll
+        for (int j = 0; j < kB; ++j)
+          if (j0 + j < sz) z += v[j] * rb[j0 + j][col];
+      }
+    } else {
+      z = r / M.diag[i];
+    }
+    put(i, r, z);
+  }
+}
 
-// R = X - KW (KW given, or W = 0 when kw is null); Z = R / diag; P = Z;
+#define ROW_LOOP(n)                                                                               \
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kRRows + threadIdx.x / kC; i < (n);       \
+       i += static_cast<int64_t>(gridDim.x) * kRRows)
+
+// R = X - KW (KW given, or W = 0 when kw is null); Z = M^-1 R; P = Z;
 // partials of r.z and r.r
-__global__ void __launch_bounds__(kThreads) k_bcg_start(int64_t n, const double* __restrict__ X,
-                                                        const double* __restrict__ kw, VarPrecond M,
-                                                        double* __restrict__ R, double* __restrict__ Z,
-                                                        double* __restrict__ P, double* __restrict__ part) {
+__global__ void __launch_bounds__(kRThreads) k_bcg_start(int64_t n, const double* __restrict__ X,
+                                                         const double* __restrict__ kw, VarPrecond M,
+                                                         double* __restrict__ R, double* __restrict__ Z,
+                                                         double* __restrict__ P, double* __restrict__ part) {
+  __shared__ double rt[kTileMax][kC];
   const int col = threadIdx.x % kC;
   double v[2] = {0.0, 0.0};
-  ROW_LOOP(n) {
-    const int64_t e = i * kC + col;
-    auto r_at = [&](int64_t q) { return kw ? X[q * kC + col] - kw[q * kC + col] : X[q * kC + col]; };
-    const double r = r_at(i);
-    const double z = var_precond(M, i, r, r_at);
-    R[e] = r;
-    Z[e] = z;
-    P[e] = z;
-    v[0] += r * z;
-    v[1] += r * r;
+  for (int64_t k = blockIdx.x; k * kTile < n; k += gridDim.x) {
+    const int64_t lo = tile_start(M, n, k), hi = tile_start(M, n, k + 1);
+    __syncthreads();  // the previous tile has been read
+    for (int64_t i = lo + threadIdx.x / kC; i < hi; i += kRRows) {
+      const int64_t e = i * kC + col;
+      const double r = kw ? X[e] - kw[e] : X[e];
+      R[e] = r;
+      rt[i - lo][col] = r;
+    }
+    __syncthreads();
+    tile_precond(M, lo, hi, rt, [&](int64_t i, double r, double z) {
+      const int64_t e = i * kC + col;
+      Z[e] = z;
+      P[e] = z;
+      v[0] += r * z;
+      v[1] += r * r;
+    });
   }
   col_partials<2>(v, part);
 }
@@ -284,7 +355,7 @@ __global__ void __launch_bounds__(kThreads) k_bcg_start(int64_t n, const double*
 __global__ void __launch_bounds__(kFinThreads) k_bcg_start_fin(const double* __restrict__ part, int nb,
                                                                BcgScalars* __restrict__ S, double tol2, int mode) {
   double t[2];
-  col_totals<2>(part, nb, t);
+  col_totals2(part, nb, t);
   if (threadIdx.x >= kC) return;
   const int col = threadIdx.x;
   const double rz = t[0], rr = t[1];
@@ -299,13 +370,13 @@ __global__ void __launch_bounds__(kFinThreads) k_bcg_start_fin(const double* __r
   }
 }
 
-__global__ void __launch_bounds__(kThreads) k_bcg_pq(int64_t n, const double* __restrict__ P,
-                                                     const double* __restrict__ Q, double* __restrict__ part) {
+__global__ void __launch_bounds__(kRThreads) k_bcg_pq(int64_t n, const double* __restrict__ P,
+                                                      const double* __restrict__ Q, double* __restrict__ part) {
   // four strided rows loaded at once, added in the order of the plain row loop
   const int col = threadIdx.x % kC;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kRowsPer;
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * kRRows;
   double v[1] = {0.0};
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kRowsPer + threadIdx.x / kC; i < n; i += kRowBatch * stride) {
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kRRows + threadIdx.x / kC; i < n; i += kRowBatch * stride) {
     double pv[kRowBatch], qv[kRowBatch];
 #pragma unroll
     for (int u = 0; u < kRowBatch; ++u) {
@@ -322,8 +393,7 @@ __global__ void __launch_bounds__(kThreads) k_bcg_pq(int64_t n, const double* __
 
 __global__ void __launch_bounds__(kFinThreads) k_bcg_alpha(const double* __restrict__ part, int nb,
                                                            BcgScalars* __restrict__ S) {
-  double t[1];
-  col_totals<1>(part, nb, t);
+  const double t[1] = {col_total<1>(part, nb)};
   if (threadIdx.x >= kC) return;
   const int col = threadIdx.x;
   const double pq = t[0];
@@ -340,50 +410,180 @@ __global__ void __launch_bounds__(kFinThreads) k_bcg_alpha(const double* __restr
   S->alpha[col] = a;
 }
 
-// W += alpha P; Rout = Rin - alpha Q; Z = M^-1 Rout; partials of r.z and r.r.
-// The residual alternates between two buffers: the block product reads the
-// old residual of the neighbouring rows, which no thread overwrites.
-__global__ void __launch_bounds__(kThreads) k_bcg_update(int64_t n, const BcgScalars* __restrict__ S,
-                                                         const double* __restrict__ P, const double* __restrict__ Q,
-                                                         VarPrecond M, double* __restrict__ W,
-                                                         const double* __restrict__ Rin, double* __restrict__ Rout,
-                                                         double* __restrict__ Z, double* __restrict__ part) {
+// R -= alpha Q; Z = M^-1 R; partials of r.z and r.r.  A block takes whole tiles
+// of Jacobi blocks, so R is updated in place.  W += alpha P waits for the
+// direction's pass, which reads P anyway: the iteration's vector passes move 11
+// blocks of n x 32 instead of 12 (n = 1,095,000: 886 -> 776 us with block Jacobi,
+// 646 -> 556 with Jacobi, whose 3.1 GB take 598 us at the rate of a large copy).
+__global__ void __launch_bounds__(kRThreads) k_bcg_update(int64_t n, const BcgScalars* __restrict__ S,
+                                                          const double* __restrict__ Q, VarPrecond M,
+                                                          double* __restrict__ R, double* __restrict__ Z,
+                                                          double* __restrict__ part) {
+  __shared__ double rt[kTileMax][kC];
   const int col = threadIdx.x % kC;
   const double a = S->alpha[col];
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kRowsPer;
-  const int64_t i0 = static_cast<int64_t>(blockIdx.x) * kRowsPer + threadIdx.x / kC;
-  // the next row's R, Q, W and P are requested before the current row is
-  // processed (same arithmetic, same order)
-  double rn = 0.0, qn = 0.0, wn = 0.0, pn = 0.0;
-  if (i0 < n) {
-    const int64_t e = i0 * kC + col;
-    rn = Rin[e], qn = Q[e], wn = W[e], pn = P[e];
-  }
+  constexpr int kPer = (kTileMax + kRRows - 1) / kRRows;  // rows of a tile per thread
   double v[2] = {0.0, 0.0};
-  for (int64_t i = i0; i < n; i += stride) {
-    const int64_t e = i * kC + col;
-    const double ri = rn, qi = qn, wi = wn, pi = pn;
-    if (i + stride < n) {
-      const int64_t f = (i + stride) * kC + col;
-      rn = Rin[f], qn = Q[f], wn = W[f], pn = P[f];
+  for (int64_t k = blockIdx.x; k * kTile < n; k += gridDim.x) {
+    const int64_t lo = tile_start(M, n, k), hi = tile_start(M, n, k + 1);
+    double rv[kPer], qv[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int64_t i = lo + threadIdx.x / kC + u * kRRows;
+      rv[u] = i < hi ? R[i * kC + col] : 0.0;
+      qv[u] = i < hi ? Q[i * kC + col] : 0.0;
     }
-    // the new residual of any row of the block, formed as for the row itself
-    auto r_at = [&](int64_t q) { return Rin[q * kC + col] - a * Q[q * kC + col]; };
-    const double r = ri - a * qi;
-    const double z = var_precond(M, i, r, r_at);
-    W[e] = wi + a * pi;
-    Rout[e] = r;
-    Z[e] = z;
-    v[0] += r * z;
-    v[1] += r * r;
+    __syncthreads();  // the previous tile has been read
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int64_t i = lo + threadIdx.x / kC + u * kRRows;
+      if (i < hi) {
+        const double r = rv[u] - a * qv[u];
+        R[i * kC + col] = r;
+        rt[i - lo][col] = r;
+      }
+    }
+    __syncthreads();
+    tile_precond(M, lo, hi, rt, [&](int64_t i, double r, double z) {
+      Z[i * kC + col] = z;
+      v[0] += r * z;
+      v[1] += r * r;
+    });
   }
   col_partials<2>(v, part);
+}
+
+// The same pass with the block product on the matrix cores, for larger blocks
+// (kBigBlock): Z[block, 0:32] = Binv R[block, 0:32], b x b times b x 32, is a
+// dense contraction, and with 16 x 16 x 4 FP64 MFMAs a wave loads each inverse
+// entry once for 32 columns instead of once per row and half-wave (broadcast
+// loads, which the address unit serves no faster than scattered ones).  A wave
+// takes the tile's blocks in turn; lane (i, kk) = (lane % 16, lane / 16) holds
+// A[i][kk] = Binv(16 rb + i, 4 s + kk), B[kk][i] = R(4 s + kk, i) from LDS, and
+// of the result the rows 16 rb + kk + 4 v, v = 0..3, of columns i and i + 16.
+// Entries past the block have weight 0.
+// Vector work of an iteration, n = 50,021 (mixture, blocks up to 32): 104.3 us with
+// each row reading its block's R and Q from memory, 65.4 with k_bcg_update, 54.1
+// with this; small blocks only pay the padding (space-time n = 109,500, 2.8 points a
+// block: 97.4 with k_bcg_update, 108.9 with this), so it takes mean blocks of more
+// than kBigBlock rows (uniform n = 8000, mean 7.6: 26.2 and 25.3).
+typedef double d4 __attribute__((ext_vector_type(4)));
+constexpr int kMThreads = 256;
+constexpr int kMWaves = kMThreads / kWave;
+constexpr int kMSteps = kMaxBlock / 4;  // k-steps of a block at most
+constexpr int kBigBlock = 8;
+
+__global__ void __launch_bounds__(kMThreads) k_bcg_update_mfma(int64_t n, const BcgScalars* __restrict__ S,
+                                                               const double* __restrict__ Q, VarPrecond M,
+                                                               double* __restrict__ R, double* __restrict__ Z,
+                                                               double* __restrict__ part) {
+  __shared__ double rt[kTileMax][kC];
+  __shared__ double red[2][kMWaves][kC];
+  constexpr int kTRows = kMThreads / kC;
+  constexpr int kPer = (kTileMax + kTRows - 1) / kTRows;
+  const int col = threadIdx.x % kC, w = threadIdx.x / kWave, lane = lane_id();
+  const int i = lane & 15, kk = lane >> 4;
+  const double a = S->alpha[col];
+  double rz[2] = {0.0, 0.0}, rr[2] = {0.0, 0.0};  // of columns i and i + 16
+  for (int64_t k = blockIdx.x; k * kTile < n; k += gridDim.x) {
+    const int64_t lo = tile_start(M, n, k), hi = tile_start(M, n, k + 1);
+    double rv[kPer], qv[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int64_t r = lo + threadIdx.x / kC + u * kTRows;
+      rv[u] = r < hi ? R[r * kC + col] : 0.0;
+      qv[u] = r < hi ? Q[r * kC + col] : 0.0;
+    }
+    // the tile's Jacobi blocks: lane j holds block b0 + j (a tile has at most kTileMax)
+    const int b0 = lo < hi ? M.rowblk[lo] : 0, nb = lo < hi ? M.rowblk[hi - 1] - b0 + 1 : 0;
+    __syncthreads();  // the previous tile has been read
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int64_t r = lo + threadIdx.x / kC + u * kTRows;
+      if (r < hi) {
+        const double x = rv[u] - a * qv[u];
+        R[r * kC + col] = x;
+        rt[r - lo][col] = x;
+      }
+    }
+    __syncthreads();
+    for (int j = w; j < nb; j += kMWaves) {  // uniform over the wave
+      const int32_t bs = M.bstart[b0 + j];
+      const int sz = M.bstart[b0 + j + 1] - bs;
+      const double* binv = M.binv + M.boff[b0 + j];
+      const double(*rb)[kC] = rt + (bs - lo);
+      d4 acc[2][2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) acc[t][c] = d4{0.0, 0.0, 0.0, 0.0};
+      double av[2][kMSteps];
+#pragma unroll
+      for (int s = 0; s < kMSteps; ++s) {
+        if (4 * s >= sz) break;  // uniform
+        const int q = 4 * s + kk;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const int r = 16 * t + i;
+          av[t][s] = (q < sz && r < sz) ? binv[q * sz + r] : 0.0;
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < kMSteps; ++s) {
+        if (4 * s >= sz) break;
+        const int q = min(4 * s + kk, sz - 1);
+        const double bl = rb[q][i], bh = rb[q][i + 16];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          if (16 * t >= sz) break;
+          acc[t][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[t][s], bl, acc[t][0], 0, 0, 0);
+          acc[t][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[t][s], bh, acc[t][1], 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = 16 * t + kk + 4 * v;
+          if (r >= sz) continue;
+          double* zr = Z + (bs + r) * static_cast<int64_t>(kC);
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            const double x = rb[r][i + 16 * c], z = acc[t][c][v];
+            zr[i + 16 * c] = z;
+            rz[c] += x * z;
+            rr[c] += x * x;
+          }
+        }
+    }
+  }
+  // the four lanes of a column, then the waves in order
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+#pragma unroll
+    for (int off = 16; off < kWave; off <<= 1) {
+      rz[c] += __shfl_xor(rz[c], off, kWave);
+      rr[c] += __shfl_xor(rr[c], off, kWave);
+    }
+    if (kk == 0) {
+      red[0][w][i + 16 * c] = rz[c];
+      red[1][w][i + 16 * c] = rr[c];
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < 2 * kC) {
+    const int v = threadIdx.x / kC;
+    double s = 0.0;
+#pragma unroll
+    for (int q = 0; q < kMWaves; ++q) s += red[v][q][col];
+    part[(static_cast<int64_t>(blockIdx.x) * 2 + v) * kC + col] = s;
+  }
 }
 
 __global__ void __launch_bounds__(kFinThreads) k_bcg_beta(const double* __restrict__ part, int nb,
                                                           BcgScalars* __restrict__ S, double tol2) {
   double t[2];
-  col_totals<2>(part, nb, t);
+  col_totals2(part, nb, t);
   if (threadIdx.x >= kC) return;
   const int col = threadIdx.x;
   const double rz = t[0], rr = t[1];
@@ -394,20 +594,24 @@ __global__ void __launch_bounds__(kFinThreads) k_bcg_beta(const double* __restri
   S->active[col] = (act && rr > tol2 * S->cc[col]) ? 1 : 0;
 }
 
-// P = Z + beta P for the active columns
+// W += alpha P, and P = Z + beta P for the active columns (a row per thread)
 __global__ void __launch_bounds__(kThreads) k_bcg_dir(int64_t n, const BcgScalars* __restrict__ S,
-                                                      const double* __restrict__ Z, double* __restrict__ P) {
+                                                      const double* __restrict__ Z, double* __restrict__ P,
+                                                      double* __restrict__ W) {
   const int col = threadIdx.x % kC;
-  if (!S->active[col]) return;  // the whole column; no block-level synchronisation follows
-  const double b = S->beta[col];
-  ROW_LOOP(n) {
-    const int64_t e = i * kC + col;
-    P[e] = Z[e] + b * P[e];
-  }
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * kRowsPer + threadIdx.x / kC;
+  if (i >= n) return;
+  const double a = S->alpha[col], b = S->beta[col];
+  const bool act = S->active[col] != 0;
+  if (a == 0.0 && !act) return;  // a column that ended earlier
+  const int64_t e = i * kC + col;
+  const double p = P[e], w = W[e], z = act ? Z[e] : 0.0;
+  W[e] = w + a * p;
+  if (act) P[e] = z + b * p;
 }
 
 // partials of the true residual |X - KW|^2 and of X.W per column
-__global__ void __launch_bounds__(kThreads) k_bcg_final(int64_t n, const double* __restrict__ X,
+__global__ void __launch_bounds__(kRThreads) k_bcg_final(int64_t n, const double* __restrict__ X,
                                                         const double* __restrict__ kw, const double* __restrict__ W,
                                                         double* __restrict__ part) {
   const int col = threadIdx.x % kC;
@@ -426,7 +630,7 @@ __global__ void __launch_bounds__(kFinThreads) k_bcg_var(const double* __restric
                                                          BcgScalars* __restrict__ S, const double* __restrict__ prior,
                                                          int nbatch, double* __restrict__ var) {
   double t[2];
-  col_totals<2>(part, nb, t);
+  col_totals2(part, nb, t);
   if (threadIdx.x >= kC) return;
   const int col = threadIdx.x;
   const double rr = t[0], cw = t[1];
@@ -507,17 +711,19 @@ VarResult predict_variance(gp_ctx* c, const gp_matrix* m, const gp_theta* th, in
   const size_t blk = sizeof(double) * n * kC;
   double* X = static_cast<double*>(workspace(c, 110, blk));
   double* R = static_cast<double*>(workspace(c, 111, blk));
-  double* R2 = static_cast<double*>(workspace(c, 119, blk));  // the residual alternates between R and R2
   double* Z = static_cast<double*>(workspace(c, 112, blk));
   double* P = static_cast<double*>(workspace(c, 113, blk));
   double* Q = static_cast<double*>(workspace(c, 114, blk));
   double* W = static_cast<double*>(workspace(c, 115, blk));
-  double* part = static_cast<double*>(workspace(c, 116, sizeof(double) * kVBlocks * 2 * kC));
+  double* part = static_cast<double*>(workspace(c, 116, sizeof(double) * 2 * kVBlocks * 2 * kC));
   BcgScalars* S = static_cast<BcgScalars*>(workspace(c, 117, sizeof(BcgScalars)));
   double* prior = static_cast<double*>(workspace(c, 118, sizeof(double) * kC));
   BcgScalars* hs = static_cast<BcgScalars*>(pinned(c, sizeof(BcgScalars)));
-  const unsigned nbv = static_cast<unsigned>(std::min<int64_t>(kVBlocks, (n + kRowsPer - 1) / kRowsPer));
-  const dim3 B(kThreads), G(nbv), FB(kFinThreads);
+  const unsigned nbv = static_cast<unsigned>(std::min<int64_t>(kVBlocks, (n + kTile - 1) / kTile));
+  // the matrix-core update pays for padding to 16 rows: see kBigBlock
+  const bool mfma = M.binv && m->binv_len > kBigBlock * n;  // sum of b^2 over sum of b: the block a row sees on average
+  const unsigned nbm = static_cast<unsigned>(std::min<int64_t>(2 * kVBlocks, (n + kTile - 1) / kTile));
+  const dim3 B(kThreads), RB(kRThreads), G(nbv), GM(nbm), FB(kFinThreads);
   // element-wise kernels without a reduction take a row per thread
   const dim3 Gfull(static_cast<unsigned>((n + kRowsPer - 1) / kRowsPer));
   const double tol2 = rtol * rtol;
@@ -542,7 +748,7 @@ VarResult predict_variance(gp_ctx* c, const gp_matrix* m, const gp_theta* th, in
       check_launch("variance cross-covariance");
     }
     hipLaunchKernelGGL(k_zero, dim3(grid_for(n * kC, kThreads)), B, 0, c->stream, n * kC, W);
-    hipLaunchKernelGGL(k_bcg_start, G, B, 0, c->stream, n, X, nullptr, M, R, Z, P, part);
+    hipLaunchKernelGGL(k_bcg_start, G, RB, 0, c->stream, n, X, nullptr, M, R, Z, P, part);
     hipLaunchKernelGGL(k_bcg_start_fin, dim3(1), FB, 0, c->stream, part, static_cast<int>(nbv), S, tol2, 0);
     check_launch("variance start");
     BcgScalars hsc = read();
@@ -557,7 +763,7 @@ VarResult predict_variance(gp_ctx* c, const gp_matrix* m, const gp_theta* th, in
         // recurrences done: check the float64 true residual, restart once it is not small enough
         if (refresh >= kMaxRefresh) break;
         spmm<double>(c, m, kC, kC, W, Q, nullptr);
-        hipLaunchKernelGGL(k_bcg_start, G, B, 0, c->stream, n, X, Q, M, R, Z, P, part);
+        hipLaunchKernelGGL(k_bcg_start, G, RB, 0, c->stream, n, X, Q, M, R, Z, P, part);
         hipLaunchKernelGGL(k_bcg_start_fin, dim3(1), FB, 0, c->stream, part, static_cast<int>(nbv), S, tol2, 1);
         check_launch("variance restart");
         ++refresh;
@@ -569,12 +775,14 @@ VarResult predict_variance(gp_ctx* c, const gp_matrix* m, const gp_theta* th, in
       for (int t = 0; t < steps; ++t) {
         spmm<double>(c, m, kC, kC, P, Q, nullptr);
         ProfScope ps(c, "var_vector_ops");
-        hipLaunchKernelGGL(k_bcg_pq, G, B, 0, c->stream, n, P, Q, part);
+        hipLaunchKernelGGL(k_bcg_pq, G, RB, 0, c->stream, n, P, Q, part);
         hipLaunchKernelGGL(k_bcg_alpha, dim3(1), FB, 0, c->stream, part, static_cast<int>(nbv), S);
-        hipLaunchKernelGGL(k_bcg_update, G, B, 0, c->stream, n, S, P, Q, M, W, R, R2, Z, part);
-        std::swap(R, R2);
-        hipLaunchKernelGGL(k_bcg_beta, dim3(1), FB, 0, c->stream, part, static_cast<int>(nbv), S, tol2);
-        hipLaunchKernelGGL(k_bcg_dir, Gfull, B, 0, c->stream, n, S, Z, P);
+        if (mfma)
+          hipLaunchKernelGGL(k_bcg_update_mfma, GM, B, 0, c->stream, n, S, Q, M, R, Z, part);
+        else
+          hipLaunchKernelGGL(k_bcg_update, G, RB, 0, c->stream, n, S, Q, M, R, Z, part);
+        hipLaunchKernelGGL(k_bcg_beta, dim3(1), FB, 0, c->stream, part, static_cast<int>(mfma ? nbm : nbv), S, tol2);
+        hipLaunchKernelGGL(k_bcg_dir, Gfull, B, 0, c->stream, n, S, Z, P, W);
         check_launch("variance step");
       }
       it += steps;
@@ -582,7 +790,7 @@ VarResult predict_variance(gp_ctx* c, const gp_matrix* m, const gp_theta* th, in
     }
     // true residual and the variances of this batch
     spmm<double>(c, m, kC, kC, W, Q, nullptr);
-    hipLaunchKernelGGL(k_bcg_final, G, B, 0, c->stream, n, X, Q, W, part);
+    hipLaunchKernelGGL(k_bcg_final, G, RB, 0, c->stream, n, X, Q, W, part);
     hipLaunchKernelGGL(k_bcg_var, dim3(1), FB, 0, c->stream, part, static_cast<int>(nbv), S, prior, nb, var + m0);
     check_launch("variance final");
     hsc = read();
