@@ -685,10 +685,13 @@ Grid make_grid(const gp_dataset* ds, const gp_theta* th) {
       const double need = th->r0[k] * (1.0 + 1e-9) / ds->cell[k];
       double R = std::ceil(need);
       if (R < 1) R = 1;
+      // beyond the grid there is nothing: its own points need no more rings than
+      // it has cells, while a point outside reaches it from further away
+      g.Rt[k] = static_cast<int32_t>(std::min(R, 1.0e9));
       if (R > ds->g[k]) R = ds->g[k];
       g.R[k] = static_cast<int32_t>(R);
     } else {
-      g.R[k] = 0;
+      g.R[k] = g.Rt[k] = 0;
     }
   }
   return g;

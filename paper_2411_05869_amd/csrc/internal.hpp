@@ -197,7 +197,8 @@ struct Grid {
   double inv_cell[3];   // unused by decisions on pattern membership
   double cell[3];
   int32_t g[3];
-  int32_t R[3];         // neighbour rings per coordinate
+  int32_t R[3];         // neighbour rings per coordinate, for points of the dataset
+  int32_t Rt[3];        // the same for any point (a test point may lie outside the grid)
 };
 
 // Per-theta point features (binned order).

@@ -594,7 +594,7 @@ static PredArgs pred_args(const gp_predictor* p) {
     a.lo[k] = ds->lo[k];
     a.cell[k] = ds->cell[k];
     a.g[k] = ds->g[k];
-    a.R[k] = p->grid.R[k];
+    a.R[k] = p->grid.Rt[k];
   }
   a.alpha = p->alpha_b;
   a.pack = p->pack;

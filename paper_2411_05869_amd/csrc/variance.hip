@@ -701,7 +701,7 @@ VarResult predict_variance(gp_ctx* c, const gp_matrix* m, const gp_theta* th, in
     a.lo[k] = ds->lo[k];
     a.cell[k] = ds->cell[k];
     a.g[k] = ds->g[k];
-    a.R[k] = grid.R[k];
+    a.R[k] = grid.Rt[k];
   }
   a.nm = f.nm;
   a.mlist = f.mlist;
