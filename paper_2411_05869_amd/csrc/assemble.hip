@@ -378,6 +378,92 @@ __global__ void __launch_bounds__(kThreads) k_local_rows(AsmArgs a) {
   }
 }
 
+// The same rows with kSplit lanes each, for data sets whose rows do not fill the
+// chip (split_rows): at n = 30,011 one row per lane is 469 waves on 1024 SIMDs,
+// and the rows of a dense cluster walk several hundred candidates one after
+// another.  The lanes take kSplit consecutive candidates of a pencil at a time
+// (two such groups requested together); a ballot gives each hit its place in the
+// row, so the entries are those of k_local_rows in the same order, and
+// neighbouring hits are stored by neighbouring lanes.
+constexpr int kSplit = 8;
+
+template <int D, bool FILL, typename VT, int CK = 0>
+__global__ void __launch_bounds__(kThreads) k_local_rows_split(AsmArgs a) {
+  const int64_t p = (xcd_remap(blockIdx.x, gridDim.x) * static_cast<int64_t>(kThreads) + threadIdx.x) / kSplit;
+  if (p >= a.n) return;  // all lanes of the row
+  const int sub = threadIdx.x % kSplit, shift = lane_id() & ~(kSplit - 1);
+  const uint64_t mp = a.mask[p];
+  const int64_t out = FILL ? a.row_ptr[p] + (mp ? a.gskip[p] : 0) : 0;
+  const int64_t len = FILL ? a.row_ptr[p + 1] - out : 0;
+  double xp[3] = {0, 0, 0};
+  load_point<D>(a.xb, a.n, p, xp);
+  int c[3];
+  decode_key(a.key[p], a.g, c);
+  const Window w = make_window<D>(a, c);
+  double sp = 0.0, Sp = 0.0;
+  if constexpr (CK == 2) {
+    sp = a.kt.core.sig[p];
+    Sp = a.kt.core.Sig[p];
+  }
+  int32_t cnt = 0;
+  VT* val = static_cast<VT*>(a.val);
+  constexpr int kU = 2;
+  for (int z = w.z0; z <= w.z1; ++z)
+    for (int y = w.y0; y <= w.y1; ++y) {
+      const int64_t base = (static_cast<int64_t>(z) * a.g[1] + y) * a.g[0];
+      const int32_t s = a.cell_start[base + w.x0], e = a.cell_start[base + w.x1 + 1];
+      for (int32_t q0 = s; q0 < e; q0 += kSplit * kU) {
+        double xq[kU][3];
+        uint64_t mq[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          const int32_t q = min(q0 + u * kSplit + sub, e - 1);
+          load_point<D>(a.xb, a.n, q, xq[u]);
+          mq[u] = mp ? a.mask[q] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          const int32_t q = q0 + u * kSplit + sub;
+          const double u2 = scaled_sq<D>(xp, xq[u], a.kt.inv0);
+          const bool hit = q < e && u2 < 1.0 && (mq[u] & mp) == 0;
+          const uint32_t bits = static_cast<uint32_t>(__ballot(hit) >> shift) & ((1u << kSplit) - 1);
+          if constexpr (FILL) {
+            const int32_t pos = cnt + __popc(bits & ((1u << sub) - 1));
+            if (hit && pos < len) {  // never past the counted row
+              double cv = 1.0;
+              if constexpr (CK == 1) cv = core_value<D, 1>(a.kt.core, xp, xq[u], 0.0, 0.0, 0.0, 0.0);
+              if constexpr (CK == 2)
+                cv = core_value<D, 2>(a.kt.core, xp, xq[u], sp, Sp, a.kt.core.sig[q], a.kt.core.Sig[q]);
+              const VT vs = static_cast<VT>(entry_value(a.kt, u2, 0, nullptr, nullptr, q == p, 1, 1, cv, p));
+              a.col[out + pos] = q;
+              val[out + pos] = vs;
+              if (q == p) a.diag[p] = static_cast<double>(vs);
+            }
+          }
+          cnt += __popc(bits);
+        }
+      }
+    }
+  if (sub != 0) return;
+  if constexpr (!FILL) {
+    a.counts[p] = cnt;
+    if (mp == 0) a.gskip[p] = 0;
+  } else if (static_cast<int64_t>(cnt) != len) {
+    atomicOr(a.err, 1);
+  }
+}
+
+// Rows up to which a local pass splits its rows over kSplit lanes.  Beyond, one
+// row per lane does less work (its candidates are staged in LDS once for 64
+// rows); with few dimensions the pencils are few and long, and the split
+// pays longer, as it does for the fill, whose stores it makes consecutive.
+// Lane per row -> split, us:
+//   d = 2, mixture, count: n = 30,011 62.9 -> 16.2, 100,003 84.4 -> 36.1, 500,003 118.9 -> 137.8
+//                   fill: 183.8 -> 32.7, 230.9 -> 72.5, 354.6 -> 259.3 (uniform n = 300,000 63.5 -> 62.6)
+//   d = 3, count: n = 60,000 39.4 -> 30.1, 109,500 71.8 -> 75.9, 365,000 111.5 -> 212.9
+//          fill: 64.5 -> 38.3, 111.6 -> 85.7, 240.9 -> 252.2
+constexpr int64_t split_rows(int d, bool fill) { return int64_t(d == 3 ? 65536 : 131072) << (fill ? 1 : 0); }
+
 // Rows with a group bit: |U_M| group entries come first in the row.
 __global__ void __launch_bounds__(kThreads) k_group_counts(int64_t nm, const int32_t* __restrict__ mlist,
                                                            const int32_t* __restrict__ did,
@@ -503,24 +589,29 @@ __global__ void __launch_bounds__(kThreads) k_group_tile_fill(AsmArgs a, const i
 }
 
 // long rows of the CSR part outside the group blocks (lengths without the
-// leading group entries); also the longest full row
+// leading group entries); also the longest full row.  A few hundred blocks
+// stride over the rows, and a block raises the maximum only where its own is
+// larger than the one it reads: one atomic on the same word per 256 rows took
+// 51 us at n = 1,095,000, now 9.
+constexpr unsigned kFlagBlocks = 512;
+
 __global__ void __launch_bounds__(kThreads) k_long_flags(int64_t n, const int32_t* __restrict__ counts,
                                                          const int32_t* __restrict__ gskip,
                                                          int32_t* __restrict__ flag, int32_t* __restrict__ maxrow) {
-  const int64_t p = blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x;
-  int32_t c = 0;
-  if (p < n) {
-    c = counts[p];
+  int32_t m = 0;
+  for (int64_t p = blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x; p < n;
+       p += static_cast<int64_t>(gridDim.x) * kThreads) {
+    const int32_t c = counts[p];
     flag[p] = (c - gskip[p]) > kLongRow ? 1 : 0;
+    m = max(m, c);
   }
-  for (int off = kWave / 2; off > 0; off >>= 1) c = max(c, __shfl_xor(c, off, kWave));
+  for (int off = kWave / 2; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off, kWave));
   __shared__ int32_t wmax[kThreads / kWave];
-  if (lane_id() == 0) wmax[threadIdx.x / kWave] = c;
+  if (lane_id() == 0) wmax[threadIdx.x / kWave] = m;
   __syncthreads();
   if (threadIdx.x == 0) {
-    int32_t m = wmax[0];
     for (int i = 1; i < kThreads / kWave; ++i) m = max(m, wmax[i]);
-    atomicMax(maxrow, m);
+    if (m > __hip_atomic_load(maxrow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(maxrow, m);
   }
 }
 
@@ -861,8 +952,12 @@ gp_matrix* assemble(gp_ctx* c, const gp_dataset* ds, const gp_theta* th, int pre
   dispatch_d(d, [&](auto DD) {
     constexpr int D = decltype(DD)::value;
     ProfScope ps(c, "asm_count_local");
-    hipLaunchKernelGGL((k_local_rows<D, false, double>), dim3(grid_for(n, kThreads)), dim3(kThreads), 0, c->stream,
-                       a);
+    if (n <= split_rows(D, false))
+      hipLaunchKernelGGL((k_local_rows_split<D, false, double>), dim3(grid_for(n * kSplit, kThreads)), dim3(kThreads),
+                         0, c->stream, a);
+    else
+      hipLaunchKernelGGL((k_local_rows<D, false, double>), dim3(grid_for(n, kThreads)), dim3(kThreads), 0, c->stream,
+                         a);
   });
   check_launch("count local");
   std::vector<uint64_t> dmask;
@@ -999,8 +1094,8 @@ gp_matrix* assemble(gp_ctx* c, const gp_dataset* ds, const gp_theta* th, int pre
     ProfScope ps(c, "asm_scan");
     scan_i32_to_i64(c, a.counts, m->row_ptr, n);
     GPS_HIP(hipMemsetAsync(maxrow, 0, sizeof(int32_t), c->stream));
-    hipLaunchKernelGGL(k_long_flags, dim3(grid_for(n, kThreads)), dim3(kThreads), 0, c->stream, n, a.counts,
-                       m->gskip, lflag, maxrow);
+    hipLaunchKernelGGL(k_long_flags, dim3(std::min(grid_for(n, kThreads), kFlagBlocks)), dim3(kThreads), 0, c->stream,
+                       n, a.counts, m->gskip, lflag, maxrow);
     check_launch("long flags");
     scan_i32_to_i32(c, lflag, lpos, n);
   }
@@ -1067,8 +1162,12 @@ gp_matrix* assemble(gp_ctx* c, const gp_dataset* ds, const gp_theta* th, int pre
         constexpr int CK = decltype(CC)::value;
         {
           ProfScope ps(c, "asm_fill_local");
-          hipLaunchKernelGGL((k_local_rows<D, true, VT, CK>), dim3(grid_for(n, kThreads)), dim3(kThreads), 0,
-                             c->stream, a);
+          if (n <= split_rows(D, true))
+            hipLaunchKernelGGL((k_local_rows_split<D, true, VT, CK>), dim3(grid_for(n * kSplit, kThreads)),
+                               dim3(kThreads), 0, c->stream, a);
+          else
+            hipLaunchKernelGGL((k_local_rows<D, true, VT, CK>), dim3(grid_for(n, kThreads)), dim3(kThreads), 0,
+                               c->stream, a);
         }
         if (ntiles > 0) {
           ProfScope ps(c, "asm_fill_group");

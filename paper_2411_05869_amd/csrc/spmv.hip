@@ -556,22 +556,44 @@ __global__ void __launch_bounds__(kThreads) k_spmv_one(int64_t n, unsigned ntile
   }
 }
 
-// offsets col - row of the CSR part (flag 1 when one does not fit in int16)
+// offsets col - row of the CSR part (flag 1 when one does not fit in int16);
+// kG lanes per row, four consecutive entries each, as in the product
 __global__ void __launch_bounds__(kThreads) k_col16(int64_t n, const int64_t* __restrict__ rp,
                                                     const int32_t* __restrict__ gskip, const int32_t* __restrict__ col,
                                                     int16_t* __restrict__ off, int* __restrict__ err) {
-  // kG lanes per row, as in the product, so consecutive lanes touch consecutive entries
-  const int64_t t = blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x;
-  const int64_t row = t / kG;
+  const unsigned b = xcd_remap(blockIdx.x, gridDim.x);
+  const int64_t row = (b * static_cast<int64_t>(kThreads) + threadIdx.x) / kG;
   if (row >= n) return;
-  for (int64_t j = rp[row] + gskip[row] + (t & (kG - 1)); j < rp[row + 1]; j += kG) {
-    const int64_t d = static_cast<int64_t>(col[j]) - row;
-    if (d < -32768 || d > 32767) {
-      atomicOr(err, 1);
-      return;
+  const int32_t self = static_cast<int32_t>(row);
+  const int64_t s = rp[row] + gskip[row], e = rp[row + 1];
+  bool bad = false;
+  auto put = [&](const int32_t* c, int64_t j) {
+    int16_t o[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int32_t d = c[u] - self;
+      if (j + u < e) bad = bad || d < -32768 || d > 32767;
+      o[u] = static_cast<int16_t>(d);
     }
-    off[j] = static_cast<int16_t>(d);
+    if (j + 4 <= e) {
+      __builtin_memcpy(off + j, o, sizeof(o));
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (j + u < e) off[j + u] = o[u];
+    }
+  };
+  constexpr int kB = 2;  // groups of four requested at once (rows of up to 64 entries: all)
+  for (int64_t j0 = s + 4 * (threadIdx.x & (kG - 1)); j0 < e; j0 += 4 * kG * kB) {
+    int32_t c[kB][4];
+#pragma unroll
+    for (int h = 0; h < kB; ++h)
+      if (j0 + 4 * kG * h < e) __builtin_memcpy(c[h], col + j0 + 4 * kG * h, sizeof(c[h]));
+#pragma unroll
+    for (int h = 0; h < kB; ++h)
+      if (j0 + 4 * kG * h < e) put(c[h], j0 + 4 * kG * h);
   }
+  if (bad) atomicOr(err, 1);
 }
 
 // Entries up to which the product takes one launch.  Two launches -> one, per
