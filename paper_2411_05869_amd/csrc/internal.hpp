@@ -174,12 +174,12 @@ struct gp_matrix {
   // each (mask id, first index in g_rows, rows, first U_M entry): a piece is
   // a super-tile's rows times at most kPiece consecutive entries of U_M
   int32_t* g_tiles = nullptr;
-  // block-Jacobi preconditioner, built on first use (blocks = binning cells)
-  int64_t nblk = 0, binv_len = 0;
-  int32_t* bstart = nullptr;    // nblk + 1 block starts (binned rows)
-  int32_t* rowblk = nullptr;    // n, block of each row
-  int64_t* boff = nullptr;      // nblk + 1 offsets into binv
-  double* binv = nullptr;       // inverses of the diagonal blocks, entry (i, j) of a block of b rows at j * b + i
+  // block-Jacobi preconditioner, built on first use (blocks = binning cells):
+  // the inverses of the diagonal blocks, entry (i, j) of a block of b rows at its
+  // start + j * b + i, and per row where its entries lie (BlockRow)
+  int64_t binv_len = 0;
+  double* binv = nullptr;
+  uint64_t* brow = nullptr;     // n
   size_t bytes = 0;
 };
 

@@ -107,20 +107,17 @@ __device__ __forceinline__ bool seg_skip(const int* skip) {
 // otherwise point Jacobi with the matrix diagonal).
 struct Precond {
   const double* diag;
-  const int32_t* rowblk;
-  const int32_t* bstart;
-  const int64_t* boff;
+  const uint64_t* brow;
   const double* binv;
 };
 
 __device__ __forceinline__ double precond_row(const Precond& M, const double* __restrict__ r, int64_t i) {
   if (!M.binv) return r[i] / M.diag[i];
-  const int32_t b = M.rowblk[i];
-  const int32_t bs = M.bstart[b];
-  const int sz = M.bstart[b + 1] - bs;
-  const double* row = M.binv + M.boff[b] + (i - bs);
+  const BlockRow br(M.brow[i]);
+  const double* row = M.binv + br.pos;
+  const double* rb = r + (i - br.k);
   double z = 0.0;
-  for (int j = 0; j < sz; ++j) z += row[j * sz] * r[bs + j];
+  for (int j = 0; j < br.sz; ++j) z += row[j * br.sz] * rb[j];
   return z;
 }
 
@@ -176,18 +173,17 @@ __global__ void __launch_bounds__(kStepThreads) k_pcg_step(int64_t n, Precond M,
   double xv = 0, pv = 0, rv = 0, qv = 0, dv = 1;
   double w[PRE];
   const double* bcol = nullptr;
-  int32_t bs = 0;
-  int sz = 0;
+  int k = 0, sz = 0;
   if (i < e) {
     xv = x[i];
     pv = p[i];
     rv = r[i];
     qv = static_cast<double>(q[i]);
     if (M.binv) {
-      const int32_t b = M.rowblk[i];
-      bs = M.bstart[b];
-      sz = M.bstart[b + 1] - bs;
-      bcol = M.binv + M.boff[b] + (i - bs);
+      const BlockRow br(M.brow[i]);
+      k = br.k;
+      sz = br.sz;
+      bcol = M.binv + br.pos;
 #pragma unroll
       for (int j = 0; j < PRE; ++j)
         if (j < sz) w[j] = bcol[j * sz];
@@ -221,7 +217,7 @@ __global__ void __launch_bounds__(kStepThreads) k_pcg_step(int64_t n, Precond M,
     x[i] = xv + alpha * pv;
     if (M.binv) {
       // z_i = sum_j binv[i][j] rn_j over the block, j ascending
-      const double* rb = sr + (kHalo + (bs - b0));
+      const double* rb = sr + (kHalo + t - k);
 #pragma unroll
       for (int j = 0; j < PRE; ++j)
         if (j < sz) zi += w[j] * rb[j];
@@ -969,11 +965,9 @@ static double logsum_f64(gp_ctx* c, const double* a, int64_t n) {
 SolveResult pcg_solve(gp_ctx* c, gp_matrix* m, const double* y, double* x, double rtol, int max_iter, int precond) {
   const int64_t n = m->n;
   if (precond == GP_PRECOND_BLOCK_JACOBI) build_block_jacobi(c, m);
-  Precond M{m->diag, nullptr, nullptr, nullptr, nullptr};
+  Precond M{m->diag, nullptr, nullptr};
   if (precond == GP_PRECOND_BLOCK_JACOBI) {
-    M.rowblk = m->rowblk;
-    M.bstart = m->bstart;
-    M.boff = m->boff;
+    M.brow = m->brow;
     M.binv = m->binv;
   }
   // the residual alternates between two buffers: a step reads one and writes the other
@@ -1194,11 +1188,9 @@ __global__ void __launch_bounds__(kCtlThreads) k_ctl_relres(const CgScalars* __r
 static void pcg_device_impl(gp_ctx* c, gp_matrix* m, const double* y, double* x, double rtol, int max_iter,
                             int precond, int R, const int64_t* off, int64_t nmax, bool poll, DeviceSolve* out) {
   const int64_t n = m->n;
-  Precond M{m->diag, nullptr, nullptr, nullptr, nullptr};
+  Precond M{m->diag, nullptr, nullptr};
   if (precond == GP_PRECOND_BLOCK_JACOBI) {
-    M.rowblk = m->rowblk;
-    M.bstart = m->bstart;
-    M.boff = m->boff;
+    M.brow = m->brow;
     M.binv = m->binv;
   }
   const bool batch = off != nullptr;
@@ -1384,12 +1376,11 @@ __global__ void __launch_bounds__(kThreads) k_mr_lanczos(int64_t n, Precond M, c
     if (!M.binv) {
       zi = ri / M.diag[i];
     } else {
-      const int32_t b = M.rowblk[i];
-      const int32_t bs = M.bstart[b];
-      const int sz = M.bstart[b + 1] - bs;
-      const double* row = M.binv + M.boff[b] + (i - bs);
+      const BlockRow br(M.brow[i]);
+      const double* row = M.binv + br.pos;
+      const int64_t bs = i - br.k;
       zi = 0.0;
-      for (int j = 0; j < sz; ++j) zi += row[j * sz] * mr_next(s, f, q, r1, r2, bs + j);
+      for (int j = 0; j < br.sz; ++j) zi += row[j * br.sz] * mr_next(s, f, q, r1, r2, bs + j);
     }
     rn[i] = ri;
     z[i] = zi;
@@ -1444,11 +1435,9 @@ SolveResult minres_solve(gp_ctx* c, gp_matrix* m, const double* y, double* x, bo
                          int precond) {
   const int64_t n = m->n;
   if (precond == GP_PRECOND_BLOCK_JACOBI) build_block_jacobi(c, m);
-  Precond M{m->diag, nullptr, nullptr, nullptr, nullptr};
+  Precond M{m->diag, nullptr, nullptr};
   if (precond == GP_PRECOND_BLOCK_JACOBI) {
-    M.rowblk = m->rowblk;
-    M.bstart = m->bstart;
-    M.boff = m->boff;
+    M.brow = m->brow;
     M.binv = m->binv;
   }
   double* buf[8];

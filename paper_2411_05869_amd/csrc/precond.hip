@@ -33,14 +33,23 @@ __global__ void __launch_bounds__(kThreads) k_block_flags(int64_t n, const int32
 
 __global__ void __launch_bounds__(kThreads) k_block_starts(int64_t n, const int32_t* __restrict__ flag,
                                                            const int32_t* __restrict__ pos,
-                                                           int32_t* __restrict__ bstart, int32_t* __restrict__ rowblk,
-                                                           int32_t* __restrict__ bsq) {
+                                                           int32_t* __restrict__ bstart) {
+  const int64_t p = blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x;
+  if (p < n && flag[p]) bstart[pos[p]] = static_cast<int32_t>(p);
+}
+
+// each row's place in the inverses (block of p: the last start at or before p)
+__global__ void __launch_bounds__(kThreads) k_block_rows(int64_t n, const int32_t* __restrict__ flag,
+                                                         const int32_t* __restrict__ pos,
+                                                         const int32_t* __restrict__ bstart,
+                                                         const int64_t* __restrict__ boff,
+                                                         uint64_t* __restrict__ brow) {
   const int64_t p = blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x;
   if (p >= n) return;
-  // block of p: the last start at or before p
   const int32_t b = pos[p] + flag[p] - 1;
-  rowblk[p] = b;
-  if (flag[p]) bstart[b] = static_cast<int32_t>(p);
+  const int32_t bs = bstart[b];
+  const int k = static_cast<int>(p - bs);
+  brow[p] = BlockRow::pack(boff[b] + k, bstart[b + 1] - bs, k);
 }
 
 __global__ void __launch_bounds__(kThreads) k_block_sizes(int64_t nblk, int64_t n, int32_t* __restrict__ bstart,
@@ -166,8 +175,9 @@ void build_block_jacobi(gp_ctx* c, gp_matrix* m) {
 static void build_block_jacobi_impl(gp_ctx* c, gp_matrix* m) {
   const gp_dataset* ds = m->ds;
   const int64_t n = m->n;
-  int32_t* flag = static_cast<int32_t*>(workspace(c, 70, sizeof(int32_t) * n));
-  int32_t* pos = static_cast<int32_t*>(workspace(c, 71, sizeof(int32_t) * (n + 1)));
+  // (the slots of the assembly's long-row flags, which are no longer needed)
+  int32_t* flag = static_cast<int32_t*>(workspace(c, 15, sizeof(int32_t) * n));
+  int32_t* pos = static_cast<int32_t*>(workspace(c, 16, sizeof(int32_t) * (n + 1)));
   hipLaunchKernelGGL(k_block_flags, dim3(grid_for(n, kThreads)), dim3(kThreads), 0, c->stream, n, ds->key,
                      ds->cell_start, flag);
   check_launch("block flags");
@@ -176,18 +186,20 @@ static void build_block_jacobi_impl(gp_ctx* c, gp_matrix* m) {
   GPS_HIP(hipMemcpyAsync(h, pos + n, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
   sync(c);
   const int64_t nblk = *h;
-  m->nblk = nblk;
-  m->bstart = dev_new<int32_t>(c, nblk + 1);
-  m->rowblk = dev_new<int32_t>(c, n);
-  m->boff = dev_new<int64_t>(c, nblk + 1);
+  TmpBuf bstart_buf(c, sizeof(int32_t) * (nblk + 1)), boff_buf(c, sizeof(int64_t) * (nblk + 1));
+  int32_t* bstart = bstart_buf.as<int32_t>();
+  int64_t* boff = boff_buf.as<int64_t>();
+  m->brow = dev_new<uint64_t>(c, n);
   int32_t* bsq = static_cast<int32_t*>(workspace(c, 72, sizeof(int32_t) * std::max<int64_t>(nblk, 1)));
-  hipLaunchKernelGGL(k_block_starts, dim3(grid_for(n, kThreads)), dim3(kThreads), 0, c->stream, n, flag, pos,
-                     m->bstart, m->rowblk, bsq);
-  hipLaunchKernelGGL(k_block_sizes, dim3(grid_for(nblk + 1, kThreads)), dim3(kThreads), 0, c->stream, nblk, n,
-                     m->bstart, bsq);
+  hipLaunchKernelGGL(k_block_starts, dim3(grid_for(n, kThreads)), dim3(kThreads), 0, c->stream, n, flag, pos, bstart);
+  hipLaunchKernelGGL(k_block_sizes, dim3(grid_for(nblk + 1, kThreads)), dim3(kThreads), 0, c->stream, nblk, n, bstart,
+                     bsq);
   check_launch("block sizes");
-  scan_i32_to_i64(c, bsq, m->boff, nblk);
-  const int64_t total = read_i64(c, m->boff + nblk);
+  scan_i32_to_i64(c, bsq, boff, nblk);
+  hipLaunchKernelGGL(k_block_rows, dim3(grid_for(n, kThreads)), dim3(kThreads), 0, c->stream, n, flag, pos, bstart,
+                     boff, m->brow);
+  check_launch("block rows");
+  const int64_t total = read_i64(c, boff + nblk);
   m->binv_len = total;
   m->binv = dev_new<double>(c, std::max<int64_t>(total, 1));
   GPS_HIP(hipMemsetAsync(c->err_flag, 0, sizeof(int), c->stream));
@@ -199,7 +211,7 @@ static void build_block_jacobi_impl(gp_ctx* c, gp_matrix* m) {
       auto one = [&](auto bsz) {
         constexpr int BS = decltype(bsz)::value;
         hipLaunchKernelGGL((k_block_invert<VT, BS>), dim3(grid_for(nblk * BS, kThreads)), dim3(kThreads), 0,
-                           c->stream, nblk, m->bstart, m->boff, m->row_ptr, m->gskip, m->col, val, m->binv,
+                           c->stream, nblk, bstart, boff, m->row_ptr, m->gskip, m->col, val, m->binv,
                            c->err_flag);
       };
       one(std::integral_constant<int, 4>{});
@@ -217,16 +229,13 @@ static void build_block_jacobi_impl(gp_ctx* c, gp_matrix* m) {
   GPS_HIP(hipMemcpyAsync(herr, c->err_flag, sizeof(int), hipMemcpyDeviceToHost, c->stream));
   sync(c);
   if (*herr) throw Error{GP_ENOTPD, "block-Jacobi setup met a non-positive pivot: matrix not positive definite"};
-  m->bytes += sizeof(int32_t) * (nblk + 1 + n) + sizeof(int64_t) * (nblk + 1) + sizeof(double) * total;
+  m->bytes += sizeof(uint64_t) * n + sizeof(double) * total;
 }
 
 void free_block_jacobi(gp_ctx* c, gp_matrix* m) {
-  if (m->bstart) dev_free(c, m->bstart, sizeof(int32_t) * (m->nblk + 1));
-  if (m->rowblk) dev_free(c, m->rowblk, sizeof(int32_t) * m->n);
-  if (m->boff) dev_free(c, m->boff, sizeof(int64_t) * (m->nblk + 1));
+  if (m->brow) dev_free(c, m->brow, sizeof(uint64_t) * m->n);
   if (m->binv) dev_free(c, m->binv, sizeof(double) * std::max<int64_t>(m->binv_len, 1));
-  m->bstart = m->rowblk = nullptr;
-  m->boff = nullptr;
+  m->brow = nullptr;
   m->binv = nullptr;
 }
 

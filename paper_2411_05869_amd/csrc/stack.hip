@@ -57,7 +57,6 @@ __global__ void __launch_bounds__(kThreads) k_stack(const Piece* __restrict__ pi
 
 // the closing entry of an offset array (its total)
 __global__ void k_put_i64(int64_t* __restrict__ p, int64_t v) { *p = v; }
-__global__ void k_put_i32(int32_t* __restrict__ p, int32_t v) { *p = v; }
 
 }  // namespace
 
@@ -73,7 +72,7 @@ gp_matrix* stack_matrices(gp_ctx* c, int R, const gp_matrix* const* ms, bool blo
   const size_t vbytes = prec == GP_MIXED ? sizeof(float) : sizeof(double);
   // offsets of every problem in every stacked array
   struct Off {
-    int64_t row, nnz, nlong, nD, utotal, nm, tiles, stiles, pieces, nblk, binv, trow, quads;
+    int64_t row, nnz, nlong, nD, utotal, nm, tiles, stiles, pieces, binv, trow, quads;
   };
   std::vector<Off> off(R + 1);
   off[0] = Off{};
@@ -90,7 +89,6 @@ gp_matrix* stack_matrices(gp_ctx* c, int R, const gp_matrix* const* ms, bool blo
     a.tiles = b.tiles + m->ntiles;
     a.stiles = b.stiles + m->nstiles;
     a.pieces = b.pieces + m->npieces;
-    a.nblk = b.nblk + (block_jacobi ? m->nblk : 0);
     a.binv = b.binv + (block_jacobi ? m->binv_len : 0);
     a.trow = b.trow + m->ntrow;
     a.quads = b.quads + m->nquad;
@@ -146,13 +144,10 @@ gp_matrix* stack_matrices(gp_ctx* c, int R, const gp_matrix* const* ms, bool blo
   m->qval = dev_alloc(c, vbytes * 4 * std::max<int64_t>(m->nquad, 1));
   m->bytes += sizeof(int32_t) * m->ntrow + sizeof(int64_t) * (ng + 1) + (sizeof(int32_t) + vbytes * 4) * m->nquad;
   if (block_jacobi) {
-    m->nblk = tot.nblk;
     m->binv_len = tot.binv;
-    m->bstart = dev_new<int32_t>(c, m->nblk + 1);
-    m->rowblk = dev_new<int32_t>(c, n);
-    m->boff = dev_new<int64_t>(c, m->nblk + 1);
+    m->brow = dev_new<uint64_t>(c, n);
     m->binv = dev_new<double>(c, std::max<int64_t>(m->binv_len, 1));
-    m->bytes += sizeof(int32_t) * (m->nblk + 1 + n) + sizeof(int64_t) * (m->nblk + 1) + sizeof(double) * m->binv_len;
+    m->bytes += sizeof(uint64_t) * n + sizeof(double) * m->binv_len;
   }
 
   // the piece table: one run of R pieces per stacked array
@@ -200,11 +195,10 @@ gp_matrix* stack_matrices(gp_ctx* c, int R, const gp_matrix* const* ms, bool blo
       add_run([&](int, const gp_matrix* x, const Off& o) { return P(x->qptr, x->ntrow / 4, o.trow / 4, o.quads); });
   const Run r_qcol = add_run([&](int, const gp_matrix* x, const Off& o) { return P(x->qcol, x->nquad, o.quads, o.row); });
   const Run r_qval = add_run([&](int, const gp_matrix* x, const Off& o) { return P(x->qval, 4 * x->nquad, 4 * o.quads); });
-  Run r_bstart{}, r_rowblk{}, r_boff{}, r_binv{};
+  Run r_brow{}, r_binv{};
   if (block_jacobi) {
-    r_bstart = add_run([&](int, const gp_matrix* x, const Off& o) { return P(x->bstart, x->nblk, o.nblk, o.row); });
-    r_rowblk = add_run([&](int, const gp_matrix* x, const Off& o) { return P(x->rowblk, x->n, o.row, o.nblk); });
-    r_boff = add_run([&](int, const gp_matrix* x, const Off& o) { return P(x->boff, x->nblk, o.nblk, o.binv); });
+    // the rows' words move by the inverses' offset (their upper 48 bits)
+    r_brow = add_run([&](int, const gp_matrix* x, const Off& o) { return P(x->brow, x->n, o.row, o.binv << 16); });
     r_binv = add_run([&](int, const gp_matrix* x, const Off& o) { return P(x->binv, x->binv_len, o.binv); });
   }
   TmpBuf dtab(c, sizeof(Piece) * tab.size());
@@ -247,11 +241,7 @@ gp_matrix* stack_matrices(gp_ctx* c, int R, const gp_matrix* const* ms, bool blo
   else
     launch(k_stack<double, kCopy>, r_qval, static_cast<double*>(m->qval));
   if (block_jacobi) {
-    launch(k_stack<int32_t, kShift>, r_bstart, m->bstart);
-    hipLaunchKernelGGL(k_put_i32, dim3(1), dim3(1), 0, c->stream, m->bstart + m->nblk, static_cast<int32_t>(n));
-    launch(k_stack<int32_t, kShift>, r_rowblk, m->rowblk);
-    launch(k_stack<int64_t, kShift>, r_boff, m->boff);
-    hipLaunchKernelGGL(k_put_i64, dim3(1), dim3(1), 0, c->stream, m->boff + m->nblk, m->binv_len);
+    launch(k_stack<int64_t, kShift>, r_brow, reinterpret_cast<int64_t*>(m->brow));
     launch(k_stack<double, kCopy>, r_binv, m->binv);
   }
   check_launch("stack matrices");

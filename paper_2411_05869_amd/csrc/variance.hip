@@ -266,9 +266,7 @@ __device__ __forceinline__ void col_totals2(const double* __restrict__ part, int
 // waiting for the others.
 struct VarPrecond {
   const double* diag;
-  const int32_t* rowblk;
-  const int32_t* bstart;
-  const int64_t* boff;
+  const uint64_t* brow;
   const double* binv;
 };
 
@@ -279,8 +277,8 @@ __device__ __forceinline__ int64_t tile_start(const VarPrecond& M, int64_t n, in
   const int64_t i = k * kTile;
   if (i >= n) return n;
   if (!M.binv) return i;
-  const int32_t b = M.rowblk[i];
-  return M.bstart[b] == i ? i : M.bstart[b + 1];
+  const BlockRow br(M.brow[i]);
+  return br.k == 0 ? i : i - br.k + br.sz;
 }
 
 // z = M^-1 r for the rows of a tile (rows lo .. hi - 1, the thread's column):
@@ -295,11 +293,10 @@ __device__ __forceinline__ void tile_precond(const VarPrecond& M, int64_t lo, in
     const double r = rt[i - lo][col];
     double z = 0.0;
     if (M.binv) {
-      const int32_t b = M.rowblk[i];
-      const int32_t bs = M.bstart[b];
-      const int sz = M.bstart[b + 1] - bs;
-      const double* w = M.binv + M.boff[b] + (i - bs);
-      const double(*rb)[kC] = rt + (bs - lo);
+      const BlockRow br(M.brow[i]);
+      const int sz = br.sz;
+      const double* w = M.binv + br.pos;
+      const double(*rb)[kC] = rt + (i - br.k - lo);
       constexpr int kB = 8;
       for (int j0 = 0; j0 < sz; j0 += kB) {
         double v[kB];
@@ -494,8 +491,15 @@ __global__ void __launch_bounds__(kMThreads) k_bcg_update_mfma(int64_t n, const 
       rv[u] = r < hi ? R[r * kC + col] : 0.0;
       qv[u] = r < hi ? Q[r * kC + col] : 0.0;
     }
-    // the tile's Jacobi blocks: lane j holds block b0 + j (a tile has at most kTileMax)
-    const int b0 = lo < hi ? M.rowblk[lo] : 0, nb = lo < hi ? M.rowblk[hi - 1] - b0 + 1 : 0;
+    // the tile's rows lane and lane + 64: where a Jacobi block starts, and its place
+    static_assert(kTileMax <= 2 * kWave, "two rows per lane");
+    uint64_t place[2], starts[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int64_t r = lo + lane + h * kWave;
+      place[h] = r < hi ? M.brow[r] : 0;
+      starts[h] = __ballot(r < hi && BlockRow(place[h]).k == 0);
+    }
     __syncthreads();  // the previous tile has been read
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
@@ -507,10 +511,19 @@ __global__ void __launch_bounds__(kMThreads) k_bcg_update_mfma(int64_t n, const 
       }
     }
     __syncthreads();
-    for (int j = w; j < nb; j += kMWaves) {  // uniform over the wave
-      const int32_t bs = M.bstart[b0 + j];
-      const int sz = M.bstart[b0 + j + 1] - bs;
-      const double* binv = M.binv + M.boff[b0 + j];
+    const int nlow = __popcll(starts[0]), nb = nlow + __popcll(starts[1]);
+    uint64_t todo = starts[0];
+    for (int j = 0, h = 0; j < nb; ++j, todo &= todo - 1) {  // uniform over the wave
+      if (j == nlow) {
+        todo = starts[1];
+        h = 1;
+      }
+      if (j % kMWaves != w) continue;
+      const int src = __builtin_ctzll(todo);
+      const BlockRow br(__shfl(place[h], src, kWave));
+      const int64_t bs = lo + src + h * kWave;
+      const int sz = br.sz;
+      const double* binv = M.binv + br.pos;
       const double(*rb)[kC] = rt + (bs - lo);
       d4 acc[2][2];
 #pragma unroll
@@ -546,7 +559,7 @@ __global__ void __launch_bounds__(kMThreads) k_bcg_update_mfma(int64_t n, const 
         for (int v = 0; v < 4; ++v) {
           const int r = 16 * t + kk + 4 * v;
           if (r >= sz) continue;
-          double* zr = Z + (bs + r) * static_cast<int64_t>(kC);
+          double* zr = Z + (bs + r) * kC;
 #pragma unroll
           for (int c = 0; c < 2; ++c) {
             const double x = rb[r][i + 16 * c], z = acc[t][c][v];
@@ -664,14 +677,12 @@ VarResult predict_variance(gp_ctx* c, const gp_matrix* m, const gp_theta* th, in
                            double rtol, int max_iter, int precond, double* var) {
   VarResult res;
   if (ntest == 0) return res;
-  VarPrecond M{m->diag, nullptr, nullptr, nullptr, nullptr};
+  VarPrecond M{m->diag, nullptr, nullptr};
   if (precond == GP_PRECOND_BLOCK_JACOBI) {
     // the inverses are cached in the matrix object on first use
     gp_matrix* mm = const_cast<gp_matrix*>(m);
     build_block_jacobi(c, mm);
-    M.rowblk = mm->rowblk;
-    M.bstart = mm->bstart;
-    M.boff = mm->boff;
+    M.brow = mm->brow;
     M.binv = mm->binv;
   }
   const gp_dataset* ds = m->ds;
