@@ -318,6 +318,7 @@ gp_status gp_ctx_destroy(gp_ctx* c) {
     if (c->ev_aux) (void)hipEventDestroy(c->ev_aux);
     c->evpool.clear();
     c->feed.reset();
+    if (c->recorder) (void)hipStreamDestroy(c->recorder);
     if (c->side) {
       (void)hipStreamSynchronize(c->side);
       (void)hipStreamDestroy(c->side);

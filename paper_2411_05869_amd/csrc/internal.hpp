@@ -101,6 +101,8 @@ struct gp_ctx {
   bool side_pending = false;  // work was forked to the side stream and not joined yet
   bool alloc_locked = false;  // set while work is enqueued on the side stream
   bool concurrent = true;     // the log det of a likelihood on the side stream
+  hipStream_t recorder = nullptr;  // launches are recorded here, none run (created on first use)
+  bool recording = false;     // what is enqueued is being recorded
   // side-stream work not enqueued yet, and a ring of events marking the
   // completion of its latest units (side_pump)
   std::unique_ptr<gps::SideFeed> feed;

@@ -421,7 +421,7 @@ __global__ void __launch_bounds__(kThreads) k_pq_part(int64_t n, const double* _
 __global__ void __launch_bounds__(kThreads) k_beta_fin(const double* __restrict__ part, int nb,
                                                        CgScalars* __restrict__ s, int mode,
                                                        const int* __restrict__ skip = nullptr, Seg g = {},
-                                                       int per_block = 0) {
+                                                       int per_block = 0, CgScalars* __restrict__ host = nullptr) {
   if (seg_skip(skip)) return;
   int64_t n = 0;
   seg_begin(g, n);
@@ -436,6 +436,7 @@ __global__ void __launch_bounds__(kThreads) k_beta_fin(const double* __restrict_
     s->rr = r[1];
     s->beta = mode == 2 ? 0.0 : r[0] / s->rz_old;
     if (!isfinite(r[0]) || !isfinite(r[1])) s->status = 1;
+    if (host) *host = *s;
   }
 }
 
@@ -962,6 +963,85 @@ static double logsum_f64(gp_ctx* c, const double* a, int64_t n) {
   return *h;
 }
 
+// Entries up to which the blocks of iterations are launched as recorded graphs.
+// A launch of the iteration's kernels costs the host 3 - 4 us (it grows with the
+// bytes of arguments), so four per iteration and the log det's seven per step
+// beside them keep the GPU waiting where the kernels are as short; a graph of
+// the block's 33 launches costs 22 us.  Plain launches -> graphs, a likelihood:
+// 0.3M entries (n = 2000) 3.8 -> 3.25 ms, 2.0M (n = 30,011) 12.5 -> 10.8, 5.0M (n = 60,013)
+// 19.8 -> 19.6; a solve of 19M entries 17.25 -> 17.35: there the GPU is the later
+// of the two either way, and leaves a little more room between a graph's kernels.
+constexpr int64_t kGraphEntries = int64_t(8) << 20;
+
+// A sequence of launches recorded once and launched with one call: 29 us to
+// record 33 kernels, 79 to instantiate and 42 to destroy, all of it while the
+// GPU works.  Kept for one solve; without the means to record (a stream, memory)
+// there is none and the caller launches plainly.
+class LaunchGraph {
+ public:
+  explicit LaunchGraph(gp_ctx* c) : c_(c) {}
+  LaunchGraph(const LaunchGraph&) = delete;
+  LaunchGraph& operator=(const LaunchGraph&) = delete;
+  ~LaunchGraph() {
+    if (exec_) (void)hipStreamSynchronize(c_->stream);
+    drop();
+  }
+  // (none of its launches is running any more)
+  void drop() {
+    if (exec_) (void)hipGraphExecDestroy(exec_);
+    exec_ = nullptr;
+  }
+  explicit operator bool() const { return exec_ != nullptr; }
+
+  // records what enqueue() launches on c->stream; nothing of it runs
+  template <typename F>
+  void record(F&& enqueue) {
+    if (!c_->recorder && hipStreamCreateWithFlags(&c_->recorder, hipStreamNonBlocking) != hipSuccess) {
+      (void)hipGetLastError();
+      c_->recorder = nullptr;
+      return;
+    }
+    if (hipStreamBeginCapture(c_->recorder, hipStreamCaptureModeThreadLocal) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    Recording rec(c_);
+    enqueue();
+    if (!rec.end()) return;
+    if (hipGraphInstantiate(&exec_, rec.graph, nullptr, nullptr, 0) != hipSuccess) {
+      (void)hipGetLastError();
+      exec_ = nullptr;
+    }
+  }
+  void launch() { GPS_HIP(hipGraphLaunch(exec_, c_->stream)); }
+
+ private:
+  // the context's launches go to the recorder while this lives (or until end())
+  struct Recording {
+    gp_ctx* c;
+    hipStream_t main;
+    hipGraph_t graph = nullptr;
+    explicit Recording(gp_ctx* c_) : c(c_), main(c_->stream) {
+      c->stream = c->recorder;
+      c->recording = true;
+    }
+    bool end() {
+      c->stream = main;
+      c->recording = false;
+      if (hipStreamEndCapture(c->recorder, &graph) == hipSuccess) return true;
+      (void)hipGetLastError();
+      graph = nullptr;
+      return false;
+    }
+    ~Recording() {
+      if (c->recording) (void)end();  // enqueue() has thrown
+      if (graph) (void)hipGraphDestroy(graph);
+    }
+  };
+  gp_ctx* c_;
+  hipGraphExec_t exec_ = nullptr;
+};
+
 SolveResult pcg_solve(gp_ctx* c, gp_matrix* m, const double* y, double* x, double rtol, int max_iter, int precond) {
   const int64_t n = m->n;
   if (precond == GP_PRECOND_BLOCK_JACOBI) build_block_jacobi(c, m);
@@ -983,23 +1063,27 @@ SolveResult pcg_solve(gp_ctx* c, gp_matrix* m, const double* y, double* x, doubl
   CgScalars* s = static_cast<CgScalars*>(workspace(c, 27, sizeof(CgScalars)));
   CgScalars* hs = static_cast<CgScalars*>(pinned(c, sizeof(CgScalars)));
   const dim3 G(kRedBlocks), B(kThreads), GR(red_blocks(n));
+  // k_beta_fin, the kernel before every read, has left the scalars in pinned memory (a
+  // copy of them was one more launch and 2 us of the stream)
   auto read = [&]() {
-    GPS_HIP(hipMemcpyAsync(hs, s, sizeof(CgScalars), hipMemcpyDeviceToHost, c->stream));
     side_pump(c);  // the side stream's queue topped up before the host waits
     sync(c);
     return *hs;
   };
+  LaunchGraph block(c);  // a whole block of iterations and the direction before it
   // z = M^-1 r and the scalars r.z, r.r (mode: see k_beta_fin)
   auto apply_precond = [&](int mode) {
     ProfScope ps(c, "pcg_precond");
     hipLaunchKernelGGL(k_precond, dim3(nbp), B, 0, c->stream, n, M, rc, z, ppart);
-    hipLaunchKernelGGL(k_beta_fin, dim3(1), B, 0, c->stream, ppart, static_cast<int>(nbp), s, mode);
+    hipLaunchKernelGGL(k_beta_fin, dim3(1), B, 0, c->stream, ppart, static_cast<int>(nbp), s, mode, nullptr, Seg{}, 0,
+                       hs);
   };
   auto true_residual = [&]() {
     spmv_f64(c, m, x, q);
     hipLaunchKernelGGL(k_true_resid, G, B, 0, c->stream, n, y, q, rc);
     apply_precond(1);
     check_launch("true residual");
+    block.drop();  // beside the pass; a solve that goes on after it launches plainly
     return read();
   };
   {
@@ -1024,8 +1108,7 @@ SolveResult pcg_solve(gp_ctx* c, gp_matrix* m, const double* y, double* x, doubl
   // host check leaves the direction to after the check
   double* pqp = part;                    // kRedBlocks partials of p.q
   double* spart = ppart;                 // 2 x nbs partials of r.z, r.r
-  while (it < max_iter && !converged) {
-    const int steps = std::min(kCheckEvery, max_iter - it);
+  auto iterations = [&](int steps) {
     for (int t = 0; t < steps; ++t) {
       // float64 vectors; a GP_MIXED matrix contributes its float32 values
       spmv_f64(c, m, p, q);
@@ -1037,11 +1120,29 @@ SolveResult pcg_solve(gp_ctx* c, gp_matrix* m, const double* y, double* x, doubl
         if (t + 1 < steps)
           hipLaunchKernelGGL(k_pcg_direction, GR, B, 0, c->stream, n, s, spart, static_cast<int>(nbs), z, p, nullptr);
         else
-          hipLaunchKernelGGL(k_beta_fin, dim3(1), B, 0, c->stream, spart, static_cast<int>(nbs), s, 3);
+          hipLaunchKernelGGL(k_beta_fin, dim3(1), B, 0, c->stream, spart, static_cast<int>(nbs), s, 3, nullptr, Seg{},
+                             0, hs);
       }
       check_launch("pcg iteration");
-      side_pump(c);
+      if (!c->recording) side_pump(c);
     }
+  };
+  static_assert(kCheckEvery % 2 == 0, "a block leaves the two residual buffers in their places");
+  while (it < max_iter && !converged) {
+    const int steps = std::min(kCheckEvery, max_iter - it);
+    auto enqueue = [&]() {
+      if (it > 0) {
+        hipLaunchKernelGGL(k_pcg_pupdate, G, B, 0, c->stream, n, s, z, p);
+        check_launch("pcg direction");
+      }
+      iterations(steps);
+    };
+    if (block && steps == kCheckEvery)
+      block.launch();
+    else
+      enqueue();
+    // recorded while the second block runs
+    if (it == kCheckEvery && steps == kCheckEvery && m->nnz <= kGraphEntries && !c->prof_on) block.record(enqueue);
     it += steps;
     sc = read();
     if (sc.status != 0) {
@@ -1056,10 +1157,6 @@ SolveResult pcg_solve(gp_ctx* c, gp_matrix* m, const double* y, double* x, doubl
       ++res.refreshes;
       last_true = std::sqrt(sc.rr);
       if (last_true <= target) converged = true;
-    }
-    if (!converged && it < max_iter) {
-      hipLaunchKernelGGL(k_pcg_pupdate, G, B, 0, c->stream, n, s, z, p);
-      check_launch("pcg direction");
     }
   }
   res.iters = it;
