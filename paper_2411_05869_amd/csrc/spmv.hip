@@ -7,7 +7,7 @@
 // bitwise reproducible; no floating-point atomics are used.
 //
 // SpMM: k <= 32 right-hand sides, X and Y row-major n x ld, optional
-// symmetric diagonal scaling Y = S K S X (see k_spmm).
+// symmetric diagonal scaling Y = S K S X (32 columns: k_spmm_quad, k_spmm_long; fewer: k_spmm_rows).
 #include <algorithm>
 #include <type_traits>
 
@@ -119,25 +119,16 @@ __global__ void __launch_bounds__(kThreads) k_spmv(int64_t n, unsigned nb_long, 
 }
 
 // SpMM, Y = S K S X (S = diag(scale), or K X without scale), k <= 32 columns of
-// a row-major block with leading dimension ld: the CSR part row by row.  With
-// 16-byte X loads (VEC) only its long-row blocks run (nb_short = 0); the
-// short rows then go through the row quads (k_spmm_quad).
-//
-// A wave stages 64 consecutive entries of a row at a time: lane l loads entry
-// l (column id and value * scale[column]) with one coalesced access.  The
-// entries are then consumed in pairs: half-wave h = l >> 5 takes entry 2i + h
-// and lane l works on column l & 31, receiving the entry's column id and
-// weight from the staging lane by ds_bpermute.  All X gathers of a staged
-// chunk are independent, so kUm of them are in flight per lane.
-// Blocks [0, nb_short) give each wave kRowsPerWave consecutive rows: the
-// bounds of all of them are read at once, and the first chunk of the next
-// row is staged while the X gathers of the current row are in flight, so the
-// dependent loads of consecutive rows overlap.  Rows of more than kLongRow
-// entries are skipped there; the remaining blocks give each such row a whole
-// block: wave w takes the chunks w, w + 4, ... and the four partial rows are
-// added in a fixed order.
-constexpr int kUm = 8;
-constexpr int kRowsPerWave = 8;
+// a row-major block with leading dimension ld.  Blocks of 32 aligned columns take
+// the row quads (k_spmm_quad) and, for rows of more than kLongRow entries, a
+// block per row (k_spmm_long); fewer columns take k_spmm_rows.
+
+// orders the LDS accesses of one wave (its own slice; no block barrier)
+__device__ __forceinline__ void wave_sync_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 template <typename T>
 __device__ __forceinline__ T shfl_any(T v, int src) {
@@ -160,32 +151,9 @@ __device__ __forceinline__ void spmm_stage(int64_t j0, int64_t e, int32_t self, 
   }
 }
 
-// sum over the m staged entries of v * X[q, column]
-template <typename T>
-__device__ __forceinline__ T spmm_consume(int32_t q, T v, int m, const T* __restrict__ X, int ld, int cl, int h) {
-  const int npairs = (m + 1) >> 1;
-  T acc = 0;
-  for (int i0 = 0; i0 < npairs; i0 += kUm) {
-    int32_t qq[kUm];
-    T vv[kUm];
-#pragma unroll
-    for (int u = 0; u < kUm; ++u) {
-      const int src = (2 * (i0 + u) + h) & (kWave - 1);  // entries past m carry weight 0
-      qq[u] = shfl_any(q, src);
-      vv[u] = shfl_any(v, src);
-      if (i0 + u >= npairs) vv[u] = 0;
-    }
-    T xv[kUm];
-#pragma unroll
-    for (int u = 0; u < kUm; ++u) xv[u] = X[static_cast<int64_t>(qq[u]) * ld + cl];
-#pragma unroll
-    for (int u = 0; u < kUm; ++u) acc += vv[u] * xv[u];
-  }
-  return acc;
-}
-
-// The same sum with 16-byte X loads, for blocks whose rows hold at least 32
-// values at 16-byte alignment: lane l works on the kCpl consecutive columns
+// Sum over the m staged entries of v * X[q, columns] with 16-byte X loads, for
+// blocks whose rows hold at least 32 values at 16-byte alignment: lane l works
+// on the kCpl consecutive columns
 // kCpl (l % kLpe) ... of entry slot l / kLpe, so one load instruction serves
 // kWave / kLpe entries.  Returns the lane's kCpl partial sums; the slots are
 // added by the caller.
@@ -237,148 +205,200 @@ __device__ __forceinline__ void slot_sum(Vec16<T>& a) {
     for (int t = 0; t < Vec16<T>::kCpl; ++t) a.v[t] += __shfl_xor(a.v[t], off, kWave);
 }
 
-template <typename VT, typename T, bool SCALE, bool VEC>
-__global__ void __launch_bounds__(kThreads) k_spmm(int64_t n, unsigned nb_short, int64_t nlong,
-                                                   const int32_t* __restrict__ rows, int k, int ld,
-                                                   const int64_t* __restrict__ rp, const int32_t* __restrict__ gskip,
-                                                   const int32_t* __restrict__ col,
-                                                   const VT* __restrict__ val, const T* __restrict__ X,
-                                                   T* __restrict__ Y, const T* __restrict__ scale,
-                                                   const double* __restrict__ colscale) {
+// Rows of more than kLongRow entries past their group part, a block each: a wave
+// stages 64 consecutive entries at a time (lane l entry l, column id and value *
+// scale[column], one coalesced access), wave w the chunks w, w + 4, ...; all X
+// gathers of a chunk are independent, so kUq of them are in flight per lane.  The
+// four partial rows are added in a fixed order, after the group part already in Y.
+template <typename VT, typename T, bool SCALE>
+__global__ void __launch_bounds__(kThreads) k_spmm_long(int64_t nlong, const int32_t* __restrict__ rows, int k, int ld,
+                                                        const int64_t* __restrict__ rp,
+                                                        const int32_t* __restrict__ gskip,
+                                                        const int32_t* __restrict__ col, const VT* __restrict__ val,
+                                                        const T* __restrict__ X, T* __restrict__ Y,
+                                                        const T* __restrict__ scale,
+                                                        const double* __restrict__ colscale) {
   using V = Vec16<T>;
-  const int lane = lane_id();
-  const int c = lane & 31;
-  const int cl = c < k ? c : k - 1;  // lanes past k re-read column k-1 (in bounds), never store
-  const int h = lane >> 5;
-  const int w = threadIdx.x / kWave;
-  // column factors, read once: lane c (pair path) or the lane's kCpl columns (VEC)
-  T csc = 1, csv[V::kCpl];
+  __shared__ T part[kThreads / kWave][32];
+  const int lane = lane_id(), w = threadIdx.x / kWave;
+  const int64_t li = xcd_remap(blockIdx.x, gridDim.x);
+  if (li >= nlong) return;  // uniform over the block
+  const int32_t row = rows[li];
+  const int32_t gs = gskip[row];
+  const int64_t s = rp[row] + gs, e = rp[row + 1];
+  V acc;
 #pragma unroll
-  for (int t = 0; t < V::kCpl; ++t) csv[t] = 1;
-  if (colscale) {
-    csc = static_cast<T>(colscale[cl]);
+  for (int t = 0; t < V::kCpl; ++t) acc.v[t] = 0;
+  for (int64_t j0 = s + static_cast<int64_t>(w) * kWave; j0 < e; j0 += kThreads) {
+    int32_t q;
+    T v;
+    spmm_stage<VT, T, SCALE>(j0, e, row, col, val, scale, lane, q, v);
+    const V a = spmm_consume16<T>(q, v, static_cast<int>(min<int64_t>(e - j0, kWave)), X, ld, lane);
 #pragma unroll
-    for (int t = 0; t < V::kCpl; ++t) csv[t] = static_cast<T>(colscale[min((lane % V::kLpe) * V::kCpl + t, k - 1)]);
+    for (int t = 0; t < V::kCpl; ++t) acc.v[t] += a.v[t];
   }
-  // finishes a row: acc holds the pair-path sum (VEC false) or the lane's
-  // slot sums (VEC true); adds the group part already in Y, scales, stores
-  auto finish = [&](int64_t row, int32_t gs, T acc, V accv) {
-    if constexpr (VEC) {
-      slot_sum<T>(accv);
-      if (lane < V::kLpe) {
-        T* yr = Y + row * ld + lane * V::kCpl;
+  slot_sum<T>(acc);
+  if (lane < V::kLpe)
 #pragma unroll
-        for (int t = 0; t < V::kCpl; ++t) {
-          if (lane * V::kCpl + t >= k) break;
-          T a = accv.v[t];
-          if (gs) a = yr[t] + a;
-          if constexpr (SCALE) a *= scale[row];
-          if (colscale) a *= csv[t];
-          yr[t] = a;
-        }
-      }
-    } else {
-      acc += __shfl_xor(acc, 32, kWave);
-      if (h == 0 && c < k) {
-        if (gs) acc = Y[row * ld + c] + acc;
-        if constexpr (SCALE) acc *= scale[row];
-        if (colscale) acc *= csc;
-        Y[row * ld + c] = acc;
-      }
-    }
-  };
-  auto consume = [&](int32_t q, T v, int m, T& acc, V& accv) {
-    if constexpr (VEC) {
-      const V a = spmm_consume16<T>(q, v, m, X, ld, lane);
+    for (int t = 0; t < V::kCpl; ++t) part[w][lane * V::kCpl + t] = acc.v[t];
+  __syncthreads();
+  const int c = threadIdx.x;
+  if (c >= k) return;
+  T t = part[0][c];
 #pragma unroll
-      for (int t = 0; t < V::kCpl; ++t) accv.v[t] += a.v[t];
-    } else {
-      acc += spmm_consume<T>(q, v, m, X, ld, cl, h);
-    }
-  };
-  if (blockIdx.x < nb_short) {
-    const int64_t r0 = (xcd_remap(blockIdx.x, nb_short) * static_cast<int64_t>(kThreads / kWave) + w) * kRowsPerWave;
-    if (r0 >= n) return;
-    const int nr = static_cast<int>(min<int64_t>(kRowsPerWave, n - r0));
-    // lane l < nr: first non-group entry, end and group flag of row r0 + l
-    int64_t rs = 0, re = 0;
-    int32_t rg = 0;
-    if (lane < nr) {
-      rg = gskip[r0 + lane];
-      rs = rp[r0 + lane] + rg;
-      re = rp[r0 + lane + 1];
-    }
-    int32_t q = 0;
-    T v = 0;
-    {
-      const int64_t s = shfl_any(rs, 0), e = shfl_any(re, 0);
-      if (e - s <= kLongRow) spmm_stage<VT, T, SCALE>(s, e, static_cast<int32_t>(r0), col, val, scale, lane, q, v);
-    }
-    for (int r = 0; r < nr; ++r) {
-      const int64_t row = r0 + r;
-      const int64_t s = shfl_any(rs, r), e = shfl_any(re, r);
-      const int32_t gs = shfl_any(rg, r);
-      // stage the next row's first chunk while this row's gathers run
-      int32_t qn = 0;
-      T vn = 0;
-      if (r + 1 < nr) {
-        const int64_t sn = shfl_any(rs, r + 1), en = shfl_any(re, r + 1);
-        if (en - sn <= kLongRow)
-          spmm_stage<VT, T, SCALE>(sn, en, static_cast<int32_t>(row + 1), col, val, scale, lane, qn, vn);
-      }
-      if (e - s <= kLongRow) {
-        T acc = 0;
-        V accv;
+  for (int i = 1; i < kThreads / kWave; ++i) t += part[i][c];
+  if (gs) t = Y[static_cast<int64_t>(row) * ld + c] + t;
+  if constexpr (SCALE) t *= scale[row];
+  if (colscale) t *= colscale[c];
+  Y[static_cast<int64_t>(row) * ld + c] = t;
+}
+
+// CSR part of the product with fewer than 32 columns (any k <= W, any ld).  A row
+// is the work of L lanes in slots of W, a lane per column.  The L lanes stage L
+// consecutive entries (a lane each: id and weight) in their LDS slice; each slot
+// then takes its entries from there and its lanes read their column of the X row,
+// so an entry costs one read of its id and value and one of its k columns.  Two
+// columns leave too few steps to a chunk for that to pay: there a slot takes four
+// consecutive entries itself, as in the one-column product.
+// Blocks [0, nb_long) take the listed long rows, a block each.
+// Bound by the gathers of X through the caches.  A wave per row and 32 columns
+// whatever k was, as before, took as long for 2 columns as for 31; the whole
+// product by columns, before -> now: n = 100,003 (mixture, FP64) 2: 187 -> 65 us, 8: 183 -> 88,
+// 16: 184 -> 116, 31: 197 -> 173; n = 1,095,000 (space-time, mixed) 2: 1062 -> 286, 8: 1058 -> 476,
+// 16: 1134 -> 728, 31: 1332 -> 1264.  Reading an entry in every lane of its slot
+// instead of staging: 8: 107 and 539 us, 16: 153 and 901.
+template <int W>
+constexpr int row_lanes() { return W <= 8 ? 16 : 2 * W; }  // lanes of a row
+constexpr int kRowUq = 4;  // X rows a lane has in flight
+template <int W, int L>
+constexpr int row_chunk() { return W < kRowUq ? L / W * kRowUq : L; }  // entries the lanes take at a time
+
+template <int W, int L, typename VT, typename T, bool SCALE>
+__device__ __forceinline__ T spmm_part(int64_t s, int64_t e, int64_t stride, int32_t self, int32_t* sq, T* sv,
+                                       const int32_t* __restrict__ col, const int16_t* __restrict__ off16,
+                                       const VT* __restrict__ val, const T* __restrict__ X, int64_t ld,
+                                       const T* __restrict__ scale) {
+  constexpr int kSlots = L / W, kU = kRowUq;
+  const int l = lane_id() % L, slot = l / W;
+  T acc = 0;
+  if constexpr (W < kU) {
+    for (int64_t j1 = s + kU * slot; j1 < e; j1 += stride) {
+      // (a load may run up to three entries past the row, into the padding at most)
+      int32_t q[kU];
+      VT raw[kU];
+      if (off16) {
+        int16_t o[kU];
+        __builtin_memcpy(o, off16 + j1, sizeof(o));
 #pragma unroll
-        for (int t = 0; t < V::kCpl; ++t) accv.v[t] = 0;
-        consume(q, v, static_cast<int>(min<int64_t>(e - s, kWave)), acc, accv);
-        for (int64_t j0 = s + kWave; j0 < e; j0 += kWave) {
-          int32_t q2;
-          T v2;
-          spmm_stage<VT, T, SCALE>(j0, e, static_cast<int32_t>(row), col, val, scale, lane, q2, v2);
-          consume(q2, v2, static_cast<int>(min<int64_t>(e - j0, kWave)), acc, accv);
-        }
-        finish(row, gs, acc, accv);
+        for (int u = 0; u < kU; ++u) q[u] = self + static_cast<int32_t>(o[u]);
+      } else {
+        __builtin_memcpy(q, col + j1, sizeof(q));
       }
-      q = qn;
-      v = vn;
+      __builtin_memcpy(raw, val + j1, sizeof(raw));
+      T xv[kU], wv[kU];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const bool in = j1 + u < e;
+        q[u] = in ? q[u] : self;
+        wv[u] = in ? static_cast<T>(raw[u]) : T(0);
+      }
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        xv[u] = X[q[u] * ld];
+        if constexpr (SCALE) wv[u] *= scale[q[u]];
+      }
+#pragma unroll
+      for (int u = 0; u < kU; ++u) acc += wv[u] * xv[u];
     }
   } else {
-    __shared__ T part[kThreads / kWave][32];
-    const int64_t li = xcd_remap(blockIdx.x - nb_short, gridDim.x - nb_short);
+    int32_t q = self;
+    T v = 0;
+    auto load = [&](int64_t j0) {
+      const int64_t j = j0 + l;
+      q = self;
+      v = 0;
+      if (j < e) {
+        q = off16 ? self + static_cast<int32_t>(off16[j]) : col[j];
+        v = static_cast<T>(val[j]);
+        if constexpr (SCALE) v *= scale[q];
+      }
+    };
+    load(s);
+    for (int64_t j0 = s; j0 < e; j0 += stride) {
+      wave_sync_lds();  // the previous entries have been read
+      sq[l] = q;
+      sv[l] = v;
+      wave_sync_lds();
+      const int m = static_cast<int>(min<int64_t>(L, e - j0));
+      load(j0 + stride);  // in flight while these are consumed
+      for (int u0 = 0; u0 * kSlots < m; u0 += kU) {
+        T xv[kU], wv[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+          const int i = (u0 + u) * kSlots + slot;  // past m: the row itself, weight 0
+          wv[u] = sv[i];
+          xv[u] = X[sq[i] * ld];
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) acc += wv[u] * xv[u];
+      }
+    }
+  }
+#pragma unroll
+  for (int off = W; off < L; off <<= 1) acc += __shfl_xor(acc, off, kWave);
+  return acc;
+}
+
+template <typename VT, typename T, bool SCALE, int W>
+__global__ void __launch_bounds__(kThreads) k_spmm_rows(int64_t n, unsigned nb_long, int64_t nlong,
+                                                        const int32_t* __restrict__ rows, int k, int ld,
+                                                        const int64_t* __restrict__ rp,
+                                                        const int32_t* __restrict__ gskip,
+                                                        const int32_t* __restrict__ col,
+                                                        const int16_t* __restrict__ off16,
+                                                        const VT* __restrict__ val, const T* __restrict__ X,
+                                                        T* __restrict__ Y, const T* __restrict__ scale,
+                                                        const double* __restrict__ colscale) {
+  constexpr int kL = row_lanes<W>();
+  __shared__ int32_t sq[kThreads];
+  __shared__ T sv[kThreads];
+  const int lane = lane_id(), c = lane % W;
+  const T* Xc = X + min(c, k - 1);  // lanes past k re-read column k - 1 and store nothing
+  auto finish = [&](int64_t row, int32_t gs, T t) {
+    T* y = Y + row * ld + c;
+    if (gs) t = *y + t;
+    if constexpr (SCALE) t *= scale[row];
+    if (colscale) t *= colscale[c];
+    *y = t;
+  };
+  if (blockIdx.x >= nb_long) {
+    const unsigned b = xcd_remap(blockIdx.x - nb_long, gridDim.x - nb_long);
+    const int64_t row = (b * static_cast<int64_t>(kThreads) + threadIdx.x) / kL;
+    if (row >= n) return;
+    const int32_t gs = gskip[row];
+    const int64_t s = rp[row] + gs, e = rp[row + 1];
+    if (e - s > kLongRow) return;  // uniform over the row's lanes
+    const int base = threadIdx.x / kL * kL;
+    const T acc = spmm_part<W, kL, VT, T, SCALE>(s, e, row_chunk<W, kL>(), static_cast<int32_t>(row), sq + base,
+                                                 sv + base, col, off16, val, Xc, ld, scale);
+    if (lane % kL < k) finish(row, gs, acc);
+  } else {
+    __shared__ T part[kThreads / kWave][W];
+    const int64_t li = xcd_remap(blockIdx.x, nb_long);
     if (li >= nlong) return;  // uniform over the block
     const int32_t row = rows[li];
     const int32_t gs = gskip[row];
-    const int64_t s = rp[row] + gs, e = rp[row + 1];
-    T acc = 0;
-    V accv;
-#pragma unroll
-    for (int t = 0; t < V::kCpl; ++t) accv.v[t] = 0;
-    for (int64_t j0 = s + static_cast<int64_t>(w) * kWave; j0 < e; j0 += kThreads) {
-      int32_t q;
-      T v;
-      spmm_stage<VT, T, SCALE>(j0, e, row, col, val, scale, lane, q, v);
-      consume(q, v, static_cast<int>(min<int64_t>(e - j0, kWave)), acc, accv);
-    }
-    if constexpr (VEC) {
-      slot_sum<T>(accv);
-      if (lane < V::kLpe)
-#pragma unroll
-        for (int t = 0; t < V::kCpl; ++t) part[w][lane * V::kCpl + t] = accv.v[t];
-    } else {
-      acc += __shfl_xor(acc, 32, kWave);
-      if (h == 0) part[w][c] = acc;
-    }
+    constexpr int kChunk = row_chunk<W, kWave>();
+    const int w = threadIdx.x / kWave, base = w * kWave;
+    const T acc = spmm_part<W, kWave, VT, T, SCALE>(rp[row] + gs + w * kChunk, rp[row + 1], kThreads / kWave * kChunk,
+                                                    row, sq + base, sv + base, col, nullptr, val, Xc, ld, scale);
+    if (lane < W) part[w][lane] = acc;
     __syncthreads();
-    if (w == 0 && h == 0 && c < k) {
-      T t = part[0][c];
+    if (static_cast<int>(threadIdx.x) >= k) return;
+    T t = part[0][c];
 #pragma unroll
-      for (int i = 1; i < kThreads / kWave; ++i) t += part[i][c];
-      if (gs) t = Y[static_cast<int64_t>(row) * ld + c] + t;
-      if constexpr (SCALE) t *= scale[row];
-      if (colscale) t *= csc;
-      Y[static_cast<int64_t>(row) * ld + c] = t;
-    }
+    for (int i = 1; i < kThreads / kWave; ++i) t += part[i][c];
+    finish(row, gs, t);
   }
 }
 
@@ -722,12 +742,11 @@ struct MfmaAcc<double> {
 constexpr int kMThreads = 512;                   // 8 waves: 4 row groups x 2 halves of each chunk
 constexpr int kMChunk = 64;                      // U_M entries per staged chunk
 constexpr int kMSteps = kMChunk / 4 / 2;         // MFMA k-steps per wave per chunk
-constexpr int kXPer = kMChunk * 32 / kMThreads;  // X values staged per thread
 static_assert(kSuperRows == 4 * 16, "one row group of 16 per wave pair");
 static_assert(kMSteps == 8 && kMChunk == 64, "lane (i, kk) of a wave half takes 8 consecutive entries");
 static_assert(kPiece % kMChunk == 0 && kPiece <= kMThreads, "piece = whole chunks, ids loaded in one pass");
 
-template <typename VT, typename T, bool SCALE>
+template <typename VT, typename T, bool SCALE, int NB>
 __global__ void __launch_bounds__(kMThreads) k_group_spmm_mfma(const int32_t* __restrict__ pieces,
                                                                const int32_t* __restrict__ grows,
                                                                const int64_t* __restrict__ uoff,
@@ -737,7 +756,9 @@ __global__ void __launch_bounds__(kMThreads) k_group_spmm_mfma(const int32_t* __
                                                                T* __restrict__ Y, const T* __restrict__ scale,
                                                                T* __restrict__ part) {
   using Acc = typename MfmaAcc<T>::type;
-  __shared__ T xs[2][kMChunk][33];
+  constexpr int kCols = 16 * NB;                      // columns: one or two blocks of 16
+  constexpr int kXPer = kMChunk * kCols / kMThreads;  // X values staged per thread
+  __shared__ T xs[2][kMChunk][kCols + 1];
   __shared__ int32_t us[kPiece];
   __shared__ T ss[SCALE ? kPiece : 1];
   const unsigned pid = xcd_remap(blockIdx.x, gridDim.x);
@@ -778,11 +799,11 @@ __global__ void __launch_bounds__(kMThreads) k_group_spmm_mfma(const int32_t* __
   load_a(0);
   __syncthreads();
   // staging of X: thread -> (chunk row, kXPer consecutive columns); rows of
-  // at least 32 values are read with vector loads (columns past k are read
+  // at least kCols values are read with vector loads (columns past k are read
   // but only feed output columns that are never stored)
-  constexpr int kSegs = 32 / kXPer;
+  constexpr int kSegs = kCols / kXPer;
   const int xr = threadIdx.x / kSegs, xc0 = (threadIdx.x % kSegs) * kXPer;
-  const bool xvec = ld >= 32;
+  const bool xvec = ld >= kCols;
   T xreg[kXPer];
   auto load_x = [&](int c0) {
     const int e = min(c0 + xr, len - 1);
@@ -802,7 +823,9 @@ __global__ void __launch_bounds__(kMThreads) k_group_spmm_mfma(const int32_t* __
 #pragma unroll
     for (int u = 0; u < kXPer; ++u) xs[buf][xr][xc0 + u] = xreg[u];
   };
-  Acc acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
+  Acc acc[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) acc[b] = Acc{0, 0, 0, 0};
   load_x(0);
   store_x(0);
 #pragma unroll
@@ -815,17 +838,16 @@ __global__ void __launch_bounds__(kMThreads) k_group_spmm_mfma(const int32_t* __
       load_a(c0 + kMChunk);
     }
     if (wave_rows) {
-      T b0[kMSteps], b1[kMSteps];
+      T bx[NB][kMSteps];
 #pragma unroll
-      for (int s = 0; s < kMSteps; ++s) {
-        b0[s] = xs[buf][ent(s)][i];
-        b1[s] = xs[buf][ent(s)][i + 16];
-      }
+      for (int s = 0; s < kMSteps; ++s)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) bx[b][s] = xs[buf][ent(s)][i + 16 * b];
 #pragma unroll
       for (int s = 0; s < kMSteps; ++s) {
         const T a = static_cast<T>(acur[s]);
-        acc0 = mfma16x16x4(a, b0[s], acc0);
-        acc1 = mfma16x16x4(a, b1[s], acc1);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[b] = mfma16x16x4(a, bx[b][s], acc[b]);
       }
     }
     if (more) {
@@ -836,14 +858,14 @@ __global__ void __launch_bounds__(kMThreads) k_group_spmm_mfma(const int32_t* __
     __syncthreads();
   }
   // the second half adds into the first in a fixed order (xs is free now)
-  T(*red)[16][33] = reinterpret_cast<T(*)[16][33]>(&xs[0][0][0]);
-  static_assert(sizeof(xs) >= 4 * 16 * 33 * sizeof(T), "reduction buffer fits in the staging buffer");
+  T(*red)[16][kCols + 1] = reinterpret_cast<T(*)[16][kCols + 1]>(&xs[0][0][0]);
+  static_assert(sizeof(xs) >= 4 * 16 * (kCols + 1) * sizeof(T), "reduction buffer fits in the staging buffer");
   if (half == 1 && wave_rows) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int rr = MfmaAcc<T>::row(kk, v);
-      red[rg][rr][i] = acc0[v];
-      red[rg][rr][i + 16] = acc1[v];
+#pragma unroll
+      for (int b = 0; b < NB; ++b) red[rg][rr][i + 16 * b] = acc[b][v];
     }
   }
   __syncthreads();
@@ -853,12 +875,12 @@ __global__ void __launch_bounds__(kMThreads) k_group_spmm_mfma(const int32_t* __
       const int rr = MfmaAcc<T>::row(kk, v);
       const int row = 16 * rg + rr;
       if (row >= t.z) continue;
-      const T y0 = acc0[v] + red[rg][rr][i], y1 = acc1[v] + red[rg][rr][i + 16];
       T* yr = whole ? Y + static_cast<int64_t>(grows[t.y + row]) * ld
                     : part + (static_cast<int64_t>(pid) * kSuperRows + row) * 32;
       const int kc = whole ? k : 32;
-      if (i < kc) yr[i] = y0;
-      if (i + 16 < kc) yr[i + 16] = y1;
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+        if (i + 16 * b < kc) yr[i + 16 * b] = acc[b][v] + red[rg][rr][i + 16 * b];
     }
   }
 }
@@ -995,13 +1017,6 @@ __global__ void __launch_bounds__(kLineThreads) k_line_rows(LineGeom lg, const i
   } else {
     for (int64_t t = running + threadIdx.x; t < pad; t += kLineThreads) trow[out0 + t] = -1;
   }
-}
-
-// orders the LDS accesses of one wave (its own slice; no block barrier)
-__device__ __forceinline__ void wave_sync_lds() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // The CSR-part column lists of the rows of quad g (listed rows 4g .. 4g+3;
@@ -1372,22 +1387,27 @@ void spmm(gp_ctx* c, const gp_matrix* m, int k, int ld, const T* X, T* Y, const 
   ProfScope ps(c, "spmm");
   // partial blocks of the pieces of multi-piece super-tiles
   T* part = m->npieces > 0 ? static_cast<T*>(workspace(c, 55, spmm_part_bytes(m))) : nullptr;
-  const unsigned nb_short = round_up8(grid_for((m->n + kRowsPerWave - 1) / kRowsPerWave, kThreads / kWave));
-  const unsigned nb = nb_short + static_cast<unsigned>(m->n_long);
   auto go = [&](auto vt, auto sc) {
     using VT = decltype(vt);
     constexpr bool SC = decltype(sc)::value;
     if (m->npieces > 0) {
       const int32_t* st = m->g_tiles + 4 * m->ntiles;
-      hipLaunchKernelGGL((k_group_spmm_mfma<VT, T, SC>), dim3(static_cast<unsigned>(m->npieces)), dim3(kMThreads), 0,
-                         c->stream, st + 4 * m->nstiles, m->g_rows, m->g_uoff, m->g_ulist, k, ld, m->row_ptr,
-                         static_cast<const VT*>(m->val), X, Y, scale, part);
+      auto group = [&](auto nb) {
+        hipLaunchKernelGGL((k_group_spmm_mfma<VT, T, SC, decltype(nb)::value>),
+                           dim3(static_cast<unsigned>(m->npieces)), dim3(kMThreads), 0, c->stream,
+                           st + 4 * m->nstiles, m->g_rows, m->g_uoff, m->g_ulist, k, ld, m->row_ptr,
+                           static_cast<const VT*>(m->val), X, Y, scale, part);
+      };
+      if (k <= 16)
+        group(std::integral_constant<int, 1>{});
+      else
+        group(std::integral_constant<int, 2>{});
       hipLaunchKernelGGL((k_group_reduce<T>), dim3(static_cast<unsigned>(m->nstiles * (kSuperRows / kRedRows))),
                          dim3(kThreads), 0, c->stream,
                          st, m->g_rows, k, ld, part, Y);
     }
     if (vec) {
-      // short rows over the row quads; the long rows by k_spmm's block-per-row path
+      // short rows over the row quads; the long rows by k_spmm_long
       const int64_t ng = mm->ntrow / kQuad;
       if (ng > 0) {
         const unsigned nbq =
@@ -1397,13 +1417,27 @@ void spmm(gp_ctx* c, const gp_matrix* m, int k, int ld, const T* X, T* Y, const 
                            static_cast<const VT*>(mm->qval), mm->trow, k, ld, X, Y, scale, colscale);
       }
       if (m->n_long > 0)
-        hipLaunchKernelGGL((k_spmm<VT, T, SC, true>), dim3(static_cast<unsigned>(m->n_long)), dim3(kThreads), 0,
-                           c->stream, m->n, 0u, m->n_long, m->long_rows, k, ld, m->row_ptr, m->gskip, m->col,
+        hipLaunchKernelGGL((k_spmm_long<VT, T, SC>), dim3(static_cast<unsigned>(m->n_long)), dim3(kThreads), 0,
+                           c->stream, m->n_long, m->long_rows, k, ld, m->row_ptr, m->gskip, m->col,
                            static_cast<const VT*>(m->val), X, Y, scale, colscale);
     } else {
-      hipLaunchKernelGGL((k_spmm<VT, T, SC, false>), dim3(nb), dim3(kThreads), 0, c->stream, m->n, nb_short,
-                         m->n_long, m->long_rows, k, ld, m->row_ptr, m->gskip, m->col, static_cast<const VT*>(m->val),
-                         X, Y, scale, colscale);
+      const unsigned nb_long = m->n_long > 0 ? round_up8(static_cast<unsigned>(m->n_long)) : 0;
+      auto rows = [&](auto w) {
+        constexpr int W = decltype(w)::value;
+        hipLaunchKernelGGL((k_spmm_rows<VT, T, SC, W>), dim3(nb_long + grid_for(m->n * row_lanes<W>(), kThreads)),
+                           dim3(kThreads), 0, c->stream, m->n, nb_long, m->n_long, m->long_rows, k, ld, m->row_ptr,
+                           m->gskip, m->col, m->col16, static_cast<const VT*>(m->val), X, Y, scale, colscale);
+      };
+      if (k <= 2)
+        rows(std::integral_constant<int, 2>{});
+      else if (k <= 4)
+        rows(std::integral_constant<int, 4>{});
+      else if (k <= 8)
+        rows(std::integral_constant<int, 8>{});
+      else if (k <= 16)
+        rows(std::integral_constant<int, 16>{});
+      else
+        rows(std::integral_constant<int, 32>{});
     }
   };
   if (m->prec == GP_MIXED) {
