@@ -482,7 +482,7 @@ GP_API gp_status gp_mean_residual(gp_ctx* ctx, int64_t n, int32_t p, const doubl
  * values; opts->precond: block Jacobi, the default, or Jacobi), each stopping
  * when |c_s - K w_s| <= opts->rtol |c_s|; a float64 true residual is taken at
  * the end.  opts may be NULL (defaults; rtol, max_iter and precond are used).
- * Work space: six n x 32 float64 blocks.
+ * Work space: six n x 32 float64 blocks (n x 16, 8 or 1 for requests of so few points).
  * out (may be NULL) receives iteration counts and the largest final relative
  * residual.
  * Errors: GP_EINVAL (theta differs from K's, m < 0, NULL buffers),

@@ -1,15 +1,15 @@
 // Posterior variance of the latent process at test points (Sec. 3.2): the
 // diagonal of C_{y|z} = C_y - C_{y,z} C_z^{-1} C_{z,y},
 //   v(x*) = C_y(x*, x*) - c^T K^{-1} c,   c = C_{z,y}(., x*),
-// for 32 test points at a time:
-//   1. the cross-covariance columns c_s are written into an n x 32 block X
-//      (rows in binned order): a thread per test point adds the local
-//      (Wendland) entries of its cell window, then a wave per test point adds
-//      the bump-group entries over the masked training points;
-//   2. K W = X is solved by 32 conjugate-gradient recurrences in lockstep
+// for up to 32 test points at a time:
+//   1. the cross-covariance columns c_s are written into an n x C block X (C = 32,
+//      fewer for the last few of a request; rows in binned order): a thread per
+//      test point adds the local (Wendland) entries of its cell window, then a
+//      wave per test point adds the bump-group entries over the masked training
+//      points;
+//   2. K W = X is solved by as many conjugate-gradient recurrences in lockstep
 //      (one SpMM per step; block-Jacobi or Jacobi preconditioner; per-column
-//      scalars; a column
-//      stops changing once |r_s| <= rtol |c_s|), with a float64 true residual
+//      scalars; a column stops changing once |r_s| <= rtol |c_s|), with a float64 true residual
 //      X - K W at the end (the recurrences restart from it if it is not small
 //      enough);
 //   3. v_s = C_y(x*_s, x*_s) - sum_q X[q, s] W[q, s].
@@ -25,17 +25,22 @@ namespace gps {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kC = 32;                 // right-hand sides per batch
-constexpr int kRowsPer = kThreads / kC;  // rows handled together by a block
+constexpr int kC = 32;                 // right-hand sides per batch at most
 // The reductions end in one block that adds every block's partials: few, large
 // blocks leave it little to add (1024 blocks of 256 threads took it 12 - 18 us
 // an iteration, longer than the pass it closed at n = 50,021).
-constexpr int kRThreads = 1024;        // threads of the reducing passes
+// A block of C right-hand sides (32, or 16, 8 or 1 for the last of a request)
+// takes 32 rows at a time, one column at least 256.
+template <int C>
+constexpr int rows() { return C >= 8 ? 32 : 256 / C; }  // rows handled together by a block of the reducing passes
+template <int C>
+constexpr int threads() { return rows<C>() * C; }
 constexpr unsigned kVBlocks = 512;     // their blocks at most
-constexpr int kRRows = kRThreads / kC; // rows handled together by one of them
 constexpr int kRowBatch = 4;           // strided rows a thread loads at once in the column reductions
-constexpr int kTile = 64;              // rows of a tile of the update, before whole Jacobi blocks
-constexpr int kTileMax = kTile + kMaxBlock - 1;
+template <int C>
+constexpr int tile() { return rows<C>() > 64 ? rows<C>() : 64; }  // rows of a tile of the update, before whole Jacobi blocks
+template <int C>
+constexpr int tile_max() { return tile<C>() + kMaxBlock - 1; }
 constexpr int kCheckEvery = 8;
 constexpr int kMaxRefresh = 3;
 
@@ -75,7 +80,7 @@ __global__ void __launch_bounds__(kThreads) k_zero(int64_t len, double* __restri
 // local part of c_s: C_core(x*, x_q) s0 f0(u) for the training points of the
 // cell window with u0^2 < 1 (each q once)
 template <int D, int CK>
-__global__ void __launch_bounds__(kThreads) k_cross_local(CrossArgs a, CoreBasis cb, int nb,
+__global__ void __launch_bounds__(kThreads) k_cross_local(CrossArgs a, CoreBasis cb, int nb, int ld,
                                                           const double* __restrict__ xs, double* __restrict__ X) {
   const int s = blockIdx.x * kThreads + threadIdx.x;
   if (s >= nb) return;
@@ -107,7 +112,7 @@ __global__ void __launch_bounds__(kThreads) k_cross_local(CrossArgs a, CoreBasis
           if constexpr (CK == 1) v = core_value<D, 1>(a.kt.core, xp, xq, 0.0, 0.0, 0.0, 0.0) * v;
           if constexpr (CK == 2)
             v = core_value<D, 2>(a.kt.core, xp, xq, sp, Sp, a.kt.core.sig[q], a.kt.core.Sig[q]) * v;
-          X[static_cast<int64_t>(q) * kC + s] = v;
+          X[static_cast<int64_t>(q) * ld + s] = v;
         }
       }
     }
@@ -116,7 +121,7 @@ __global__ void __launch_bounds__(kThreads) k_cross_local(CrossArgs a, CoreBasis
 // bump-group part of c_s and the prior variance C_y(x*, x*): one wave per
 // test point; lane i < n1 forms f_i(x*) (bumps of group i in j order)
 template <int D, int CK>
-__global__ void __launch_bounds__(kThreads) k_cross_groups(CrossArgs a, CoreBasis cb, int nb,
+__global__ void __launch_bounds__(kThreads) k_cross_groups(CrossArgs a, CoreBasis cb, int nb, int ld,
                                                            const double* __restrict__ xs, double* __restrict__ X,
                                                            double* __restrict__ prior) {
   __shared__ double fs[kThreads / kWave][kWave];
@@ -179,48 +184,53 @@ __global__ void __launch_bounds__(kThreads) k_cross_groups(CrossArgs a, CoreBasi
         bsum = core_value<D, 2>(a.kt.core, xp, xq, sp, Sp, a.kt.core.sig[q], a.kt.core.Sig[q]) * bsum;
     }
     // one wave owns column s, so these read-modify-writes do not race
-    X[static_cast<int64_t>(q) * kC + s] += bsum;
+    X[static_cast<int64_t>(q) * ld + s] += bsum;
   }
 }
 
 // ------------------------------------------------------- column reductions
-// Thread (r, col) = (threadIdx.x / 32, threadIdx.x % 32) of kRThreads takes rows
-// r, r + 32, ... of the block's share; per block and column the NV partial sums
-// go to part[(blockIdx.x * NV + v) * 32 + col].  A wave first adds its two rows,
-// then thread (v, col) the waves in order.
-template <int NV>
+// Thread (r, col) = (threadIdx.x / C, threadIdx.x % C) takes rows
+// r, r + rows<C>(), ... of the block's share; per block and column the NV partial sums
+// go to part[(blockIdx.x * NV + v) * C + col].  A wave first adds its rows, then
+// thread (v, col) the waves in order.
+template <int C>
+__device__ __forceinline__ double add_wave_rows(double v) {
+#pragma unroll
+  for (int off = kWave / 2; off >= C; off >>= 1) v += __shfl_xor(v, off, kWave);
+  return v;
+}
+
+template <int NV, int C>
 __device__ __forceinline__ void col_partials(const double (&v)[NV], double* __restrict__ part) {
-  constexpr int kW = kRThreads / kWave;
-  __shared__ double sh[NV][kW][kC];
-  const int col = threadIdx.x % kC, w = threadIdx.x / kWave;
+  constexpr int kW = threads<C>() / kWave;
+  __shared__ double sh[NV][kW][C];
+  const int col = threadIdx.x % C, w = threadIdx.x / kWave;
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
-    const double t = v[i] + __shfl_xor(v[i], kC, kWave);
-    if (lane_id() < kC) sh[i][w][col] = t;
+    const double t = add_wave_rows<C>(v[i]);
+    if (lane_id() < C) sh[i][w][col] = t;
   }
   __syncthreads();
-  if (threadIdx.x < NV * kC) {
-    const int i = threadIdx.x / kC;
+  if (threadIdx.x < NV * C) {
+    const int i = threadIdx.x / C;
     double s = 0.0;
 #pragma unroll
     for (int k = 0; k < kW; ++k) s += sh[i][k][col];
-    part[(static_cast<int64_t>(blockIdx.x) * NV + i) * kC + col] = s;
+    part[(static_cast<int64_t>(blockIdx.x) * NV + i) * C + col] = s;
   }
 }
 
 // Column totals of the partials of nb blocks, in a fixed order: thread
-// (chunk, col) of a kFinThreads-thread block adds the partials of blocks chunk,
-// chunk + 32, ... (eight loaded at once), a wave its two chunks, then thread
-// (v, col) the waves in order.  tot[0] is the total of value threadIdx.x / 32,
-// valid in threads 0 .. 32 NV - 1 (column threadIdx.x % 32); every thread of the
+// (chunk, col) adds the partials of blocks chunk, chunk + rows<C>(), ...
+// (eight loaded at once), a wave its chunks, then thread
+// (v, col) the waves in order.  The result is the total of value threadIdx.x / C,
+// valid in threads 0 .. C NV - 1 (column threadIdx.x % C); every thread of the
 // block must call it.
-constexpr int kFinThreads = 1024;
-
-template <int NV>
+template <int NV, int C>
 __device__ __forceinline__ double col_total(const double* __restrict__ part, int nb) {
-  constexpr int kW = kFinThreads / kWave, kChunks = kFinThreads / kC, kB = 8;
-  __shared__ double sh[NV][kW][kC];
-  const int col = threadIdx.x % kC, ch = threadIdx.x / kC;
+  constexpr int kW = threads<C>() / kWave, kChunks = rows<C>(), kB = 8;
+  __shared__ double sh[NV][kW][C];
+  const int col = threadIdx.x % C, ch = threadIdx.x / C;
   double s[NV];
 #pragma unroll
   for (int v = 0; v < NV; ++v) s[v] = 0.0;
@@ -231,7 +241,7 @@ __device__ __forceinline__ double col_total(const double* __restrict__ part, int
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         const int b = b0 + u * kChunks;
-        t[u][v] = b < nb ? part[(static_cast<int64_t>(b) * NV + v) * kC + col] : 0.0;
+        t[u][v] = b < nb ? part[(static_cast<int64_t>(b) * NV + v) * C + col] : 0.0;
       }
 #pragma unroll
     for (int u = 0; u < kB; ++u)
@@ -240,23 +250,24 @@ __device__ __forceinline__ double col_total(const double* __restrict__ part, int
   }
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
-    const double t = s[v] + __shfl_xor(s[v], kC, kWave);
-    if (lane_id() < kC) sh[v][threadIdx.x / kWave][col] = t;
+    const double t = add_wave_rows<C>(s[v]);
+    if (lane_id() < C) sh[v][threadIdx.x / kWave][col] = t;
   }
   __syncthreads();
   double r = 0.0;
-  if (threadIdx.x < NV * kC)
+  if (threadIdx.x < NV * C)
 #pragma unroll
-    for (int k = 0; k < kW; ++k) r += sh[threadIdx.x / kC][k][col];
+    for (int k = 0; k < kW; ++k) r += sh[threadIdx.x / C][k][col];
   return r;
 }
 
-// The totals of two values: both valid in threads 0 .. 31 (the second handed
-// over from threads 32 .. 63 of the same wave).
+// The totals of two values: both valid in threads 0 .. C - 1 (the second handed
+// over from threads C .. 2 C - 1 of the same wave).
+template <int C>
 __device__ __forceinline__ void col_totals2(const double* __restrict__ part, int nb, double (&tot)[2]) {
-  const double t = col_total<2>(part, nb);
+  const double t = col_total<2, C>(part, nb);
   tot[0] = t;
-  tot[1] = __shfl_xor(t, kC, kWave);
+  tot[1] = __shfl_xor(t, C, kWave);
 }
 
 // Preconditioner of the recurrences: the matrix diagonal, or (binv set) the
@@ -271,10 +282,11 @@ struct VarPrecond {
 };
 
 // Rows of tile k: from the first Jacobi block that starts at or after row
-// kTile k to the one that starts at or after row kTile (k + 1), so that a tile
-// holds whole blocks (at most kTileMax rows) and the tiles hold every row once.
+// tile<C>() k to the one that starts at or after the next tile's, so that a tile
+// holds whole blocks (at most tile_max<C>() rows) and the tiles hold every row once.
+template <int C>
 __device__ __forceinline__ int64_t tile_start(const VarPrecond& M, int64_t n, int64_t k) {
-  const int64_t i = k * kTile;
+  const int64_t i = k * tile<C>();
   if (i >= n) return n;
   if (!M.binv) return i;
   const BlockRow br(M.brow[i]);
@@ -286,17 +298,17 @@ __device__ __forceinline__ int64_t tile_start(const VarPrecond& M, int64_t n, in
 // The block product is rt's rows times the block's inverse: r is read once
 // from memory for the whole block instead of once per row of it, and a row's
 // inverse entries (stored by columns) are loaded eight at a time.
-template <typename F>
-__device__ __forceinline__ void tile_precond(const VarPrecond& M, int64_t lo, int64_t hi, double (*rt)[kC], F&& put) {
-  const int col = threadIdx.x % kC;
-  for (int64_t i = lo + threadIdx.x / kC; i < hi; i += kRRows) {
+template <int C, typename F>
+__device__ __forceinline__ void tile_precond(const VarPrecond& M, int64_t lo, int64_t hi, double (*rt)[C], F&& put) {
+  const int col = threadIdx.x % C;
+  for (int64_t i = lo + threadIdx.x / C; i < hi; i += rows<C>()) {
     const double r = rt[i - lo][col];
     double z = 0.0;
     if (M.binv) {
       const BlockRow br(M.brow[i]);
       const int sz = br.sz;
       const double* w = M.binv + br.pos;
-      const double(*rb)[kC] = rt + (i - br.k - lo);
+      const double(*rb)[C] = rt + (i - br.k - lo);
       constexpr int kB = 8;
       for (int j0 = 0; j0 < sz; j0 += kB) {
         double v[kB];
@@ -314,46 +326,48 @@ __device__ __forceinline__ void tile_precond(const VarPrecond& M, int64_t lo, in
 }
 
 #define ROW_LOOP(n)                                                                               \
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kRRows + threadIdx.x / kC; i < (n);       \
-       i += static_cast<int64_t>(gridDim.x) * kRRows)
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * rows<C>() + threadIdx.x / C; i < (n);       \
+       i += static_cast<int64_t>(gridDim.x) * rows<C>())
 
 // R = X - KW (KW given, or W = 0 when kw is null); Z = M^-1 R; P = Z;
 // partials of r.z and r.r
-__global__ void __launch_bounds__(kRThreads) k_bcg_start(int64_t n, const double* __restrict__ X,
+template <int C>
+__global__ void __launch_bounds__(threads<C>()) k_bcg_start(int64_t n, const double* __restrict__ X,
                                                          const double* __restrict__ kw, VarPrecond M,
                                                          double* __restrict__ R, double* __restrict__ Z,
                                                          double* __restrict__ P, double* __restrict__ part) {
-  __shared__ double rt[kTileMax][kC];
-  const int col = threadIdx.x % kC;
+  __shared__ double rt[tile_max<C>()][C];
+  const int col = threadIdx.x % C;
   double v[2] = {0.0, 0.0};
-  for (int64_t k = blockIdx.x; k * kTile < n; k += gridDim.x) {
-    const int64_t lo = tile_start(M, n, k), hi = tile_start(M, n, k + 1);
+  for (int64_t k = blockIdx.x; k * tile<C>() < n; k += gridDim.x) {
+    const int64_t lo = tile_start<C>(M, n, k), hi = tile_start<C>(M, n, k + 1);
     __syncthreads();  // the previous tile has been read
-    for (int64_t i = lo + threadIdx.x / kC; i < hi; i += kRRows) {
-      const int64_t e = i * kC + col;
+    for (int64_t i = lo + threadIdx.x / C; i < hi; i += rows<C>()) {
+      const int64_t e = i * C + col;
       const double r = kw ? X[e] - kw[e] : X[e];
       R[e] = r;
       rt[i - lo][col] = r;
     }
     __syncthreads();
-    tile_precond(M, lo, hi, rt, [&](int64_t i, double r, double z) {
-      const int64_t e = i * kC + col;
+    tile_precond<C>(M, lo, hi, rt, [&](int64_t i, double r, double z) {
+      const int64_t e = i * C + col;
       Z[e] = z;
       P[e] = z;
       v[0] += r * z;
       v[1] += r * r;
     });
   }
-  col_partials<2>(v, part);
+  col_partials<2, C>(v, part);
 }
 
 // mode 0: first start (|c|^2 = r.r, a column with c = 0 is never active);
 // mode 1: restart from the true residual (active columns stay active)
-__global__ void __launch_bounds__(kFinThreads) k_bcg_start_fin(const double* __restrict__ part, int nb,
+template <int C>
+__global__ void __launch_bounds__(threads<C>()) k_bcg_start_fin(const double* __restrict__ part, int nb,
                                                                BcgScalars* __restrict__ S, double tol2, int mode) {
   double t[2];
-  col_totals2(part, nb, t);
-  if (threadIdx.x >= kC) return;
+  col_totals2<C>(part, nb, t);
+  if (threadIdx.x >= C) return;
   const int col = threadIdx.x;
   const double rz = t[0], rr = t[1];
   S->rz[col] = rz;
@@ -367,31 +381,33 @@ __global__ void __launch_bounds__(kFinThreads) k_bcg_start_fin(const double* __r
   }
 }
 
-__global__ void __launch_bounds__(kRThreads) k_bcg_pq(int64_t n, const double* __restrict__ P,
+template <int C>
+__global__ void __launch_bounds__(threads<C>()) k_bcg_pq(int64_t n, const double* __restrict__ P,
                                                       const double* __restrict__ Q, double* __restrict__ part) {
   // four strided rows loaded at once, added in the order of the plain row loop
-  const int col = threadIdx.x % kC;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kRRows;
+  const int col = threadIdx.x % C;
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * rows<C>();
   double v[1] = {0.0};
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kRRows + threadIdx.x / kC; i < n; i += kRowBatch * stride) {
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * rows<C>() + threadIdx.x / C; i < n; i += kRowBatch * stride) {
     double pv[kRowBatch], qv[kRowBatch];
 #pragma unroll
     for (int u = 0; u < kRowBatch; ++u) {
       const int64_t k = i + u * stride;
-      pv[u] = k < n ? P[k * kC + col] : 0.0;
-      qv[u] = k < n ? Q[k * kC + col] : 0.0;
+      pv[u] = k < n ? P[k * C + col] : 0.0;
+      qv[u] = k < n ? Q[k * C + col] : 0.0;
     }
 #pragma unroll
     for (int u = 0; u < kRowBatch; ++u)
       if (i + u * stride < n) v[0] += pv[u] * qv[u];
   }
-  col_partials<1>(v, part);
+  col_partials<1, C>(v, part);
 }
 
-__global__ void __launch_bounds__(kFinThreads) k_bcg_alpha(const double* __restrict__ part, int nb,
+template <int C>
+__global__ void __launch_bounds__(threads<C>()) k_bcg_alpha(const double* __restrict__ part, int nb,
                                                            BcgScalars* __restrict__ S) {
-  const double t[1] = {col_total<1>(part, nb)};
-  if (threadIdx.x >= kC) return;
+  const double t[1] = {col_total<1, C>(part, nb)};
+  if (threadIdx.x >= C) return;
   const int col = threadIdx.x;
   const double pq = t[0];
   S->pq[col] = pq;
@@ -412,53 +428,55 @@ __global__ void __launch_bounds__(kFinThreads) k_bcg_alpha(const double* __restr
 // direction's pass, which reads P anyway: the iteration's vector passes move 11
 // blocks of n x 32 instead of 12 (n = 1,095,000: 886 -> 776 us with block Jacobi,
 // 646 -> 556 with Jacobi, whose 3.1 GB take 598 us at the rate of a large copy).
-__global__ void __launch_bounds__(kRThreads) k_bcg_update(int64_t n, const BcgScalars* __restrict__ S,
+template <int C>
+__global__ void __launch_bounds__(threads<C>()) k_bcg_update(int64_t n, const BcgScalars* __restrict__ S,
                                                           const double* __restrict__ Q, VarPrecond M,
                                                           double* __restrict__ R, double* __restrict__ Z,
                                                           double* __restrict__ part) {
-  __shared__ double rt[kTileMax][kC];
-  const int col = threadIdx.x % kC;
+  __shared__ double rt[tile_max<C>()][C];
+  const int col = threadIdx.x % C;
   const double a = S->alpha[col];
-  constexpr int kPer = (kTileMax + kRRows - 1) / kRRows;  // rows of a tile per thread
+  constexpr int kPer = (tile_max<C>() + rows<C>() - 1) / rows<C>();  // rows of a tile per thread
   double v[2] = {0.0, 0.0};
-  for (int64_t k = blockIdx.x; k * kTile < n; k += gridDim.x) {
-    const int64_t lo = tile_start(M, n, k), hi = tile_start(M, n, k + 1);
+  for (int64_t k = blockIdx.x; k * tile<C>() < n; k += gridDim.x) {
+    const int64_t lo = tile_start<C>(M, n, k), hi = tile_start<C>(M, n, k + 1);
     double rv[kPer], qv[kPer];
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
-      const int64_t i = lo + threadIdx.x / kC + u * kRRows;
-      rv[u] = i < hi ? R[i * kC + col] : 0.0;
-      qv[u] = i < hi ? Q[i * kC + col] : 0.0;
+      const int64_t i = lo + threadIdx.x / C + u * rows<C>();
+      rv[u] = i < hi ? R[i * C + col] : 0.0;
+      qv[u] = i < hi ? Q[i * C + col] : 0.0;
     }
     __syncthreads();  // the previous tile has been read
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
-      const int64_t i = lo + threadIdx.x / kC + u * kRRows;
+      const int64_t i = lo + threadIdx.x / C + u * rows<C>();
       if (i < hi) {
         const double r = rv[u] - a * qv[u];
-        R[i * kC + col] = r;
+        R[i * C + col] = r;
         rt[i - lo][col] = r;
       }
     }
     __syncthreads();
-    tile_precond(M, lo, hi, rt, [&](int64_t i, double r, double z) {
-      Z[i * kC + col] = z;
+    tile_precond<C>(M, lo, hi, rt, [&](int64_t i, double r, double z) {
+      Z[i * C + col] = z;
       v[0] += r * z;
       v[1] += r * r;
     });
   }
-  col_partials<2>(v, part);
+  col_partials<2, C>(v, part);
 }
 
 // The same pass with the block product on the matrix cores, for larger blocks
-// (kBigBlock): Z[block, 0:32] = Binv R[block, 0:32], b x b times b x 32, is a
+// (kBigBlock): Z[block, 0:C] = Binv R[block, 0:C], b x b times b x C, is a
 // dense contraction, and with 16 x 16 x 4 FP64 MFMAs a wave loads each inverse
-// entry once for 32 columns instead of once per row and half-wave (broadcast
+// entry once for C columns instead of once per row and half-wave (broadcast
 // loads, which the address unit serves no faster than scattered ones).  A wave
 // takes the tile's blocks in turn; lane (i, kk) = (lane % 16, lane / 16) holds
 // A[i][kk] = Binv(16 rb + i, 4 s + kk), B[kk][i] = R(4 s + kk, i) from LDS, and
-// of the result the rows 16 rb + kk + 4 v, v = 0..3, of columns i and i + 16.
-// Entries past the block have weight 0.
+// of the result the rows 16 rb + kk + 4 v, v = 0..3, of columns i and (C = 32)
+// i + 16.  Entries past the block have weight 0; with C = 8 the lanes i >= 8 repeat
+// a column and keep nothing.
 // Vector work of an iteration, n = 50,021 (mixture, blocks up to 32): 104.3 us with
 // each row reading its block's R and Q from memory, 65.4 with k_bcg_update, 54.1
 // with this; small blocks only pay the padding (space-time n = 109,500, 2.8 points a
@@ -470,29 +488,32 @@ constexpr int kMWaves = kMThreads / kWave;
 constexpr int kMSteps = kMaxBlock / 4;  // k-steps of a block at most
 constexpr int kBigBlock = 8;
 
+template <int C>
 __global__ void __launch_bounds__(kMThreads) k_bcg_update_mfma(int64_t n, const BcgScalars* __restrict__ S,
                                                                const double* __restrict__ Q, VarPrecond M,
                                                                double* __restrict__ R, double* __restrict__ Z,
                                                                double* __restrict__ part) {
-  __shared__ double rt[kTileMax][kC];
-  __shared__ double red[2][kMWaves][kC];
-  constexpr int kTRows = kMThreads / kC;
-  constexpr int kPer = (kTileMax + kTRows - 1) / kTRows;
-  const int col = threadIdx.x % kC, w = threadIdx.x / kWave, lane = lane_id();
+  __shared__ double rt[tile_max<C>()][C];
+  __shared__ double red[2][kMWaves][C];
+  constexpr int kTRows = kMThreads / C;
+  constexpr int kPer = (tile_max<C>() + kTRows - 1) / kTRows;
+  const int col = threadIdx.x % C, w = threadIdx.x / kWave, lane = lane_id();
   const int i = lane & 15, kk = lane >> 4;
   const double a = S->alpha[col];
-  double rz[2] = {0.0, 0.0}, rr[2] = {0.0, 0.0};  // of columns i and i + 16
-  for (int64_t k = blockIdx.x; k * kTile < n; k += gridDim.x) {
-    const int64_t lo = tile_start(M, n, k), hi = tile_start(M, n, k + 1);
+  constexpr int kNB = (C + 15) / 16;
+  const bool mine = C >= 16 || i < C;
+  double rz[kNB] = {}, rr[kNB] = {};  // of columns i and i + 16
+  for (int64_t k = blockIdx.x; k * tile<C>() < n; k += gridDim.x) {
+    const int64_t lo = tile_start<C>(M, n, k), hi = tile_start<C>(M, n, k + 1);
     double rv[kPer], qv[kPer];
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
-      const int64_t r = lo + threadIdx.x / kC + u * kTRows;
-      rv[u] = r < hi ? R[r * kC + col] : 0.0;
-      qv[u] = r < hi ? Q[r * kC + col] : 0.0;
+      const int64_t r = lo + threadIdx.x / C + u * kTRows;
+      rv[u] = r < hi ? R[r * C + col] : 0.0;
+      qv[u] = r < hi ? Q[r * C + col] : 0.0;
     }
     // the tile's rows lane and lane + 64: where a Jacobi block starts, and its place
-    static_assert(kTileMax <= 2 * kWave, "two rows per lane");
+    static_assert(tile_max<C>() <= 2 * kWave, "two rows per lane");
     uint64_t place[2], starts[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -503,10 +524,10 @@ __global__ void __launch_bounds__(kMThreads) k_bcg_update_mfma(int64_t n, const 
     __syncthreads();  // the previous tile has been read
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
-      const int64_t r = lo + threadIdx.x / kC + u * kTRows;
+      const int64_t r = lo + threadIdx.x / C + u * kTRows;
       if (r < hi) {
         const double x = rv[u] - a * qv[u];
-        R[r * kC + col] = x;
+        R[r * C + col] = x;
         rt[r - lo][col] = x;
       }
     }
@@ -524,12 +545,12 @@ __global__ void __launch_bounds__(kMThreads) k_bcg_update_mfma(int64_t n, const 
       const int64_t bs = lo + src + h * kWave;
       const int sz = br.sz;
       const double* binv = M.binv + br.pos;
-      const double(*rb)[kC] = rt + (bs - lo);
-      d4 acc[2][2];
+      const double(*rb)[C] = rt + (bs - lo);
+      d4 acc[2][kNB];
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int c = 0; c < 2; ++c) acc[t][c] = d4{0.0, 0.0, 0.0, 0.0};
+        for (int c = 0; c < kNB; ++c) acc[t][c] = d4{0.0, 0.0, 0.0, 0.0};
       double av[2][kMSteps];
 #pragma unroll
       for (int s = 0; s < kMSteps; ++s) {
@@ -545,12 +566,15 @@ __global__ void __launch_bounds__(kMThreads) k_bcg_update_mfma(int64_t n, const 
       for (int s = 0; s < kMSteps; ++s) {
         if (4 * s >= sz) break;
         const int q = min(4 * s + kk, sz - 1);
-        const double bl = rb[q][i], bh = rb[q][i + 16];
+        double b[kNB];
+#pragma unroll
+        for (int c = 0; c < kNB; ++c) b[c] = rb[q][(i + 16 * c) % C];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
           if (16 * t >= sz) break;
-          acc[t][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[t][s], bl, acc[t][0], 0, 0, 0);
-          acc[t][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[t][s], bh, acc[t][1], 0, 0, 0);
+#pragma unroll
+          for (int c = 0; c < kNB; ++c)
+            acc[t][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[t][s], b[c], acc[t][c], 0, 0, 0);
         }
       }
 #pragma unroll
@@ -558,10 +582,10 @@ __global__ void __launch_bounds__(kMThreads) k_bcg_update_mfma(int64_t n, const 
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int r = 16 * t + kk + 4 * v;
-          if (r >= sz) continue;
-          double* zr = Z + (bs + r) * kC;
+          if (r >= sz || !mine) continue;
+          double* zr = Z + (bs + r) * C;
 #pragma unroll
-          for (int c = 0; c < 2; ++c) {
+          for (int c = 0; c < kNB; ++c) {
             const double x = rb[r][i + 16 * c], z = acc[t][c][v];
             zr[i + 16 * c] = z;
             rz[c] += x * z;
@@ -572,32 +596,33 @@ __global__ void __launch_bounds__(kMThreads) k_bcg_update_mfma(int64_t n, const 
   }
   // the four lanes of a column, then the waves in order
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
+  for (int c = 0; c < kNB; ++c) {
 #pragma unroll
     for (int off = 16; off < kWave; off <<= 1) {
       rz[c] += __shfl_xor(rz[c], off, kWave);
       rr[c] += __shfl_xor(rr[c], off, kWave);
     }
-    if (kk == 0) {
+    if (kk == 0 && mine) {
       red[0][w][i + 16 * c] = rz[c];
       red[1][w][i + 16 * c] = rr[c];
     }
   }
   __syncthreads();
-  if (threadIdx.x < 2 * kC) {
-    const int v = threadIdx.x / kC;
+  if (threadIdx.x < 2 * C) {
+    const int v = threadIdx.x / C;
     double s = 0.0;
 #pragma unroll
     for (int q = 0; q < kMWaves; ++q) s += red[v][q][col];
-    part[(static_cast<int64_t>(blockIdx.x) * 2 + v) * kC + col] = s;
+    part[(static_cast<int64_t>(blockIdx.x) * 2 + v) * C + col] = s;
   }
 }
 
-__global__ void __launch_bounds__(kFinThreads) k_bcg_beta(const double* __restrict__ part, int nb,
+template <int C>
+__global__ void __launch_bounds__(threads<C>()) k_bcg_beta(const double* __restrict__ part, int nb,
                                                           BcgScalars* __restrict__ S, double tol2) {
   double t[2];
-  col_totals2(part, nb, t);
-  if (threadIdx.x >= kC) return;
+  col_totals2<C>(part, nb, t);
+  if (threadIdx.x >= C) return;
   const int col = threadIdx.x;
   const double rz = t[0], rr = t[1];
   const bool act = S->active[col] != 0;
@@ -608,43 +633,46 @@ __global__ void __launch_bounds__(kFinThreads) k_bcg_beta(const double* __restri
 }
 
 // W += alpha P, and P = Z + beta P for the active columns (a row per thread)
+template <int C>
 __global__ void __launch_bounds__(kThreads) k_bcg_dir(int64_t n, const BcgScalars* __restrict__ S,
                                                       const double* __restrict__ Z, double* __restrict__ P,
                                                       double* __restrict__ W) {
-  const int col = threadIdx.x % kC;
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * kRowsPer + threadIdx.x / kC;
+  const int col = threadIdx.x % C;
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * (kThreads / C) + threadIdx.x / C;
   if (i >= n) return;
   const double a = S->alpha[col], b = S->beta[col];
   const bool act = S->active[col] != 0;
   if (a == 0.0 && !act) return;  // a column that ended earlier
-  const int64_t e = i * kC + col;
+  const int64_t e = i * C + col;
   const double p = P[e], w = W[e], z = act ? Z[e] : 0.0;
   W[e] = w + a * p;
   if (act) P[e] = z + b * p;
 }
 
 // partials of the true residual |X - KW|^2 and of X.W per column
-__global__ void __launch_bounds__(kRThreads) k_bcg_final(int64_t n, const double* __restrict__ X,
+template <int C>
+__global__ void __launch_bounds__(threads<C>()) k_bcg_final(int64_t n, const double* __restrict__ X,
                                                         const double* __restrict__ kw, const double* __restrict__ W,
                                                         double* __restrict__ part) {
-  const int col = threadIdx.x % kC;
+  const int col = threadIdx.x % C;
   double v[2] = {0.0, 0.0};
   ROW_LOOP(n) {
-    const int64_t e = i * kC + col;
+    const int64_t e = i * C + col;
     const double r = X[e] - kw[e];
     v[0] += r * r;
     v[1] += X[e] * W[e];
   }
-  col_partials<2>(v, part);
+  col_partials<2, C>(v, part);
 }
 
 // true residual per column into S->rr; v_s = prior_s - c_s . w_s for s < nbatch
-__global__ void __launch_bounds__(kFinThreads) k_bcg_var(const double* __restrict__ part, int nb,
+template <int C>
+__global__ void __launch_bounds__(threads<C>()) k_bcg_var(const double* __restrict__ part, int nb,
                                                          BcgScalars* __restrict__ S, const double* __restrict__ prior,
                                                          int nbatch, double* __restrict__ var) {
   double t[2];
-  col_totals2(part, nb, t);
-  if (threadIdx.x >= kC) return;
+  col_totals2<C>(part, nb, t);
+  if (threadIdx.x >= C) return;
   const int col = threadIdx.x;
   const double rr = t[0], cw = t[1];
   S->rr[col] = rr;
@@ -670,6 +698,15 @@ void dispatch_dk(int d, int kind, F3&& f) {
   else
     with_d(std::integral_constant<int, 3>{});
 }
+
+// Columns of the block that takes nb right-hand sides: the narrowest there is.  An
+// iteration in blocks of 1 / 8 / 16 / 32: n = 50,021 (mixture, mixed, block Jacobi)
+// 30 / 65 / 80 / 107 us, n = 20,021 (FP64, Jacobi) 27 / 43 / 50 / 73, n = 109,500 (space-time)
+// 67 / 135 / 174 / 243; every request took blocks of 32 before.  Two narrow blocks
+// cost more than one that holds both, so only the last block of a request is
+// narrow.  Widths of 2 and 4 would save little on 8: its small kernels are at
+// their latency.
+int width(int nb) { return nb <= 1 ? 1 : nb <= 8 ? 8 : nb <= 16 ? 16 : kC; }
 
 }  // namespace
 
@@ -719,7 +756,9 @@ VarResult predict_variance(gp_ctx* c, const gp_matrix* m, const gp_theta* th, in
   a.mmask = f.mmask;
   a.F = f.F;
 
-  const size_t blk = sizeof(double) * n * kC;
+  // the widest block of right-hand sides of the request (see width)
+  const int cmax = width(static_cast<int>(std::min<int64_t>(kC, ntest)));
+  const size_t blk = sizeof(double) * n * cmax;
   double* X = static_cast<double*>(workspace(c, 110, blk));
   double* R = static_cast<double*>(workspace(c, 111, blk));
   double* Z = static_cast<double*>(workspace(c, 112, blk));
@@ -730,42 +769,50 @@ VarResult predict_variance(gp_ctx* c, const gp_matrix* m, const gp_theta* th, in
   BcgScalars* S = static_cast<BcgScalars*>(workspace(c, 117, sizeof(BcgScalars)));
   double* prior = static_cast<double*>(workspace(c, 118, sizeof(double) * kC));
   BcgScalars* hs = static_cast<BcgScalars*>(pinned(c, sizeof(BcgScalars)));
-  const unsigned nbv = static_cast<unsigned>(std::min<int64_t>(kVBlocks, (n + kTile - 1) / kTile));
   // the matrix-core update pays for padding to 16 rows: see kBigBlock
   const bool mfma = M.binv && m->binv_len > kBigBlock * n;  // sum of b^2 over sum of b: the block a row sees on average
-  const unsigned nbm = static_cast<unsigned>(std::min<int64_t>(2 * kVBlocks, (n + kTile - 1) / kTile));
-  const dim3 B(kThreads), RB(kRThreads), G(nbv), GM(nbm), FB(kFinThreads);
-  // element-wise kernels without a reduction take a row per thread
-  const dim3 Gfull(static_cast<unsigned>((n + kRowsPer - 1) / kRowsPer));
   const double tol2 = rtol * rtol;
   auto read = [&]() {
     GPS_HIP(hipMemcpyAsync(hs, S, sizeof(BcgScalars), hipMemcpyDeviceToHost, c->stream));
     sync(c);
     return *hs;
   };
-  for (int64_t m0 = 0; m0 < ntest; m0 += kC) {
-    const int nb = static_cast<int>(std::min<int64_t>(kC, ntest - m0));
+  // test points m0 .. m0 + nb - 1 in a block of C >= nb columns
+  auto batch = [&](auto CC, int64_t m0, int nb) {
+    constexpr int C = decltype(CC)::value;
     const double* xb = xs + m0 * d;
+    const int64_t ntiles = (n + tile<C>() - 1) / tile<C>();
+    const unsigned nbv = static_cast<unsigned>(std::min<int64_t>(kVBlocks, ntiles));
+    const unsigned nbm = static_cast<unsigned>(std::min<int64_t>(2 * kVBlocks, ntiles));
+    const dim3 B(kThreads), RB(threads<C>()), G(nbv), FB(threads<C>());
+    auto product = [&](const double* V, double* out) {
+      if constexpr (C == 1)
+        spmv_f64(c, m, V, out);
+      else
+        spmm<double>(c, m, C, C, V, out, nullptr);
+    };
+    // element-wise kernels without a reduction take a row per thread
+    const dim3 Gfull(static_cast<unsigned>(grid_for(n * C, kThreads)));
     {
       ProfScope ps(c, "var_cross");
-      hipLaunchKernelGGL(k_zero, dim3(grid_for(n * kC, kThreads)), B, 0, c->stream, n * kC, X);
+      hipLaunchKernelGGL(k_zero, dim3(grid_for(n * C, kThreads)), B, 0, c->stream, n * C, X);
       dispatch_dk(d, kt.core.kind, [&](auto DD, auto CC) {
         constexpr int D = decltype(DD)::value;
         constexpr int CK = decltype(CC)::value;
-        hipLaunchKernelGGL((k_cross_local<D, CK>), dim3(1), B, 0, c->stream, a, cb, nb, xb, X);
+        hipLaunchKernelGGL((k_cross_local<D, CK>), dim3(1), B, 0, c->stream, a, cb, nb, C, xb, X);
         hipLaunchKernelGGL((k_cross_groups<D, CK>), dim3((nb * kWave + kThreads - 1) / kThreads), B, 0, c->stream,
-                           a, cb, nb, xb, X, prior);
+                           a, cb, nb, C, xb, X, prior);
       });
       check_launch("variance cross-covariance");
     }
-    hipLaunchKernelGGL(k_zero, dim3(grid_for(n * kC, kThreads)), B, 0, c->stream, n * kC, W);
-    hipLaunchKernelGGL(k_bcg_start, G, RB, 0, c->stream, n, X, nullptr, M, R, Z, P, part);
-    hipLaunchKernelGGL(k_bcg_start_fin, dim3(1), FB, 0, c->stream, part, static_cast<int>(nbv), S, tol2, 0);
+    hipLaunchKernelGGL(k_zero, dim3(grid_for(n * C, kThreads)), B, 0, c->stream, n * C, W);
+    hipLaunchKernelGGL(k_bcg_start<C>, G, RB, 0, c->stream, n, X, nullptr, M, R, Z, P, part);
+    hipLaunchKernelGGL(k_bcg_start_fin<C>, dim3(1), FB, 0, c->stream, part, static_cast<int>(nbv), S, tol2, 0);
     check_launch("variance start");
     BcgScalars hsc = read();
     int it = 0, refresh = 0;
     auto any_active = [](const BcgScalars& s) {
-      for (int j = 0; j < kC; ++j)
+      for (int j = 0; j < C; ++j)
         if (s.active[j]) return true;
       return false;
     };
@@ -773,9 +820,9 @@ VarResult predict_variance(gp_ctx* c, const gp_matrix* m, const gp_theta* th, in
       if (!any_active(hsc)) {
         // recurrences done: check the float64 true residual, restart once it is not small enough
         if (refresh >= kMaxRefresh) break;
-        spmm<double>(c, m, kC, kC, W, Q, nullptr);
-        hipLaunchKernelGGL(k_bcg_start, G, RB, 0, c->stream, n, X, Q, M, R, Z, P, part);
-        hipLaunchKernelGGL(k_bcg_start_fin, dim3(1), FB, 0, c->stream, part, static_cast<int>(nbv), S, tol2, 1);
+        product(W, Q);
+        hipLaunchKernelGGL(k_bcg_start<C>, G, RB, 0, c->stream, n, X, Q, M, R, Z, P, part);
+        hipLaunchKernelGGL(k_bcg_start_fin<C>, dim3(1), FB, 0, c->stream, part, static_cast<int>(nbv), S, tol2, 1);
         check_launch("variance restart");
         ++refresh;
         hsc = read();
@@ -784,25 +831,29 @@ VarResult predict_variance(gp_ctx* c, const gp_matrix* m, const gp_theta* th, in
       }
       const int steps = std::min(kCheckEvery, max_iter - it);
       for (int t = 0; t < steps; ++t) {
-        spmm<double>(c, m, kC, kC, P, Q, nullptr);
+        product(P, Q);
         ProfScope ps(c, "var_vector_ops");
-        hipLaunchKernelGGL(k_bcg_pq, G, RB, 0, c->stream, n, P, Q, part);
-        hipLaunchKernelGGL(k_bcg_alpha, dim3(1), FB, 0, c->stream, part, static_cast<int>(nbv), S);
-        if (mfma)
-          hipLaunchKernelGGL(k_bcg_update_mfma, GM, B, 0, c->stream, n, S, Q, M, R, Z, part);
-        else
-          hipLaunchKernelGGL(k_bcg_update, G, RB, 0, c->stream, n, S, Q, M, R, Z, part);
-        hipLaunchKernelGGL(k_bcg_beta, dim3(1), FB, 0, c->stream, part, static_cast<int>(mfma ? nbm : nbv), S, tol2);
-        hipLaunchKernelGGL(k_bcg_dir, Gfull, B, 0, c->stream, n, S, Z, P, W);
+        hipLaunchKernelGGL(k_bcg_pq<C>, G, RB, 0, c->stream, n, P, Q, part);
+        hipLaunchKernelGGL(k_bcg_alpha<C>, dim3(1), FB, 0, c->stream, part, static_cast<int>(nbv), S);
+        unsigned np = nbv;
+        if constexpr (C >= 8) {
+          if (mfma) {
+            np = nbm;
+            hipLaunchKernelGGL(k_bcg_update_mfma<C>, dim3(nbm), B, 0, c->stream, n, S, Q, M, R, Z, part);
+          }
+        }
+        if (C < 8 || !mfma) hipLaunchKernelGGL(k_bcg_update<C>, G, RB, 0, c->stream, n, S, Q, M, R, Z, part);
+        hipLaunchKernelGGL(k_bcg_beta<C>, dim3(1), FB, 0, c->stream, part, static_cast<int>(np), S, tol2);
+        hipLaunchKernelGGL(k_bcg_dir<C>, Gfull, B, 0, c->stream, n, S, Z, P, W);
         check_launch("variance step");
       }
       it += steps;
       hsc = read();
     }
     // true residual and the variances of this batch
-    spmm<double>(c, m, kC, kC, W, Q, nullptr);
-    hipLaunchKernelGGL(k_bcg_final, G, RB, 0, c->stream, n, X, Q, W, part);
-    hipLaunchKernelGGL(k_bcg_var, dim3(1), FB, 0, c->stream, part, static_cast<int>(nbv), S, prior, nb, var + m0);
+    product(W, Q);
+    hipLaunchKernelGGL(k_bcg_final<C>, G, RB, 0, c->stream, n, X, Q, W, part);
+    hipLaunchKernelGGL(k_bcg_var<C>, dim3(1), FB, 0, c->stream, part, static_cast<int>(nbv), S, prior, nb, var + m0);
     check_launch("variance final");
     hsc = read();
     res.iters += it;
@@ -817,6 +868,22 @@ VarResult predict_variance(gp_ctx* c, const gp_matrix* m, const gp_theta* th, in
       res.st = GP_ENOTPD;
     else if (!ok && res.st == GP_OK)
       res.st = GP_ENOTCONV;
+  };
+  for (int64_t m0 = 0; m0 < ntest; m0 += kC) {
+    const int nb = static_cast<int>(std::min<int64_t>(kC, ntest - m0));
+    switch (width(nb)) {
+      case 1:
+        batch(std::integral_constant<int, 1>{}, m0, nb);
+        break;
+      case 8:
+        batch(std::integral_constant<int, 8>{}, m0, nb);
+        break;
+      case 16:
+        batch(std::integral_constant<int, 16>{}, m0, nb);
+        break;
+      default:
+        batch(std::integral_constant<int, 32>{}, m0, nb);
+    }
   }
   return res;
 }
