@@ -221,6 +221,16 @@ __global__ void __launch_bounds__(kThreads) k_check_tau2(int64_t n, const double
 // with coalesced loads and every lane scans its own range there; otherwise
 // the lanes read the points from global memory.  A row with a group bit reads
 // its candidates' masks from global memory (few rows have one).
+//
+// A hit's value is many times the work of a test, and formed within the scan it is
+// formed by the few lanes of the wave whose candidate is one at that step.  Where
+// that shows, a lane's scan only marks its hits (kMaskBits candidates at a time) and
+// the lanes then form theirs together: fill of 292,000 rows with a Matern / Paciorek
+// core 345 -> 294 / 497 -> 384 us, 10^6 uniform rows with d = 1 / 2 119 -> 105 / 161 -> 138.
+// Pencils of the plain kernel with d = 3 hold too few hits each (1.1M rows, 1.7 of
+// 7.5 candidates: 558 -> 585), and hits queued in LDS over several pencils cost as
+// much to queue as they save (664; 584 with half the stage): they keep the scan.
+constexpr int kMaskBits = 32;
 constexpr int kBuf = 4;
 constexpr int kStage = 256;
 constexpr int kCu = 2;  // candidates whose global loads are in flight together
@@ -237,6 +247,7 @@ __device__ __forceinline__ void wave_sync_lds() {
 // checks that they are exactly the rest of the row.
 template <int D, bool FILL, typename VT, int CK = 0>
 __global__ void __launch_bounds__(kThreads) k_local_rows(AsmArgs a) {
+  constexpr bool kHits = FILL && (CK != 0 || D < 3);
   __shared__ double stage[kThreads / kWave][D][kStage];
   // each XCD takes a contiguous range of rows: their candidates and output
   // cache lines stay within its L2
@@ -326,26 +337,35 @@ __global__ void __launch_bounds__(kThreads) k_local_rows(AsmArgs a) {
           for (int k = 0; k < D; ++k) st[k][j] = xq[k];
         }
         wave_sync_lds();
-        // two candidates per step (independent chains); an odd last one alone
-        int32_t q = s;
-        for (; q + 1 < e; q += 2) {
-          double xa[3], xb2[3];
-#pragma unroll
-          for (int k = 0; k < D; ++k) {
-            xa[k] = st[k][q - lo];
-            xb2[k] = st[k][q + 1 - lo];
-          }
-          const double ua = scaled_sq<D>(xp, xa, a.kt.inv0);
-          const double ub = scaled_sq<D>(xp, xb2, a.kt.inv0);
-          if (local(q, ua)) hit_at(q, ua, xa);
-          if (local(q + 1, ub)) hit_at(q + 1, ub, xb2);
-        }
-        if (q < e) {
-          double xq[3];
+        // the scaled square distance to staged candidate q
+        auto staged = [&](int32_t q, double* xq) {
 #pragma unroll
           for (int k = 0; k < D; ++k) xq[k] = st[k][q - lo];
-          const double u2 = scaled_sq<D>(xp, xq, a.kt.inv0);
-          if (local(q, u2)) hit_at(q, u2, xq);
+          return scaled_sq<D>(xp, xq, a.kt.inv0);
+        };
+        for (int32_t q0 = s; q0 < e; q0 += kHits ? kMaskBits : e - s) {
+          const int32_t q1 = kHits ? min(e, q0 + kMaskBits) : e;
+          uint32_t hits = 0;
+          auto test = [&](int32_t q, double u2, const double* xq) {
+            if constexpr (kHits)
+              hits |= static_cast<uint32_t>(local(q, u2)) << (q - q0);
+            else if (local(q, u2))
+              hit_at(q, u2, xq);
+          };
+          // two candidates per step (independent chains); an odd last one alone
+          int32_t q = q0;
+          double xa[3], xb2[3];
+          for (; q + 1 < q1; q += 2) {
+            const double ua = staged(q, xa), ub = staged(q + 1, xb2);
+            test(q, ua, xa);
+            test(q + 1, ub, xb2);
+          }
+          if (q < q1) test(q, staged(q, xa), xa);
+          for (; hits; hits &= hits - 1) {
+            const int32_t h = q0 + __builtin_ctz(hits);
+            const double u2 = staged(h, xa);
+            hit_at(h, u2, xa);
+          }
         }
       } else {
         for (int32_t q0 = s; q0 < e; q0 += kCu) {
