@@ -89,6 +89,13 @@ void record_aux(gp_ctx* c) {
 
 void wait_aux(gp_ctx* c) { GPS_HIP(hipEventSynchronize(c->ev_aux)); }
 
+void record_block(gp_ctx* c, int i) {
+  if (!c->ev_block[i]) GPS_HIP(hipEventCreateWithFlags(&c->ev_block[i], hipEventDisableTiming));
+  GPS_HIP(hipEventRecord(c->ev_block[i], c->stream));
+}
+
+void wait_block(gp_ctx* c, int i) { GPS_HIP(hipEventSynchronize(c->ev_block[i])); }
+
 void fork_side(gp_ctx* c) {
   if (!c->side) {
     GPS_HIP(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
@@ -316,6 +323,8 @@ gp_status gp_ctx_destroy(gp_ctx* c) {
     c->pinned = nullptr;
     for (hipEvent_t e : c->evpool) (void)hipEventDestroy(e);
     if (c->ev_aux) (void)hipEventDestroy(c->ev_aux);
+    for (hipEvent_t e : c->ev_block)
+      if (e) (void)hipEventDestroy(e);
     c->evpool.clear();
     c->feed.reset();
     if (c->recorder) (void)hipStreamDestroy(c->recorder);

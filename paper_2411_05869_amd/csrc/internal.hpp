@@ -84,6 +84,7 @@ struct gp_ctx {
   int* err_flag = nullptr;  // device int, set by kernels on consistency failures
   bool h2d_pending = false;   // a host-to-device copy from the pinned buffer may not have run yet
   hipEvent_t ev_aux = nullptr;  // event for partial waits (created on first use)
+  hipEvent_t ev_block[2] = {nullptr, nullptr};  // of the last two blocks of iterations (created on first use)
   // optional per-kernel timing with events on the context's stream
   bool prof_on = false;
   struct ProfRec {
@@ -260,6 +261,9 @@ void h2d_async(gp_ctx* c, void* dst, const void* src, size_t bytes);
 void record_aux(gp_ctx* c);
 void wait_aux(gp_ctx* c);
 void sync(gp_ctx* c);
+// marks the end of a block of iterations (two in flight: i = 0, 1), and waits for it
+void record_block(gp_ctx* c, int i);
+void wait_block(gp_ctx* c, int i);
 // Side stream: fork_side() orders the side stream after everything enqueued
 // on the main stream so far; while a SideScope lives, the context's stream is
 // the side stream and device allocations are refused (memory the side stream
