@@ -540,11 +540,12 @@ gp_status gp_matvec(gp_ctx* c, const gp_matrix* m, int32_t nrhs, const double* x
     double* xb = static_cast<double*>(gps::workspace(c, 42, sizeof(double) * n * nrhs));
     double* yb = static_cast<double*>(gps::workspace(c, 43, sizeof(double) * n * nrhs));
     gps::permute_to_binned<double>(c, m->ds, nrhs, x, xb);
+    // yb takes the group parts; the rows' last pass writes y in the caller's order
+    const gps::RowDest<double> out{y, m->ds->perm};
     if (nrhs == 1)
-      gps::spmv_f64(c, m, xb, yb);
+      gps::spmv_f64(c, m, xb, yb, nullptr, out);
     else
-      gps::spmm<double>(c, m, nrhs, nrhs, xb, yb, nullptr);
-    gps::permute_to_orig<double>(c, m->ds, nrhs, yb, y);
+      gps::spmm<double>(c, m, nrhs, nrhs, xb, yb, nullptr, nullptr, false, out);
     gps::sync(c);
   });
 }

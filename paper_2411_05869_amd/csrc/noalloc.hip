@@ -52,8 +52,7 @@ void matvec_noalloc(gp_ctx* c, const gp_matrix* m, const double* x, double* y) {
   // every entry of xb and yb is written before it is read, so nothing from an
   // earlier call needs clearing
   permute_to_binned<double>(c, m->ds, 1, x, xb);
-  spmv_f64_enqueue(c, m, xb, yb);
-  permute_to_orig<double>(c, m->ds, 1, yb, y);
+  spmv_f64_enqueue(c, m, xb, yb, RowDest<double>{y, m->ds->perm});
 }
 
 }  // namespace gps

@@ -78,12 +78,12 @@ __device__ __forceinline__ AT spmv_part16(int64_t s, int64_t e, int sub, int32_t
 // (dispatched first, they set the tail); the remaining blocks take rows of at
 // most kLongRow entries with kG lanes per row.  Rows with group entries add
 // the group-block part that k_group_spmv wrote to y before.
-template <typename VT, typename XT, typename AT, typename YT>
+template <typename VT, typename XT, typename AT, typename YT, bool PERM>
 __global__ void __launch_bounds__(kThreads) k_spmv(int64_t n, unsigned nb_long, int64_t nlong,
                                                    const int32_t* __restrict__ rows, const int64_t* __restrict__ rp,
                                                    const int32_t* __restrict__ gskip,
                                                    const int32_t* __restrict__ col, const VT* __restrict__ val,
-                                                   const XT* __restrict__ x, YT* __restrict__ y,
+                                                   const XT* __restrict__ x, const YT* y, RowDest<YT> out,
                                                    const int16_t* __restrict__ off16, const int* __restrict__ skip) {
   if (skip && *skip) return;  // a device-side decision cancelled this product
   solve_wave_priority();
@@ -99,7 +99,7 @@ __global__ void __launch_bounds__(kThreads) k_spmv(int64_t n, unsigned nb_long, 
                        : spmv_part<VT, XT, AT, kG>(s, e, sub, static_cast<int32_t>(row), col, val, x);
 #pragma unroll
         for (int off = kG / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kG);
-        if (sub == 0) y[row] = static_cast<YT>(gs ? static_cast<AT>(y[row]) + acc : acc);
+        if (sub == 0) *out.template row<PERM>(row, 1) = static_cast<YT>(gs ? static_cast<AT>(y[row]) + acc : acc);
       }
     }
   } else {
@@ -113,7 +113,7 @@ __global__ void __launch_bounds__(kThreads) k_spmv(int64_t n, unsigned nb_long, 
       AT acc = spmv_part<VT, XT, AT, kWave>(s, e, lane, row, col, val, x);
 #pragma unroll
       for (int off = kWave / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kWave);
-      if (lane == 0) y[row] = static_cast<YT>(gs ? static_cast<AT>(y[row]) + acc : acc);
+      if (lane == 0) *out.template row<PERM>(row, 1) = static_cast<YT>(gs ? static_cast<AT>(y[row]) + acc : acc);
     }
   }
 }
@@ -210,13 +210,13 @@ __device__ __forceinline__ void slot_sum(Vec16<T>& a) {
 // scale[column], one coalesced access), wave w the chunks w, w + 4, ...; all X
 // gathers of a chunk are independent, so kUq of them are in flight per lane.  The
 // four partial rows are added in a fixed order, after the group part already in Y.
-template <typename VT, typename T, bool SCALE>
+template <typename VT, typename T, bool SCALE, bool PERM>
 __global__ void __launch_bounds__(kThreads) k_spmm_long(int64_t nlong, const int32_t* __restrict__ rows, int k, int ld,
                                                         const int64_t* __restrict__ rp,
                                                         const int32_t* __restrict__ gskip,
                                                         const int32_t* __restrict__ col, const VT* __restrict__ val,
-                                                        const T* __restrict__ X, T* __restrict__ Y,
-                                                        const T* __restrict__ scale,
+                                                        const T* __restrict__ X, const T* Y,
+                                                        RowDest<T> out, const T* __restrict__ scale,
                                                         const double* __restrict__ colscale) {
   using V = Vec16<T>;
   __shared__ T part[kThreads / kWave][32];
@@ -250,7 +250,7 @@ __global__ void __launch_bounds__(kThreads) k_spmm_long(int64_t nlong, const int
   if (gs) t = Y[static_cast<int64_t>(row) * ld + c] + t;
   if constexpr (SCALE) t *= scale[row];
   if (colscale) t *= colscale[c];
-  Y[static_cast<int64_t>(row) * ld + c] = t;
+  out.template row<PERM>(row, ld)[c] = t;
 }
 
 // CSR part of the product with fewer than 32 columns (any k <= W, any ld).  A row
@@ -349,7 +349,7 @@ __device__ __forceinline__ T spmm_part(int64_t s, int64_t e, int64_t stride, int
   return acc;
 }
 
-template <typename VT, typename T, bool SCALE, int W>
+template <typename VT, typename T, bool SCALE, bool PERM, int W>
 __global__ void __launch_bounds__(kThreads) k_spmm_rows(int64_t n, unsigned nb_long, int64_t nlong,
                                                         const int32_t* __restrict__ rows, int k, int ld,
                                                         const int64_t* __restrict__ rp,
@@ -357,7 +357,8 @@ __global__ void __launch_bounds__(kThreads) k_spmm_rows(int64_t n, unsigned nb_l
                                                         const int32_t* __restrict__ col,
                                                         const int16_t* __restrict__ off16,
                                                         const VT* __restrict__ val, const T* __restrict__ X,
-                                                        T* __restrict__ Y, const T* __restrict__ scale,
+                                                        const T* Y, RowDest<T> out,
+                                                        const T* __restrict__ scale,
                                                         const double* __restrict__ colscale) {
   constexpr int kL = row_lanes<W>();
   __shared__ int32_t sq[kThreads];
@@ -365,11 +366,10 @@ __global__ void __launch_bounds__(kThreads) k_spmm_rows(int64_t n, unsigned nb_l
   const int lane = lane_id(), c = lane % W;
   const T* Xc = X + min(c, k - 1);  // lanes past k re-read column k - 1 and store nothing
   auto finish = [&](int64_t row, int32_t gs, T t) {
-    T* y = Y + row * ld + c;
-    if (gs) t = *y + t;
+    if (gs) t = Y[row * ld + c] + t;
     if constexpr (SCALE) t *= scale[row];
     if (colscale) t *= colscale[c];
-    *y = t;
+    out.template row<PERM>(row, ld)[c] = t;
   };
   if (blockIdx.x >= nb_long) {
     const unsigned b = xcd_remap(blockIdx.x - nb_long, gridDim.x - nb_long);
@@ -500,7 +500,7 @@ __global__ void __launch_bounds__(kThreads) k_group_spmv(const int32_t* __restri
 // block adds its rows' CSR parts to their group parts; the long rows without a
 // group part take a wave each, the other rows kG lanes.  Every row is summed in
 // the order of the two kernels.  Blocks: tiles, then nb_long, then rows.
-template <typename VT>
+template <typename VT, bool PERM>
 __global__ void __launch_bounds__(kThreads) k_spmv_one(int64_t n, unsigned ntiles, unsigned nb_long, int64_t nlong,
                                                        const int32_t* __restrict__ tiles,
                                                        const int32_t* __restrict__ grows,
@@ -510,7 +510,7 @@ __global__ void __launch_bounds__(kThreads) k_spmv_one(int64_t n, unsigned ntile
                                                        const int64_t* __restrict__ rp,
                                                        const int32_t* __restrict__ gskip,
                                                        const int32_t* __restrict__ col, const VT* __restrict__ val,
-                                                       const double* __restrict__ x, double* __restrict__ y,
+                                                       const double* __restrict__ x, RowDest<double> out,
                                                        const int16_t* __restrict__ off16,
                                                        const int* __restrict__ skip) {
   if (skip && *skip) return;  // uniform over the launch
@@ -553,14 +553,14 @@ __global__ void __launch_bounds__(kThreads) k_spmv_one(int64_t n, unsigned ntile
 #pragma unroll
     for (int r = 0; r < kWaveRows; ++r)
       if (r == r8) mine = acc[r];
-    if (own && sub == 0) y[row] = mine + csr;
+    if (own && sub == 0) *out.template row<PERM>(row, 1) = mine + csr;
   } else if (blockIdx.x < ntiles + nb_long) {
     const int64_t i = static_cast<int64_t>(blockIdx.x - ntiles) * kWaves + w;
     if (i < nlong) {
       const int32_t row = long_rows[i];
       if (gskip[row] == 0) {
         const double a = long_row(rp[row], rp[row + 1], row);
-        if (lane == 0) y[row] = a;
+        if (lane == 0) *out.template row<PERM>(row, 1) = a;
       }
     }
   } else {
@@ -570,7 +570,7 @@ __global__ void __launch_bounds__(kThreads) k_spmv_one(int64_t n, unsigned ntile
       const int64_t s = rp[row], e = rp[row + 1];
       if (gskip[row] == 0 && e - s <= kLongRow) {  // uniform within the group
         const double a = short_row(s, e, static_cast<int32_t>(row));
-        if (sub == 0) y[row] = a;
+        if (sub == 0) *out.template row<PERM>(row, 1) = a;
       }
     }
   }
@@ -623,8 +623,8 @@ __global__ void __launch_bounds__(kThreads) k_col16(int64_t n, const int64_t* __
 // registers): 146.3 -> 150.7 and 202.1 -> 214.5.
 constexpr int64_t kOneLaunchEntries = int64_t(64) << 20;
 
-template <typename VT, typename XT, typename AT, typename YT>
-void spmv_launch(gp_ctx* c, const gp_matrix* m, const XT* x, YT* y, const int* skip = nullptr) {
+template <typename VT, typename XT, typename AT, typename YT, bool PERM>
+void spmv_launch_to(gp_ctx* c, const gp_matrix* m, const XT* x, YT* y, const int* skip, RowDest<YT> out) {
   const VT* val = static_cast<const VT*>(m->val);
   // long-row blocks padded to a multiple of the XCD count so that both block
   // ranges start on XCD 0 (see xcd_remap)
@@ -633,9 +633,9 @@ void spmv_launch(gp_ctx* c, const gp_matrix* m, const XT* x, YT* y, const int* s
     if (m->ntiles > 0 && m->nnz <= kOneLaunchEntries) {
       const unsigned nt = static_cast<unsigned>(m->ntiles);
       const unsigned nl = m->n_long > 0 ? grid_for(m->n_long, kWaves) : 0;
-      hipLaunchKernelGGL((k_spmv_one<VT>), dim3(nt + nl + nb_short), dim3(kThreads), 0, c->stream, m->n, nt, nl,
+      hipLaunchKernelGGL((k_spmv_one<VT, PERM>), dim3(nt + nl + nb_short), dim3(kThreads), 0, c->stream, m->n, nt, nl,
                          m->n_long, m->g_tiles, m->g_rows, m->g_uoff, m->g_ulist, m->long_rows, m->row_ptr, m->gskip,
-                         m->col, val, x, y, m->col16, skip);
+                         m->col, val, x, out, m->col16, skip);
       check_launch("spmv");
       return;
     }
@@ -644,15 +644,24 @@ void spmv_launch(gp_ctx* c, const gp_matrix* m, const XT* x, YT* y, const int* s
   if (m->ntiles > 0)
     hipLaunchKernelGGL((k_group_spmv<VT, XT, AT, YT>), dim3(static_cast<unsigned>(m->ntiles)), dim3(kThreads), 0,
                        c->stream, m->g_tiles, m->g_rows, m->g_uoff, m->g_ulist, m->row_ptr, val, x, y, skip);
-  hipLaunchKernelGGL((k_spmv<VT, XT, AT, YT>), dim3(nb_short + nb_long), dim3(kThreads), 0, c->stream, m->n,
-                     nb_long, m->n_long, m->long_rows, m->row_ptr, m->gskip, m->col, val, x, y, m->col16, skip);
+  hipLaunchKernelGGL((k_spmv<VT, XT, AT, YT, PERM>), dim3(nb_short + nb_long), dim3(kThreads), 0, c->stream, m->n,
+                     nb_long, m->n_long, m->long_rows, m->row_ptr, m->gskip, m->col, val, x, y, out, m->col16, skip);
   check_launch("spmv");
 }
 
 template <typename VT, typename XT, typename AT, typename YT>
-void spmv_impl(gp_ctx* c, const gp_matrix* m, const XT* x, YT* y, const int* skip) {
+void spmv_launch(gp_ctx* c, const gp_matrix* m, const XT* x, YT* y, const int* skip, RowDest<YT> out) {
+  if (!out.y) out.y = y;
+  if (out.perm)
+    spmv_launch_to<VT, XT, AT, YT, true>(c, m, x, y, skip, out);
+  else
+    spmv_launch_to<VT, XT, AT, YT, false>(c, m, x, y, skip, out);
+}
+
+template <typename VT, typename XT, typename AT, typename YT>
+void spmv_impl(gp_ctx* c, const gp_matrix* m, const XT* x, YT* y, const int* skip, RowDest<YT> out) {
   ProfScope ps(c, sizeof(VT) == 4 ? (sizeof(XT) == 4 ? "spmv_f32" : "spmv_f32val_f64") : "spmv_f64");
-  spmv_launch<VT, XT, AT, YT>(c, m, x, y, skip);
+  spmv_launch<VT, XT, AT, YT>(c, m, x, y, skip, out);
 }
 
 }  // namespace
@@ -691,19 +700,19 @@ static void build_col16(gp_ctx* c, gp_matrix* m) {
 // The same product with whatever caches the matrix already holds: nothing is
 // built, allocated, timed or waited for (the int16 offsets are read when an
 // earlier product built them; both column forms give bitwise equal sums).
-void spmv_f64_enqueue(gp_ctx* c, const gp_matrix* m, const double* x, double* y) {
+void spmv_f64_enqueue(gp_ctx* c, const gp_matrix* m, const double* x, double* y, RowDest<double> out) {
   if (m->prec == GP_MIXED)
-    spmv_launch<float, double, double, double>(c, m, x, y);
+    spmv_launch<float, double, double, double>(c, m, x, y, nullptr, out);
   else
-    spmv_launch<double, double, double, double>(c, m, x, y);
+    spmv_launch<double, double, double, double>(c, m, x, y, nullptr, out);
 }
 
-void spmv_f64(gp_ctx* c, const gp_matrix* m, const double* x, double* y, const int* skip) {
+void spmv_f64(gp_ctx* c, const gp_matrix* m, const double* x, double* y, const int* skip, RowDest<double> out) {
   build_col16(c, const_cast<gp_matrix*>(m));
   if (m->prec == GP_MIXED)
-    spmv_impl<float, double, double, double>(c, m, x, y, skip);
+    spmv_impl<float, double, double, double>(c, m, x, y, skip, out);
   else
-    spmv_impl<double, double, double, double>(c, m, x, y, skip);
+    spmv_impl<double, double, double, double>(c, m, x, y, skip, out);
 }
 
 
@@ -1174,12 +1183,13 @@ constexpr int kQuadUq = 2;  // X loads in flight per lane (two keep the kernel a
 // 6.94 likelihood evaluations per second; alone the product is 2% slower).
 constexpr unsigned kShareLds = 15 * 1024;
 
-template <typename VT, bool SCALE>
+template <typename VT, bool SCALE, bool PERM>
 __global__ void __launch_bounds__(kThreads) k_spmm_quad(int64_t ngroups, const int64_t* __restrict__ qptr,
                                                         const int32_t* __restrict__ qcol,
                                                         const VT* __restrict__ qval, const int32_t* __restrict__ code,
                                                         int k, int ld,
                                                         const double* __restrict__ X, double* __restrict__ Y,
+                                                        double* __restrict__ dest, const int32_t* __restrict__ perm,
                                                         const double* __restrict__ scale,
                                                         const double* __restrict__ colscale) {
   using V = Vec16<double>;
@@ -1265,12 +1275,15 @@ __global__ void __launch_bounds__(kThreads) k_spmm_quad(int64_t ngroups, const i
       const bool grow = cr < -1;
       const int64_t row = grow ? -static_cast<int64_t>(cr) - 2 : cr;
       if (lane < V::kLpe) {
-        double* yr = Y + row * ld + lane * V::kCpl;
+        // (Y and not a copy of the pointer where the rows stay: with two the kernel
+        // takes 74 registers and loses its seventh wave)
+        double* yg = Y + row * ld + lane * V::kCpl;
+        double* yr = PERM ? dest + static_cast<int64_t>(perm[row]) * ld + lane * V::kCpl : yg;
 #pragma unroll
         for (int t = 0; t < V::kCpl; ++t) {
           if (lane * V::kCpl + t >= k) break;
           double a = acc[r].v[t];
-          if (grow) a = yr[t] + a;
+          if (grow) a = yg[t] + a;
           if constexpr (SCALE) a *= scale[row];
           if (colscale) a *= csv[t];
           yr[t] = a;
@@ -1377,7 +1390,8 @@ void spmm_reserve(gp_ctx* c, const gp_matrix* m) {
 
 template <typename T>
 void spmm(gp_ctx* c, const gp_matrix* m, int k, int ld, const T* X, T* Y, const T* scale, const double* colscale,
-          bool share) {
+          bool share, RowDest<T> out) {
+  if (!out.y) out.y = Y;
   static_assert(std::is_same<T, double>::value, "the products take float64 vectors");
   if (k > 32 || ld < k) throw Error{GP_EINVAL, "spmm: at most 32 right-hand sides per call"};
   // 16-byte X loads need rows of at least 32 values at 16-byte alignment
@@ -1387,9 +1401,9 @@ void spmm(gp_ctx* c, const gp_matrix* m, int k, int ld, const T* X, T* Y, const 
   ProfScope ps(c, "spmm");
   // partial blocks of the pieces of multi-piece super-tiles
   T* part = m->npieces > 0 ? static_cast<T*>(workspace(c, 55, spmm_part_bytes(m))) : nullptr;
-  auto go = [&](auto vt, auto sc) {
+  auto go = [&](auto vt, auto sc, auto pm) {
     using VT = decltype(vt);
-    constexpr bool SC = decltype(sc)::value;
+    constexpr bool SC = decltype(sc)::value, PM = decltype(pm)::value;
     if (m->npieces > 0) {
       const int32_t* st = m->g_tiles + 4 * m->ntiles;
       auto group = [&](auto nb) {
@@ -1412,21 +1426,21 @@ void spmm(gp_ctx* c, const gp_matrix* m, int k, int ld, const T* X, T* Y, const 
       if (ng > 0) {
         const unsigned nbq =
             static_cast<unsigned>(round_up8(grid_for((ng + kQuadsPerWave - 1) / kQuadsPerWave, kThreads / kWave)));
-        hipLaunchKernelGGL((k_spmm_quad<VT, SC>), dim3(nbq), dim3(kThreads), share ? kShareLds : 0, c->stream, ng,
+        hipLaunchKernelGGL((k_spmm_quad<VT, SC, PM>), dim3(nbq), dim3(kThreads), share ? kShareLds : 0, c->stream, ng,
                            mm->qptr, mm->qcol,
-                           static_cast<const VT*>(mm->qval), mm->trow, k, ld, X, Y, scale, colscale);
+                           static_cast<const VT*>(mm->qval), mm->trow, k, ld, X, Y, out.y, out.perm, scale, colscale);
       }
       if (m->n_long > 0)
-        hipLaunchKernelGGL((k_spmm_long<VT, T, SC>), dim3(static_cast<unsigned>(m->n_long)), dim3(kThreads), 0,
+        hipLaunchKernelGGL((k_spmm_long<VT, T, SC, PM>), dim3(static_cast<unsigned>(m->n_long)), dim3(kThreads), 0,
                            c->stream, m->n_long, m->long_rows, k, ld, m->row_ptr, m->gskip, m->col,
-                           static_cast<const VT*>(m->val), X, Y, scale, colscale);
+                           static_cast<const VT*>(m->val), X, Y, out, scale, colscale);
     } else {
       const unsigned nb_long = m->n_long > 0 ? round_up8(static_cast<unsigned>(m->n_long)) : 0;
       auto rows = [&](auto w) {
         constexpr int W = decltype(w)::value;
-        hipLaunchKernelGGL((k_spmm_rows<VT, T, SC, W>), dim3(nb_long + grid_for(m->n * row_lanes<W>(), kThreads)),
+        hipLaunchKernelGGL((k_spmm_rows<VT, T, SC, PM, W>), dim3(nb_long + grid_for(m->n * row_lanes<W>(), kThreads)),
                            dim3(kThreads), 0, c->stream, m->n, nb_long, m->n_long, m->long_rows, k, ld, m->row_ptr,
-                           m->gskip, m->col, m->col16, static_cast<const VT*>(m->val), X, Y, scale, colscale);
+                           m->gskip, m->col, m->col16, static_cast<const VT*>(m->val), X, Y, out, scale, colscale);
       };
       if (k <= 2)
         rows(std::integral_constant<int, 2>{});
@@ -1440,22 +1454,28 @@ void spmm(gp_ctx* c, const gp_matrix* m, int k, int ld, const T* X, T* Y, const 
         rows(std::integral_constant<int, 32>{});
     }
   };
+  auto with_dest = [&](auto vt, auto sc) {
+    if (out.perm)
+      go(vt, sc, std::true_type{});
+    else
+      go(vt, sc, std::false_type{});
+  };
   if (m->prec == GP_MIXED) {
     if (scale)
-      go(float{}, std::true_type{});
+      with_dest(float{}, std::true_type{});
     else
-      go(float{}, std::false_type{});
+      with_dest(float{}, std::false_type{});
   } else {
     if (scale)
-      go(double{}, std::true_type{});
+      with_dest(double{}, std::true_type{});
     else
-      go(double{}, std::false_type{});
+      with_dest(double{}, std::false_type{});
   }
   check_launch("spmm");
 }
 
 template void spmm<double>(gp_ctx*, const gp_matrix*, int, int, const double*, double*, const double*,
-                           const double*, bool);
+                           const double*, bool, RowDest<double>);
 
 void build_product_caches(gp_ctx* c, gp_matrix* m) {
   build_col16(c, m);
