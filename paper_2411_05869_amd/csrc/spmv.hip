@@ -500,8 +500,10 @@ __global__ void __launch_bounds__(kThreads) k_group_spmv(const int32_t* __restri
 // block adds its rows' CSR parts to their group parts; the long rows without a
 // group part take a wave each, the other rows kG lanes.  Every row is summed in
 // the order of the two kernels.  Blocks: tiles, then nb_long, then rows.
-template <typename VT, bool PERM>
-__global__ void __launch_bounds__(kThreads) k_spmv_one(int64_t n, unsigned ntiles, unsigned nb_long, int64_t nlong,
+//
+// WAVES: waves per SIMD its registers are held to (one_waves).
+template <typename VT, bool PERM, int WAVES>
+__global__ void __launch_bounds__(kThreads, WAVES) k_spmv_one(int64_t n, unsigned ntiles, unsigned nb_long, int64_t nlong,
                                                        const int32_t* __restrict__ tiles,
                                                        const int32_t* __restrict__ grows,
                                                        const int64_t* __restrict__ uoff,
@@ -619,9 +621,23 @@ __global__ void __launch_bounds__(kThreads) k_col16(int64_t n, const int64_t* __
 // Entries up to which the product takes one launch.  Two launches -> one, per
 // product: 0.3M entries (FP64) 10.5 -> 8.0 us, 2.0M (mixture n = 30,011, mixed)
 // 13.7 -> 9.6, 5.0M 21.4 -> 16.2, 42M 52.5 -> 49.0 and 87.5 -> 79.2 (FP64).  At 87M
-// entries the CSR rows' occupancy counts for more (the tile code holds 80
-// registers): 146.3 -> 150.7 and 202.1 -> 214.5.
+// entries the CSR rows want the waves that the tile code's registers cost them:
+// FP64 239 -> 243 us (gp_matvec); mixed (6 waves, see one_waves) 183 -> 180, but a
+// likelihood with the log det's products beside it 114.6 -> 116.6 ms.
 constexpr int64_t kOneLaunchEntries = int64_t(64) << 20;
+
+// Waves per SIMD the one-launch product is compiled for.  The tile code is at its
+// best with the registers it asks for (float32 values 96: 5 waves; FP64 113: 4), the
+// CSR rows with more waves, which hide their gathers.  Held to 6 waves (80
+// registers, float32), per CG iteration: 0.3M to 3.7M entries 17.66 -> 17.89 and 20.1 ->
+// 20.8 us, 5M 26.1 -> 25.2, 14M (eight problems) 36.4 -> 35.4, 42M 55.8 -> 52.1, 46M 59.7 -> 58.9.  To
+// 5 waves (96, FP64), by the share of group entries: 0.18 29.3 -> 28.2, 0.35 23.5 -> 22.9,
+// 0.84 103.1 -> 100.5, 0.93 89.9 -> 90.3 and 78.6 -> 80.2.  (6 waves spill there.)
+template <typename VT>
+int one_waves(const gp_matrix* m) {
+  if (sizeof(VT) == 4) return m->nnz > (int64_t(4) << 20) ? 6 : 1;
+  return 8 * m->nnz_group < 7 * m->nnz ? 5 : 1;
+}
 
 template <typename VT, typename XT, typename AT, typename YT, bool PERM>
 void spmv_launch_to(gp_ctx* c, const gp_matrix* m, const XT* x, YT* y, const int* skip, RowDest<YT> out) {
@@ -633,9 +649,15 @@ void spmv_launch_to(gp_ctx* c, const gp_matrix* m, const XT* x, YT* y, const int
     if (m->ntiles > 0 && m->nnz <= kOneLaunchEntries) {
       const unsigned nt = static_cast<unsigned>(m->ntiles);
       const unsigned nl = m->n_long > 0 ? grid_for(m->n_long, kWaves) : 0;
-      hipLaunchKernelGGL((k_spmv_one<VT, PERM>), dim3(nt + nl + nb_short), dim3(kThreads), 0, c->stream, m->n, nt, nl,
-                         m->n_long, m->g_tiles, m->g_rows, m->g_uoff, m->g_ulist, m->long_rows, m->row_ptr, m->gskip,
-                         m->col, val, x, out, m->col16, skip);
+      auto one = [&](auto waves) {
+        hipLaunchKernelGGL((k_spmv_one<VT, PERM, decltype(waves)::value>), dim3(nt + nl + nb_short), dim3(kThreads), 0,
+                           c->stream, m->n, nt, nl, m->n_long, m->g_tiles, m->g_rows, m->g_uoff, m->g_ulist,
+                           m->long_rows, m->row_ptr, m->gskip, m->col, val, x, out, m->col16, skip);
+      };
+      if (one_waves<VT>(m) > 1)
+        one(std::integral_constant<int, sizeof(VT) == 4 ? 6 : 5>{});
+      else
+        one(std::integral_constant<int, 1>{});
       check_launch("spmv");
       return;
     }
