@@ -3,10 +3,9 @@
 //   v(x*) = C_y(x*, x*) - c^T K^{-1} c,   c = C_{z,y}(., x*),
 // for up to 32 test points at a time:
 //   1. the cross-covariance columns c_s are written into an n x C block X (C = 32,
-//      fewer for the last few of a request; rows in binned order): a thread per
-//      test point adds the local (Wendland) entries of its cell window, then a
-//      wave per test point adds the bump-group entries over the masked training
-//      points;
+//      fewer for the last few of a request; rows in binned order): the local
+//      (Wendland) entries of each point's cell window, then the bump-group
+//      entries over the masked training points are added;
 //   2. K W = X is solved by as many conjugate-gradient recurrences in lockstep
 //      (one SpMM per step; block-Jacobi or Jacobi preconditioner; per-column
 //      scalars; a column stops changing once |r_s| <= rtol |c_s|), with a float64 true residual
@@ -78,11 +77,15 @@ __global__ void __launch_bounds__(kThreads) k_zero(int64_t len, double* __restri
 }
 
 // local part of c_s: C_core(x*, x_q) s0 f0(u) for the training points of the
-// cell window with u0^2 < 1 (each q once)
+// cell window with u0^2 < 1 (each q once).  A block per test point, kXl lanes per
+// pencil (cell row along x) of its window: walked by one thread the window is a
+// chain of as many dependent loads (32 points, n = 109,500: 109 us, now 5.4).
+constexpr int kXl = 16;
+
 template <int D, int CK>
 __global__ void __launch_bounds__(kThreads) k_cross_local(CrossArgs a, CoreBasis cb, int nb, int ld,
                                                           const double* __restrict__ xs, double* __restrict__ X) {
-  const int s = blockIdx.x * kThreads + threadIdx.x;
+  const int s = blockIdx.x;
   if (s >= nb) return;
   double xp[3];
   int c[3] = {0, 0, 0};
@@ -98,36 +101,44 @@ __global__ void __launch_bounds__(kThreads) k_cross_local(CrossArgs a, CoreBasis
   }
   double sp = 0.0, Sp = 0.0;
   if constexpr (CK == 2) core_point_fields<D>(cb, xp, &sp, &Sp);
-  for (int z = lo[2]; z <= hi[2]; ++z)
-    for (int y = lo[1]; y <= hi[1]; ++y) {
-      const int64_t base = (static_cast<int64_t>(z) * a.g[1] + y) * a.g[0];
-      const int32_t b = a.cell_start[base + lo[0]];
-      const int32_t e = a.cell_start[base + hi[0] + 1];
-      for (int32_t q = b; q < e; ++q) {
-        double xq[3];
-        load_train<D>(a, q, xq);
-        const double u2 = scaled_sq<D>(xp, xq, a.kt.inv0);
-        if (u2 < 1.0) {
-          double v = a.kt.s0 * wendland(u2, a.kt.variant);
-          if constexpr (CK == 1) v = core_value<D, 1>(a.kt.core, xp, xq, 0.0, 0.0, 0.0, 0.0) * v;
-          if constexpr (CK == 2)
-            v = core_value<D, 2>(a.kt.core, xp, xq, sp, Sp, a.kt.core.sig[q], a.kt.core.Sig[q]) * v;
-          X[static_cast<int64_t>(q) * ld + s] = v;
-        }
+  const int ny = hi[1] - lo[1] + 1;
+  const int64_t npen = static_cast<int64_t>(ny) * (hi[2] - lo[2] + 1);
+  for (int64_t k = threadIdx.x / kXl; k < npen; k += kThreads / kXl) {
+    const int y = lo[1] + static_cast<int>(k % ny), z = lo[2] + static_cast<int>(k / ny);
+    const int64_t base = (static_cast<int64_t>(z) * a.g[1] + y) * a.g[0];
+    const int32_t e = a.cell_start[base + hi[0] + 1];
+    for (int32_t q = a.cell_start[base + lo[0]] + threadIdx.x % kXl; q < e; q += kXl) {
+      double xq[3];
+      load_train<D>(a, q, xq);
+      const double u2 = scaled_sq<D>(xp, xq, a.kt.inv0);
+      if (u2 < 1.0) {
+        double v = a.kt.s0 * wendland(u2, a.kt.variant);
+        if constexpr (CK == 1) v = core_value<D, 1>(a.kt.core, xp, xq, 0.0, 0.0, 0.0, 0.0) * v;
+        if constexpr (CK == 2)
+          v = core_value<D, 2>(a.kt.core, xp, xq, sp, Sp, a.kt.core.sig[q], a.kt.core.Sig[q]) * v;
+        X[static_cast<int64_t>(q) * ld + s] = v;
       }
     }
+  }
 }
 
-// bump-group part of c_s and the prior variance C_y(x*, x*): one wave per
-// test point; lane i < n1 forms f_i(x*) (bumps of group i in j order)
+// bump-group part of c_s and the prior variance C_y(x*, x*): gridDim.y blocks of
+// waves per test point, each forming the f_i(x*) for itself (lane i < n1, bumps of
+// group i in j order) and taking its share of the masked training points.  (One
+// wave per test point went through all of them: 32 points, n = 109,500, nearly all
+// masked, 202 us, now 8.3.)
+constexpr int kGroupShare = 256;  // masked points per wave, about
+constexpr int kGroupBlocks = 64;  // blocks per test point at most
+
 template <int D, int CK>
 __global__ void __launch_bounds__(kThreads) k_cross_groups(CrossArgs a, CoreBasis cb, int nb, int ld,
                                                            const double* __restrict__ xs, double* __restrict__ X,
                                                            double* __restrict__ prior) {
   __shared__ double fs[kThreads / kWave][kWave];
-  const int s = (blockIdx.x * kThreads + threadIdx.x) / kWave;
-  if (s >= nb) return;  // uniform per wave
+  const int s = blockIdx.x;
+  if (s >= nb) return;
   const int lane = lane_id();
+  const int64_t wave = blockIdx.y * (kThreads / kWave) + threadIdx.x / kWave;
   double* f = fs[threadIdx.x / kWave];
   double xp[3];
   for (int k = 0; k < D; ++k) xp[k] = xs[static_cast<int64_t>(s) * D + k];
@@ -151,7 +162,7 @@ __global__ void __launch_bounds__(kThreads) k_cross_groups(CrossArgs a, CoreBasi
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   double sp = 0.0, Sp = 0.0;
   if constexpr (CK == 2) core_point_fields<D>(cb, xp, &sp, &Sp);
-  if (lane == 0) {
+  if (wave == 0 && lane == 0) {
 #pragma clang fp contract(off)
     double v = a.kt.s0 * wendland(0.0, a.kt.variant);
     uint64_t mm = mask;
@@ -165,7 +176,7 @@ __global__ void __launch_bounds__(kThreads) k_cross_groups(CrossArgs a, CoreBasi
     prior[s] = v;
   }
   if (mask == 0) return;  // uniform
-  for (int64_t j = lane; j < a.nm; j += kWave) {
+  for (int64_t j = wave * kWave + lane; j < a.nm; j += static_cast<int64_t>(gridDim.y) * kThreads) {
     uint64_t sh = a.mmask[j] & mask;
     if (!sh) continue;
     double bsum = 0.0;
@@ -183,7 +194,7 @@ __global__ void __launch_bounds__(kThreads) k_cross_groups(CrossArgs a, CoreBasi
       else
         bsum = core_value<D, 2>(a.kt.core, xp, xq, sp, Sp, a.kt.core.sig[q], a.kt.core.Sig[q]) * bsum;
     }
-    // one wave owns column s, so these read-modify-writes do not race
+    // row q is listed once, so these read-modify-writes do not race
     X[static_cast<int64_t>(q) * ld + s] += bsum;
   }
 }
@@ -799,9 +810,9 @@ VarResult predict_variance(gp_ctx* c, const gp_matrix* m, const gp_theta* th, in
       dispatch_dk(d, kt.core.kind, [&](auto DD, auto CC) {
         constexpr int D = decltype(DD)::value;
         constexpr int CK = decltype(CC)::value;
-        hipLaunchKernelGGL((k_cross_local<D, CK>), dim3(1), B, 0, c->stream, a, cb, nb, C, xb, X);
-        hipLaunchKernelGGL((k_cross_groups<D, CK>), dim3((nb * kWave + kThreads - 1) / kThreads), B, 0, c->stream,
-                           a, cb, nb, C, xb, X, prior);
+        hipLaunchKernelGGL((k_cross_local<D, CK>), dim3(nb), B, 0, c->stream, a, cb, nb, C, xb, X);
+        const unsigned share = std::min<unsigned>(kGroupBlocks, grid_for(a.nm, kGroupShare * (kThreads / kWave)));
+        hipLaunchKernelGGL((k_cross_groups<D, CK>), dim3(nb, share), B, 0, c->stream, a, cb, nb, C, xb, X, prior);
       });
       check_launch("variance cross-covariance");
     }
