@@ -97,10 +97,10 @@ CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2411_0586
 TRAFFIC_GROUPS = {
     # the conjugate-gradient product: float32 values, float64 vectors
     "spmv_f32val_f64": ("spmv.hip", ("k_group_spmv<float, double, double, double>(",
-                                     "k_spmv<float, double, double, double>(")),
+                                     "k_spmv<float, double, double, double, false>(")),
     # the 32-column SLQ product: MFMA group blocks, their piece sums, the row quads
-    "spmm": ("spmv.hip", ("k_group_spmm_mfma<float, double, true>(", "k_group_reduce<double>(",
-                          "k_spmm_quad<float, true>(")),
+    "spmm": ("spmv.hip", ("k_group_spmm_mfma<float, double, true, 2>(", "k_group_reduce<double>(",
+                          "k_spmm_quad<float, true, false>(")),
     # the assembly's main kernels (float32 values)
     "assembly": ("assemble.hip", ("k_mask<3>(", "k_fvals<3>(", "k_local_rows<3, false, double, 0>(",
                                   "k_ulists(", "k_ugather<3>(", "k_local_rows<3, true, float, 0>(",

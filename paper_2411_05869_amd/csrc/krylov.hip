@@ -990,22 +990,18 @@ static double logsum_f64(gp_ctx* c, const double* a, int64_t n) {
 constexpr int64_t kGraphEntries = int64_t(8) << 20;
 
 // A sequence of launches recorded once and launched with one call: 29 us to
-// record 33 kernels, 79 to instantiate and 42 to destroy, all of it while the
-// GPU works.  Kept for one solve; without the means to record (a stream, memory)
-// there is none and the caller launches plainly.
+// record 33 kernels and 79 to instantiate (a solve does both while its second
+// block runs), 42 to destroy.  Kept for one solve; without the means to record (a
+// stream, memory) there is none and the caller launches plainly.
 class LaunchGraph {
  public:
   explicit LaunchGraph(gp_ctx* c) : c_(c) {}
   LaunchGraph(const LaunchGraph&) = delete;
   LaunchGraph& operator=(const LaunchGraph&) = delete;
   ~LaunchGraph() {
-    if (exec_) (void)hipStreamSynchronize(c_->stream);
-    drop();
-  }
-  // (none of its launches is running any more)
-  void drop() {
-    if (exec_) (void)hipGraphExecDestroy(exec_);
-    exec_ = nullptr;
+    if (!exec_) return;
+    (void)hipStreamSynchronize(c_->stream);  // (a launch may still be running after an error)
+    (void)hipGraphExecDestroy(exec_);
   }
   explicit operator bool() const { return exec_ != nullptr; }
 
