@@ -179,6 +179,10 @@ constexpr int kCandList = 256;  // candidates listed at a time
 constexpr int kCandUnroll = 4;  // candidates whose loads a lane has in flight
 constexpr int kHitUnroll = 2;
 
+// Rows a launch takes: a grid of 2^32 threads or more loses its upper bits without
+// an error, and the group kernels take a wave per row (2^31 threads here).
+constexpr int64_t kLaunchRows = int64_t(1) << 25;
+
 // orders the LDS accesses of a point's lanes (one wave; no block barrier)
 __device__ __forceinline__ void lanes_sync_lds() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -309,12 +313,13 @@ __device__ __forceinline__ double predict_point(const PredArgs& a, const CoreBas
   return acc;
 }
 
+// rows t0 .. m - 1
 template <int D, bool MIXED, int CK>
-__global__ void __launch_bounds__(kThreads) k_predict(PredArgs a, CoreBasis cb, int64_t m,
+__global__ void __launch_bounds__(kThreads) k_predict(PredArgs a, CoreBasis cb, int64_t t0, int64_t m,
                                                       const double* __restrict__ xs, double* __restrict__ out) {
   __shared__ int32_t ids[kPointsPerBlock][kCandList];
   const int g = threadIdx.x / kPl, lane = threadIdx.x % kPl;
-  const int64_t t = blockIdx.x * static_cast<int64_t>(kPointsPerBlock) + g;
+  const int64_t t = t0 + blockIdx.x * static_cast<int64_t>(kPointsPerBlock) + g;
   if (t >= m) return;
   double xp[3];
   for (int k = 0; k < D; ++k) xp[k] = xs[t * D + k];
@@ -336,17 +341,18 @@ __device__ __forceinline__ int batch_request(const int64_t* __restrict__ roff, i
   return lo;
 }
 
-// Batched form: the rows of all requests in one launch, each row with the
+// Batched form: the rows of all requests (t0 .. m - 1 of them), each with the
 // arguments of its request's predictor.
 template <int D, bool MIXED, int CK>
 __global__ void __launch_bounds__(kThreads) k_predict_batch(const PredArgs* __restrict__ args,
                                                             const CoreBasis* __restrict__ cbs,
                                                             const int32_t* __restrict__ req_pred,
-                                                            const int64_t* __restrict__ roff, int nreq, int64_t m,
-                                                            const double* __restrict__ xs, double* __restrict__ out) {
+                                                            const int64_t* __restrict__ roff, int nreq, int64_t t0,
+                                                            int64_t m, const double* __restrict__ xs,
+                                                            double* __restrict__ out) {
   __shared__ int32_t ids[kPointsPerBlock][kCandList];
   const int g = threadIdx.x / kPl, lane = threadIdx.x % kPl;
-  const int64_t t = blockIdx.x * static_cast<int64_t>(kPointsPerBlock) + g;
+  const int64_t t = t0 + blockIdx.x * static_cast<int64_t>(kPointsPerBlock) + g;
   if (t >= m) return;
   const int pi = req_pred[batch_request(roff, nreq, t)];
   double xp[3];
@@ -429,10 +435,10 @@ __device__ __forceinline__ void predict_groups_point(const PredArgs& a, const Co
 }
 
 template <int D, int CK>
-__global__ void __launch_bounds__(kThreads) k_predict_groups(PredArgs a, CoreBasis cb, int64_t m,
+__global__ void __launch_bounds__(kThreads) k_predict_groups(PredArgs a, CoreBasis cb, int64_t t0, int64_t m,
                                                              const double* __restrict__ xs, double* __restrict__ out) {
   __shared__ double fs[kThreads / kWave][kWave];
-  const int64_t t = (blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x) / kWave;
+  const int64_t t = t0 + (blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x) / kWave;
   if (t >= m) return;  // uniform per wave
   predict_groups_point<D, CK>(a, cb, t, xs, out, fs[threadIdx.x / kWave]);
 }
@@ -442,10 +448,11 @@ __global__ void __launch_bounds__(kThreads) k_predict_groups_batch(const PredArg
                                                                    const CoreBasis* __restrict__ cbs,
                                                                    const int32_t* __restrict__ req_pred,
                                                                    const int64_t* __restrict__ roff, int nreq,
-                                                                   int64_t m, const double* __restrict__ xs,
+                                                                   int64_t t0, int64_t m,
+                                                                   const double* __restrict__ xs,
                                                                    double* __restrict__ out) {
   __shared__ double fs[kThreads / kWave][kWave];
-  const int64_t t = (blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x) / kWave;
+  const int64_t t = t0 + (blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x) / kWave;
   if (t >= m) return;  // uniform per wave
   const int pi = req_pred[batch_request(roff, nreq, t)];
   if (args[pi].nm == 0) return;  // no masked training points: no group part (uniform per wave)
@@ -614,20 +621,24 @@ void predict(gp_ctx* c, const gp_predictor* p, int64_t m, const double* xs, int 
   if (m == 0) return;
   const gp_dataset* ds = p->ds;
   const PredArgs a = pred_args(p);
-  const dim3 G(grid_for(m, kPointsPerBlock)), B(kThreads);
+  const dim3 B(kThreads);
   ProfScope ps(c, prec == GP_MIXED ? "predict_f32" : "predict_f64");
   auto go = [&](auto DD) {
     constexpr int D = decltype(DD)::value;
     auto with_core = [&](auto CC) {
       constexpr int CK = decltype(CC)::value;
-      if (prec == GP_MIXED)
-        hipLaunchKernelGGL((k_predict<D, true, CK>), G, B, 0, c->stream, a, p->cb, m, xs, out);
-      else
-        hipLaunchKernelGGL((k_predict<D, false, CK>), G, B, 0, c->stream, a, p->cb, m, xs, out);
-      if constexpr (CK != 0) {
-        if (p->nm > 0)
-          hipLaunchKernelGGL((k_predict_groups<D, CK>), dim3(grid_for(m * kWave, kThreads)), B, 0, c->stream, a,
-                             p->cb, m, xs, out);
+      for (int64_t t0 = 0; t0 < m; t0 += kLaunchRows) {
+        const int64_t t1 = std::min(m, t0 + kLaunchRows);
+        const dim3 G(grid_for(t1 - t0, kPointsPerBlock));
+        if (prec == GP_MIXED)
+          hipLaunchKernelGGL((k_predict<D, true, CK>), G, B, 0, c->stream, a, p->cb, t0, t1, xs, out);
+        else
+          hipLaunchKernelGGL((k_predict<D, false, CK>), G, B, 0, c->stream, a, p->cb, t0, t1, xs, out);
+        if constexpr (CK != 0) {
+          if (p->nm > 0)
+            hipLaunchKernelGGL((k_predict_groups<D, CK>), dim3(grid_for((t1 - t0) * kWave, kThreads)), B, 0,
+                               c->stream, a, p->cb, t0, t1, xs, out);
+        }
       }
     };
     if (p->kt.core.kind == GP_CORE_MATERN)
@@ -689,21 +700,26 @@ void predict_batch(gp_ctx* c, int32_t nreq, const gp_predictor* const* preds, co
   const CoreBasis* dc = reinterpret_cast<const CoreBasis*>(dbuf + up(b_args));
   const int32_t* dreq = reinterpret_cast<const int32_t*>(dbuf + up(b_args) + up(b_cb));
   const int64_t* droff = reinterpret_cast<const int64_t*>(dbuf + up(b_args) + up(b_cb) + up(b_req));
-  const dim3 G(grid_for(m, kPointsPerBlock)), B(kThreads);
+  const dim3 B(kThreads);
   ProfScope ps(c, prec == GP_MIXED ? "predict_batch_f32" : "predict_batch_f64");
   auto go = [&](auto DD) {
     constexpr int D = decltype(DD)::value;
     auto with_core = [&](auto CC) {
       constexpr int CK = decltype(CC)::value;
-      if (prec == GP_MIXED)
-        hipLaunchKernelGGL((k_predict_batch<D, true, CK>), G, B, 0, c->stream, da, dc, dreq, droff, nreq, m, xs, out);
-      else
-        hipLaunchKernelGGL((k_predict_batch<D, false, CK>), G, B, 0, c->stream, da, dc, dreq, droff, nreq, m, xs,
-                           out);
-      if constexpr (CK != 0) {
-        if (any_nm)
-          hipLaunchKernelGGL((k_predict_groups_batch<D, CK>), dim3(grid_for(m * kWave, kThreads)), B, 0, c->stream,
-                             da, dc, dreq, droff, nreq, m, xs, out);
+      for (int64_t t0 = 0; t0 < m; t0 += kLaunchRows) {
+        const int64_t t1 = std::min(m, t0 + kLaunchRows);
+        const dim3 G(grid_for(t1 - t0, kPointsPerBlock));
+        if (prec == GP_MIXED)
+          hipLaunchKernelGGL((k_predict_batch<D, true, CK>), G, B, 0, c->stream, da, dc, dreq, droff, nreq, t0, t1, xs,
+                             out);
+        else
+          hipLaunchKernelGGL((k_predict_batch<D, false, CK>), G, B, 0, c->stream, da, dc, dreq, droff, nreq, t0, t1,
+                             xs, out);
+        if constexpr (CK != 0) {
+          if (any_nm)
+            hipLaunchKernelGGL((k_predict_groups_batch<D, CK>), dim3(grid_for((t1 - t0) * kWave, kThreads)), B, 0,
+                               c->stream, da, dc, dreq, droff, nreq, t0, t1, xs, out);
+        }
       }
     };
     if (ck == GP_CORE_MATERN)
