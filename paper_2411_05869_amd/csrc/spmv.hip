@@ -260,7 +260,8 @@ __global__ void __launch_bounds__(kThreads) k_spmm_long(int64_t nlong, const int
 // so an entry costs one read of its id and value and one of its k columns.  Two
 // columns leave too few steps to a chunk for that to pay: there a slot takes four
 // consecutive entries itself, as in the one-column product.
-// Blocks [0, nb_long) take the listed long rows, a block each.
+// Blocks [0, nb_long) take the listed long rows, a block each; the others rows
+// row0 .. n - 1.
 // Bound by the gathers of X through the caches.  A wave per row and 32 columns
 // whatever k was, as before, took as long for 2 columns as for 31; the whole
 // product by columns, before -> now: n = 100,003 (mixture, FP64) 2: 187 -> 65 us, 8: 183 -> 88,
@@ -270,6 +271,9 @@ __global__ void __launch_bounds__(kThreads) k_spmm_long(int64_t nlong, const int
 template <int W>
 constexpr int row_lanes() { return W <= 8 ? 16 : 2 * W; }  // lanes of a row
 constexpr int kRowUq = 4;  // X rows a lane has in flight
+// Blocks of a launch at most (whole eighths, see xcd_remap): a grid of 2^32 threads
+// or more loses its upper bits without an error.
+constexpr int64_t kLaunchBlocks = (int64_t(1) << 32) / kThreads - 8;
 template <int W, int L>
 constexpr int row_chunk() { return W < kRowUq ? L / W * kRowUq : L; }  // entries the lanes take at a time
 
@@ -350,7 +354,7 @@ __device__ __forceinline__ T spmm_part(int64_t s, int64_t e, int64_t stride, int
 }
 
 template <typename VT, typename T, bool SCALE, bool PERM, int W>
-__global__ void __launch_bounds__(kThreads) k_spmm_rows(int64_t n, unsigned nb_long, int64_t nlong,
+__global__ void __launch_bounds__(kThreads) k_spmm_rows(int64_t row0, int64_t n, unsigned nb_long, int64_t nlong,
                                                         const int32_t* __restrict__ rows, int k, int ld,
                                                         const int64_t* __restrict__ rp,
                                                         const int32_t* __restrict__ gskip,
@@ -373,7 +377,7 @@ __global__ void __launch_bounds__(kThreads) k_spmm_rows(int64_t n, unsigned nb_l
   };
   if (blockIdx.x >= nb_long) {
     const unsigned b = xcd_remap(blockIdx.x - nb_long, gridDim.x - nb_long);
-    const int64_t row = (b * static_cast<int64_t>(kThreads) + threadIdx.x) / kL;
+    const int64_t row = row0 + (b * static_cast<int64_t>(kThreads) + threadIdx.x) / kL;
     if (row >= n) return;
     const int32_t gs = gskip[row];
     const int64_t s = rp[row] + gs, e = rp[row + 1];
@@ -1457,12 +1461,16 @@ void spmm(gp_ctx* c, const gp_matrix* m, int k, int ld, const T* X, T* Y, const 
                            c->stream, m->n_long, m->long_rows, k, ld, m->row_ptr, m->gskip, m->col,
                            static_cast<const VT*>(m->val), X, Y, out, scale, colscale);
     } else {
-      const unsigned nb_long = m->n_long > 0 ? round_up8(static_cast<unsigned>(m->n_long)) : 0;
+      unsigned nb_long = m->n_long > 0 ? round_up8(static_cast<unsigned>(m->n_long)) : 0;
       auto rows = [&](auto w) {
-        constexpr int W = decltype(w)::value;
-        hipLaunchKernelGGL((k_spmm_rows<VT, T, SC, PM, W>), dim3(nb_long + grid_for(m->n * row_lanes<W>(), kThreads)),
-                           dim3(kThreads), 0, c->stream, m->n, nb_long, m->n_long, m->long_rows, k, ld, m->row_ptr,
-                           m->gskip, m->col, m->col16, static_cast<const VT*>(m->val), X, Y, out, scale, colscale);
+        constexpr int W = decltype(w)::value, kRows = kThreads / row_lanes<W>();  // rows of a block
+        for (int64_t row0 = 0, row1; row0 < m->n; row0 = row1, nb_long = 0) {
+          row1 = std::min<int64_t>(m->n, row0 + std::max<int64_t>(kLaunchBlocks - nb_long, 1) * kRows);
+          hipLaunchKernelGGL((k_spmm_rows<VT, T, SC, PM, W>), dim3(nb_long + grid_for(row1 - row0, kRows)),
+                             dim3(kThreads), 0, c->stream, row0, row1, nb_long, m->n_long, m->long_rows, k, ld,
+                             m->row_ptr, m->gskip, m->col, m->col16, static_cast<const VT*>(m->val), X, Y, out, scale,
+                             colscale);
+        }
       };
       if (k <= 2)
         rows(std::integral_constant<int, 2>{});

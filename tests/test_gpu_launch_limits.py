@@ -38,3 +38,20 @@ def test_predict_of_more_rows_than_a_launch_takes():
     cut = (1 << 27) + 9
     out = ctx.predict_batch([preds[0], preds[0], preds[1]], xs, [0, cut, cut, m], out=out.fill_(np.nan))
     assert rows_equal(out, short[0], 0, cut) and rows_equal(out, short[1], cut, m)
+
+
+def test_narrow_product_of_more_rows_than_a_launch_takes():
+    """Sixty-four lanes a row for 17 columns: 2^26 rows are 2^32 threads.  The
+    points are further apart than the radius, so row p of the product is its
+    diagonal value times x_p: one term, exact."""
+    import torch
+    import paper_2411_05869_amd as gp
+    n, k = (1 << 26) + 3, 17
+    p = uniform_problem(8, 1, 5, r0=0.5, n1=0, n2=0, nugget=0.25)
+    ctx = gp.Context()
+    x = torch.arange(n, dtype=torch.float64, device="cuda").view(n, 1)
+    K = ctx.assemble(ctx.dataset(x, cell=[8.0]), p.theta, gp.MIXED)
+    assert K.nnz == n
+    X = torch.rand((n, k), dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(3))
+    Y = ctx.matvec(K, X)
+    assert torch.equal(Y, X.mul_(1.25))
