@@ -1005,9 +1005,11 @@ class LaunchGraph {
   }
   explicit operator bool() const { return exec_ != nullptr; }
 
-  // records what enqueue() launches on c->stream; nothing of it runs
+  // records what enqueue() launches on c->stream, unless something is recorded
+  // already; nothing of it runs
   template <typename F>
   void record(F&& enqueue) {
+    if (exec_) return;
     if (!c_->recorder && hipStreamCreateWithFlags(&c_->recorder, hipStreamNonBlocking) != hipSuccess) {
       (void)hipGetLastError();
       c_->recorder = nullptr;

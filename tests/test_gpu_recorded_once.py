@@ -30,19 +30,21 @@ def _host_bytes():
 def test_refused_convergence_leaves_nothing():
     import torch
     import paper_2411_05869_amd as gp
-    # well conditioned: eight iterations take the recursion below a bound that rounding keeps the
-    # recomputed residual above
-    p = uniform_problem(1500, 2, 78, r0=0.02, n1=0, n2=0, nugget=1.0)
+    # a nugget of 100 times the variance: eight iterations take the recursion to 1e-18 |y|, while
+    # rounding keeps the recomputed residual above 1e-16 |y|
+    p = uniform_problem(1500, 2, 78, r0=0.02, n1=0, n2=0, nugget=100.0)
     ctx = gp.Context()
     K = ctx.assemble(ctx.dataset(dev(p.x), cell=p.cell), p.theta, 0)
     y, a = dev(p.z_std), torch.empty(p.n, dtype=torch.float64, device="cuda")
 
-    def solve():
-        return ctx.solve(K, y, a, rtol=1e-17, max_iter=24, solver=gp.SOLVER_CG, raise_on_error=False)
+    def solve(max_iter=24):
+        return ctx.solve(K, y, a, rtol=1e-17, max_iter=max_iter, solver=gp.SOLVER_CG, precond=gp.PRECOND_JACOBI,
+                         raise_on_error=False)
 
+    assert solve(8)["refreshes"] == 1  # the first block looks converged
     for _ in range(100):
         r = solve()
-    assert r["cg_iters"] == 24 and r["refreshes"] == 3  # refused after each of its blocks, the first among them
+    assert r["cg_iters"] == 24 and r["refreshes"] >= 1  # and is refused
     before = _host_bytes()
     solves = 200
     for _ in range(solves):
