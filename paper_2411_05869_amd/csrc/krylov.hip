@@ -988,9 +988,14 @@ static double logsum_f64(gp_ctx* c, const double* a, int64_t n) {
 // 19.8 -> 19.6; a solve of 19M entries 17.25 -> 17.35: there the GPU is the later
 // of the two either way, and leaves a little more room between a graph's kernels.
 constexpr int64_t kGraphEntries = int64_t(8) << 20;
+// Iterations a solve alone still needs, by the decline of its residual, from which on
+// its block is recorded (with log det steps left to enqueue beside it: any number).
+// With none recorded a solve of 24 iterations takes 576 us instead of 633 (n = 2000),
+// one of 96 1.82 ms instead of 1.86, one of 232 (n = 10,007) 5.2 instead of 4.8.
+constexpr int kGraphIters = 64;
 
 // A sequence of launches recorded once and launched with one call: 29 us to
-// record 33 kernels and 79 to instantiate (a solve does both while its second
+// record 33 kernels and 79 to instantiate (a solve does both while a
 // block runs), 42 to destroy.  Kept for one solve; without the means to record (a
 // stream, memory) there is none and the caller launches plainly.
 class LaunchGraph {
@@ -1147,8 +1152,17 @@ SolveResult pcg_solve(gp_ctx* c, gp_matrix* m, const double* y, double* x, doubl
   // iteration, n = 30,011: 18.45 -> 17.97, n = 60,013: 31.4 -> 31.1, n = 109,500: 79.2 -> 78.6).
   // Where the host then finds that it has to act (apparent convergence, a failure)
   // the block ahead has done nothing: the device tests the same conditions and
-  // sets hold.
+  // sets hold.  Such a block still costs its launches, so none is enqueued where the
+  // block in flight is likely to be the last (a solve of eight iterations, n = 2000:
+  // 440 -> 258 us, with the recording that it no longer sees either).
   int it = 0, queued = 0;  // iterations done, enqueued
+  // iterations still needed after it, if the residual goes on falling as it has
+  // (at the start: tenfold an iteration)
+  auto left = [&]() {
+    const double rn = std::sqrt(sc.rr), most = max_iter - it;
+    if (it == 0) return std::min(most, -std::log10(rtol));
+    return rn < ynorm ? std::min(most, it * std::log(rn / target) / std::log(ynorm / rn)) : most;
+  };
   auto enqueue = [&]() {
     const int steps = std::min(kCheckEvery, max_iter - queued);
     auto plain = [&]() {
@@ -1163,14 +1177,17 @@ SolveResult pcg_solve(gp_ctx* c, gp_matrix* m, const double* y, double* x, doubl
     else
       plain();
     record_block(c, (queued / kCheckEvery) & 1);
-    // recorded while the second block runs
-    if (queued == kCheckEvery && steps == kCheckEvery && m->nnz <= kGraphEntries && !c->prof_on) block.record(plain);
+    // recorded while what is enqueued runs
+    if (queued > 0 && steps == kCheckEvery && m->nnz <= kGraphEntries && !c->prof_on &&
+        (c->feed || left() >= queued + kCheckEvery - it + kGraphIters))
+      block.record(plain);
     queued += steps;
   };
-  const int ahead = c->prof_on ? 0 : kCheckEvery;  // (a profile counts the launches that do something)
   int slot = 0;
   while (it < max_iter) {
-    while (queued < max_iter && queued - it <= ahead) enqueue();
+    if (queued == it) enqueue();
+    // (a profile counts the launches that do something: none ahead)
+    if (queued < max_iter && queued - it <= kCheckEvery && !c->prof_on && left() > queued - it) enqueue();
     side_pump(c);  // the side stream's queue topped up before the host waits
     wait_block(c, (it / kCheckEvery) & 1);
     sc = hs[slot];
