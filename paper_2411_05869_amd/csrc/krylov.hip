@@ -444,7 +444,7 @@ __global__ void __launch_bounds__(kThreads) k_beta_fin(const double* __restrict_
     if (!isfinite(r[0]) || !isfinite(r[1])) s->status = 1;
     if (host) {
       if (mode == 3) {
-        // the host's own conditions for looking at the solve before it goes on
+        // the host has to look at the solve before it goes on
         s->hold = s->status != 0 || sqrt(r[1]) <= target;
         host += s->blocks & 1;
         s->blocks += 1;
@@ -1151,10 +1151,10 @@ SolveResult pcg_solve(gp_ctx* c, gp_matrix* m, const double* y, double* x, doubl
   // does not wait for the host to wake and enqueue (n = 2000: 20.2 -> 19.6 us an
   // iteration, n = 30,011: 18.45 -> 17.97, n = 60,013: 31.4 -> 31.1, n = 109,500: 79.2 -> 78.6).
   // Where the host then finds that it has to act (apparent convergence, a failure)
-  // the block ahead has done nothing: the device tests the same conditions and
-  // sets hold.  Such a block still costs its launches, so none is enqueued where the
-  // block in flight is likely to be the last (a solve of eight iterations, n = 2000:
-  // 440 -> 258 us, with the recording that it no longer sees either).
+  // the block ahead has done nothing: the device sets hold, and the host goes by that.
+  // Such a block still costs its launches, so none is enqueued where the block in flight
+  // is likely to be the last (a solve of eight iterations, n = 2000: 440 -> 258 us, with
+  // the recording that it no longer sees either).
   int it = 0, queued = 0;  // iterations done, enqueued
   // iterations still needed after it, if the residual goes on falling as it has
   // (at the start: tenfold an iteration)
@@ -1197,9 +1197,9 @@ SolveResult pcg_solve(gp_ctx* c, gp_matrix* m, const double* y, double* x, doubl
       res.st = GP_ENOTPD;
       break;
     }
-    // at apparent convergence the residual is recomputed as y - K x and replaces
-    // the recursive one
-    if (std::sqrt(sc.rr) <= target) {
+    // at apparent convergence (the device has decided and holds the block ahead) the
+    // residual is recomputed as y - K x and replaces the recursive one
+    if (sc.hold) {
       queued = it;  // the block ahead has done nothing
       sc = true_residual();
       ++res.refreshes;
