@@ -5,6 +5,7 @@
 
 #include <cstdint>
 #include <cstdio>
+#include <exception>
 #include <memory>
 #include <string>
 #include <vector>
@@ -306,6 +307,20 @@ struct JoinGuard {
       c->side_pending = false;
     }
   }
+};
+
+// For a scope whose kernels write the context's pinned buffer: left by an exception,
+// it waits for the context's stream, so that no kernel still in flight writes there
+// when a later call has filled the buffer anew.
+struct DrainGuard {
+  gp_ctx* c;  // null: nothing to wait for
+  int entered = std::uncaught_exceptions();
+  explicit DrainGuard(gp_ctx* c_) : c(c_) {}
+  ~DrainGuard() {
+    if (c && std::uncaught_exceptions() > entered) (void)hipStreamSynchronize(c->stream);
+  }
+  DrainGuard(const DrainGuard&) = delete;
+  DrainGuard& operator=(const DrainGuard&) = delete;
 };
 
 template <typename T>

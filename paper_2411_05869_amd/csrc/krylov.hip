@@ -1084,6 +1084,7 @@ SolveResult pcg_solve(gp_ctx* c, gp_matrix* m, const double* y, double* x, doubl
   // launch and 2 us of the stream): of the last two blocks in hs[0] and hs[1], of a
   // start or a recomputed residual in hs[2]
   CgScalars* hs = static_cast<CgScalars*>(pinned(c, 3 * sizeof(CgScalars)));
+  const DrainGuard drain(c);
   const dim3 G(kRedBlocks), B(kThreads), GR(red_blocks(n));
   auto read = [&]() {
     side_pump(c);  // the side stream's queue topped up before the host waits
@@ -1392,6 +1393,7 @@ static void pcg_device_impl(gp_ctx* c, gp_matrix* m, const double* y, double* x,
   double* pqp = part;
   double* spart = ppart;
   CtlAll* hall = poll ? static_cast<CtlAll*>(pinned(c, sizeof(CtlAll))) : nullptr;
+  const DrainGuard drain(poll ? c : nullptr);
   auto wait = [&]() {
     side_pump(c);
     sync(c);
