@@ -797,8 +797,10 @@ Grid make_grid(const gp_dataset* ds, const gp_theta* th) {
       double R = std::ceil(need);
       if (R < 1) R = 1;
       // beyond the grid there is nothing: its own points need no more rings than
-      // it has cells, while a point outside reaches it from further away
-      g.Rt[k] = static_cast<int32_t>(std::min(R, 1.0e9));
+      // it has cells, while a point outside reaches it from further away (cell_coord
+      // stops at 10^9 cells either way: that and the rings fit in an int together,
+      // and the rings pass it by more than an axis has cells)
+      g.Rt[k] = static_cast<int32_t>(std::min(R, 1.1e9));
       if (R > ds->g[k]) R = ds->g[k];
       g.R[k] = static_cast<int32_t>(R);
     } else {
