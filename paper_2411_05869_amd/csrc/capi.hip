@@ -96,12 +96,14 @@ void record_block(gp_ctx* c, int i) {
 
 void wait_block(gp_ctx* c, int i) { GPS_HIP(hipEventSynchronize(c->ev_block[i])); }
 
+void make_side(gp_ctx* c) {
+  if (!c->side) GPS_HIP(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
+}
+
 void fork_side(gp_ctx* c) {
-  if (!c->side) {
-    GPS_HIP(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
-    GPS_HIP(hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming));
-    GPS_HIP(hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming));
-  }
+  make_side(c);
+  if (!c->ev_fork) GPS_HIP(hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming));
+  if (!c->ev_join) GPS_HIP(hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming));
   GPS_HIP(hipEventRecord(c->ev_fork, c->stream));
   GPS_HIP(hipStreamWaitEvent(c->side, c->ev_fork, 0));
   c->side_pending = true;
@@ -327,12 +329,11 @@ gp_status gp_ctx_destroy(gp_ctx* c) {
       if (e) (void)hipEventDestroy(e);
     c->evpool.clear();
     c->feed.reset();
-    if (c->recorder) (void)hipStreamDestroy(c->recorder);
     if (c->side) {
       (void)hipStreamSynchronize(c->side);
       (void)hipStreamDestroy(c->side);
-      (void)hipEventDestroy(c->ev_fork);
-      (void)hipEventDestroy(c->ev_join);
+      if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
+      if (c->ev_join) (void)hipEventDestroy(c->ev_join);
     }
     for (hipEvent_t e : c->feed_ev) (void)hipEventDestroy(e);
     c->feed_ev.clear();

@@ -103,7 +103,6 @@ struct gp_ctx {
   bool side_pending = false;  // work was forked to the side stream and not joined yet
   bool alloc_locked = false;  // set while work is enqueued on the side stream
   bool concurrent = true;     // the log det of a likelihood on the side stream
-  hipStream_t recorder = nullptr;  // launches are recorded here, none run (created on first use)
   bool recording = false;     // what is enqueued is being recorded
   // side-stream work not enqueued yet, and a ring of events marking the
   // completion of its latest units (side_pump)
@@ -271,6 +270,7 @@ void wait_block(gp_ctx* c, int i);
 // uses must be allocated before the fork, in the main stream's order);
 // join_side() orders the main stream after the side stream's work.
 void fork_side(gp_ctx* c);
+void make_side(gp_ctx* c);   // creates the stream
 void join_side(gp_ctx* c);
 // A long side-stream sequence (the SLQ log det: several hundred launches) is
 // not enqueued in one go: once the device queue is full the host blocks in

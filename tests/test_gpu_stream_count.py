@@ -1,0 +1,43 @@
+"""A context takes one stream beside the caller's, for the log det.
+
+HIP deals streams to four hardware queues in turn, so that with one stream a
+context at most a quarter of consecutive contexts have their log det on the
+solve's queue, where the two take turns instead of overlapping: 3 of 12.  A
+likelihood there takes what it takes with the overlap off (about 10.4 ms
+against 8.2 with it); the line is drawn half way."""
+import time
+
+import numpy as np
+import pytest
+
+from gpu_util import dev
+from workloads import gmm_problem
+
+pytestmark = pytest.mark.gpu
+
+
+def test_log_dets_overlap_their_solves():
+    import torch
+    import paper_2411_05869_amd as gp
+    p = gmm_problem(30011, 3, 0.01, 0.03)
+    y = dev(p.y)
+    alpha = torch.empty_like(y)
+
+    def median(ctx, K):
+        t = []
+        for _ in range(7):
+            t0 = time.perf_counter()
+            ctx.loglik(K, y, alpha_out=alpha)
+            t.append(time.perf_counter() - t0)
+        return float(np.median(t[1:]))
+
+    on, off = [], []
+    for _ in range(12):
+        ctx = gp.Context()
+        K = ctx.assemble(ctx.dataset(dev(p.x), cell=p.cell), p.theta, gp.MIXED)
+        on.append(median(ctx, K))
+        ctx.set_concurrency(False)
+        off.append(median(ctx, K))
+    line = 0.5 * (min(on) + float(np.median(off)))
+    turns = int(np.sum(np.array(on) > line))
+    assert turns <= 3, (turns, on, off)
