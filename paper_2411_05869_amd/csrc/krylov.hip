@@ -983,11 +983,17 @@ static double logsum_f64(gp_ctx* c, const double* a, int64_t n) {
 // A launch of the iteration's kernels costs the host 3 - 4 us (it grows with the
 // bytes of arguments), so four per iteration and the log det's seven per step
 // beside them keep the GPU waiting where the kernels are as short; a graph of
-// the block's 33 launches costs 22 us.  Plain launches -> graphs, a likelihood:
-// 0.3M entries (n = 2000) 3.8 -> 3.25 ms, 2.0M (n = 30,011) 12.5 -> 10.8, 5.0M (n = 60,013)
-// 19.8 -> 19.6; a solve of 19M entries 17.25 -> 17.35: there the GPU is the later
-// of the two either way, and leaves a little more room between a graph's kernels.
-constexpr int64_t kGraphEntries = int64_t(8) << 20;
+// the block's 33 launches costs 22 us.  Longer kernels wait for no host, and a graph
+// leaves a little more room between them.  Plain launches -> graphs, a likelihood
+// (50 Lanczos steps) and a solve alone, ms (mixture; FP64 / mixed, Jacobi):
+//   0.6M entries 11.3 -> 9.7, 10.1 -> 9.1 / 11.5 -> 9.9, 10.4 -> 9.0
+//   1.5M         12.4 -> 11.4, 10.8 -> 10.1 / 12.1 -> 11.1, 10.6 -> 9.9
+//   2.7M         18.3 -> 17.8, 16.6 -> 16.2 / 16.8 -> 16.1, 15.4 -> 14.6
+//   5.0M         19.2 -> 19.3, 16.9 -> 17.4 / 17.6 -> 17.6, 15.5 -> 15.9
+//   6.3M         24.6 -> 24.9, 21.9 -> 22.4 / 21.9 -> 22.3, 19.6 -> 20.2
+// (block Jacobi: 2.7M 21.8 -> 21.9, 19.9 -> 20.4 / 20.7 -> 20.0, 18.7 -> 18.4; 5.0M 22.2 -> 22.7,
+// 20.2 -> 20.8 / 20.6 -> 21.0, 18.7 -> 19.2.)
+constexpr int64_t kGraphEntries = int64_t(3) << 20;
 // Iterations a solve alone still needs, by the decline of its residual, from which on
 // its block is recorded (with log det steps left to enqueue beside it: any number).
 // With none recorded a solve of 24 iterations takes 576 us instead of 633 (n = 2000),
