@@ -190,6 +190,53 @@ __device__ __forceinline__ void lanes_sync_lds() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// The cells lo .. hi of the point's window; false: none
+template <int D>
+__device__ __forceinline__ bool point_window(const PredArgs& a, const double* xp, int* lo, int* hi) {
+  bool some = true;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    lo[k] = hi[k] = 0;
+    if (k < D) {
+      const int c = cell_coord(xp[k], a.lo[k], a.cell[k]);
+      lo[k] = max(c - a.R[k], 0);
+      hi[k] = min(c + a.R[k], a.g[k] - 1);
+      some = some && lo[k] <= hi[k];
+    }
+  }
+  return some;
+}
+
+// acc += C_core(x*, x_q) s0 f0(u) alpha_q, u2 = u^2 < 1
+template <int D, bool MIXED, int CK>
+__device__ __forceinline__ void add_hit(const PredArgs& a, const double* xp, double sp, double Sp, int32_t q,
+                                        const double* xq, double u2, double al, double& acc) {
+  double v = a.kt.s0 * wendland(u2, a.kt.variant);
+  if constexpr (CK == 1) v = core_value<D, 1>(a.kt.core, xp, xq, 0.0, 0.0, 0.0, 0.0) * v;
+  if constexpr (CK == 2) v = core_value<D, 2>(a.kt.core, xp, xq, sp, Sp, a.kt.core.sig[q], a.kt.core.Sig[q]) * v;
+  // the mixed form: the value and alpha rounded to float32, their product in float32
+  if constexpr (MIXED)
+    acc += static_cast<double>(static_cast<float>(v) * static_cast<float>(al));
+  else
+    acc += v * al;
+}
+
+// acc += f_i(x*) c_i where the point lies in a bump of group i
+template <int D>
+__device__ __forceinline__ void add_bumps(const PredArgs& a, const double* xp, int i, double& acc) {
+  double f = 0.0;
+  bool in_group = false;
+  for (int j = 0; j < a.kt.n2; ++j) {
+    const Bump& bp = a.kt.bumps[i * a.kt.n2 + j];
+    const double ub2 = scaled_sq<D>(xp, bp.h, bp.inv);
+    if (bp.a > 0.0 && ub2 < 1.0) {
+      in_group = true;
+      f = f + bp.a * exp(bp.b * (1.0 - 1.0 / (1.0 - ub2)));
+    }
+  }
+  if (in_group) acc += f * a.coef[i];
+}
+
 // The mean at one test point xp (local part over the cell window, plus the
 // bump groups through c_i when there is no core kernel), by the kPl lanes of a
 // point; lane: 0 .. kPl - 1, ids: the point's kCandList words of LDS.  Every lane
@@ -197,17 +244,10 @@ __device__ __forceinline__ void lanes_sync_lds() {
 template <int D, bool MIXED, int CK>
 __device__ __forceinline__ double predict_point(const PredArgs& a, const CoreBasis& cb, const double* xp, int lane,
                                                 int32_t* ids) {
-  int c[3] = {0, 0, 0};
-  for (int k = 0; k < D; ++k) c[k] = cell_coord(xp[k], a.lo[k], a.cell[k]);
   double sp = 0.0, Sp = 0.0;
   if constexpr (CK == 2) core_point_fields<D>(cb, xp, &sp, &Sp);
-  int lo_[3] = {0, 0, 0}, hi_[3] = {0, 0, 0};
-  bool empty = false;
-  for (int k = 0; k < D; ++k) {
-    lo_[k] = max(c[k] - a.R[k], 0);
-    hi_[k] = min(c[k] + a.R[k], a.g[k] - 1);
-    if (lo_[k] > hi_[k]) empty = true;
-  }
+  int lo_[3], hi_[3];
+  const bool empty = !point_window<D>(a, xp, lo_, hi_);
   const int shift = lane_id() & ~(kPl - 1);  // the point's first lane of the wave
   const uint32_t below = (1u << lane) - 1;
   double acc = 0.0;
@@ -280,37 +320,56 @@ __device__ __forceinline__ double predict_point(const PredArgs& a, const CoreBas
         for (int u = 0; u < kHitUnroll; ++u) load_train<D>(a, q[u], xq[u], al[u]);
 #pragma unroll
         for (int u = 0; u < kHitUnroll; ++u)
-          if (t0 + u * kPl + lane < nhit) {
-            double v = a.kt.s0 * wendland(scaled_sq<D>(xp, xq[u], a.kt.inv0), a.kt.variant);
-            if constexpr (CK == 1) v = core_value<D, 1>(a.kt.core, xp, xq[u], 0.0, 0.0, 0.0, 0.0) * v;
-            if constexpr (CK == 2)
-              v = core_value<D, 2>(a.kt.core, xp, xq[u], sp, Sp, a.kt.core.sig[q[u]], a.kt.core.Sig[q[u]]) * v;
-            // the mixed form: the value and alpha rounded to float32, their product in float32
-            if constexpr (MIXED)
-              acc += static_cast<double>(static_cast<float>(v) * static_cast<float>(al[u]));
-            else
-              acc += v * al[u];
-          }
+          if (t0 + u * kPl + lane < nhit)
+            add_hit<D, MIXED, CK>(a, xp, sp, Sp, q[u], xq[u], scaled_sq<D>(xp, xq[u], a.kt.inv0), al[u], acc);
       }
     }
   }
   // bump groups of the test point, a group per lane (with a core kernel: k_predict_groups)
-  for (int i = lane; CK == 0 && i < a.kt.n1; i += kPl) {
-    double f = 0.0;
-    bool in_group = false;
-    for (int j = 0; j < a.kt.n2; ++j) {
-      const Bump& bp = a.kt.bumps[i * a.kt.n2 + j];
-      const double ub2 = scaled_sq<D>(xp, bp.h, bp.inv);
-      if (bp.a > 0.0 && ub2 < 1.0) {
-        in_group = true;
-        f = f + bp.a * exp(bp.b * (1.0 - 1.0 / (1.0 - ub2)));
-      }
-    }
-    if (in_group) acc += f * a.coef[i];
-  }
+  for (int i = lane; CK == 0 && i < a.kt.n1; i += kPl) add_bumps<D>(a, xp, i, acc);
 #pragma unroll
   for (int off = kPl / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kPl);
   return acc;
+}
+
+// The same mean by one thread: acc, kPl words of LDS kThreads apart, holds the sums
+// of the sixteen lanes.  Candidates come in the order of the list (lane by lane its
+// pencils of a round), and a round's hits go to the lanes in turn.
+template <int D, bool MIXED, int CK>
+__device__ __forceinline__ double predict_point_alone(const PredArgs& a, const CoreBasis& cb, const double* xp,
+                                                      double* acc) {
+  double sp = 0.0, Sp = 0.0;
+  if constexpr (CK == 2) core_point_fields<D>(cb, xp, &sp, &Sp);
+  int lo_[3], hi_[3];
+  const bool some = point_window<D>(a, xp, lo_, hi_);
+#pragma unroll
+  for (int l = 0; l < kPl; ++l) acc[l * kThreads] = 0.0;
+  const int ny = hi_[1] - lo_[1] + 1;
+  const int64_t npen = some ? static_cast<int64_t>(ny) * (hi_[2] - lo_[2] + 1) : 0;
+  for (int64_t p0 = 0; p0 < npen; p0 += kPl * kPencils) {
+    int32_t nhit = 0;
+    for (int l = 0; l < kPl && p0 + l < npen; ++l)
+      for (int64_t pk = p0 + l; pk < min(npen, p0 + kPl * kPencils); pk += kPl) {
+        const int y = lo_[1] + static_cast<int>(pk % ny), z = lo_[2] + static_cast<int>(pk / ny);
+        const int64_t base = (static_cast<int64_t>(z) * a.g[1] + y) * a.g[0];
+        const int32_t e = a.cell_start[base + hi_[0] + 1];
+        for (int32_t q = a.cell_start[base + lo_[0]]; q < e; ++q) {
+          double xq[3], al;
+          load_train<D>(a, q, xq, al);
+          const double u2 = scaled_sq<D>(xp, xq, a.kt.inv0);
+          if (u2 < 1.0) add_hit<D, MIXED, CK>(a, xp, sp, Sp, q, xq, u2, al, acc[nhit++ % kPl * kThreads]);
+        }
+      }
+  }
+  for (int i = 0; CK == 0 && i < a.kt.n1; ++i) add_bumps<D>(a, xp, i, acc[i % kPl * kThreads]);
+  double s[kPl];
+#pragma unroll
+  for (int l = 0; l < kPl; ++l) s[l] = acc[l * kThreads];
+#pragma unroll
+  for (int off = kPl / 2; off > 0; off >>= 1)
+#pragma unroll
+    for (int l = 0; l < off; ++l) s[l] += s[l + off];
+  return s[0];
 }
 
 // rows t0 .. m - 1
@@ -325,6 +384,18 @@ __global__ void __launch_bounds__(kThreads) k_predict(PredArgs a, CoreBasis cb, 
   for (int k = 0; k < D; ++k) xp[k] = xs[t * D + k];
   const double v = predict_point<D, MIXED, CK>(a, cb, xp, lane, ids[g]);
   if (lane == 0) out[t] = v;
+}
+
+template <int D, bool MIXED, int CK>
+__global__ void __launch_bounds__(kThreads) k_predict_alone(PredArgs a, CoreBasis cb, int64_t t0, int64_t m,
+                                                            const double* __restrict__ xs,
+                                                            double* __restrict__ out) {
+  __shared__ double acc[kPl][kThreads];
+  const int64_t t = t0 + blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x;
+  if (t >= m) return;
+  double xp[3];
+  for (int k = 0; k < D; ++k) xp[k] = xs[t * D + k];
+  out[t] = predict_point_alone<D, MIXED, CK>(a, cb, xp, &acc[0][threadIdx.x]);
 }
 
 // Request of row t of a batch: the last r with roff[r] <= t (empty requests
@@ -359,6 +430,23 @@ __global__ void __launch_bounds__(kThreads) k_predict_batch(const PredArgs* __re
   for (int k = 0; k < D; ++k) xp[k] = xs[t * D + k];
   const double v = predict_point<D, MIXED, CK>(args[pi], cbs[pi], xp, lane, ids[g]);
   if (lane == 0) out[t] = v;
+}
+
+template <int D, bool MIXED, int CK>
+__global__ void __launch_bounds__(kThreads) k_predict_batch_alone(const PredArgs* __restrict__ args,
+                                                                  const CoreBasis* __restrict__ cbs,
+                                                                  const int32_t* __restrict__ req_pred,
+                                                                  const int64_t* __restrict__ roff, int nreq,
+                                                                  int64_t t0, int64_t m,
+                                                                  const double* __restrict__ xs,
+                                                                  double* __restrict__ out) {
+  __shared__ double acc[kPl][kThreads];
+  const int64_t t = t0 + blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x;
+  if (t >= m) return;
+  const int pi = req_pred[batch_request(roff, nreq, t)];
+  double xp[3];
+  for (int k = 0; k < D; ++k) xp[k] = xs[t * D + k];
+  out[t] = predict_point_alone<D, MIXED, CK>(args[pi], cbs[pi], xp, &acc[0][threadIdx.x]);
 }
 
 // Bump part with a core kernel: one wave per test point.  Lane i < n1 forms
@@ -617,11 +705,42 @@ static PredArgs pred_args(const gp_predictor* p) {
   return a;
 }
 
+// Whether a request of m rows takes a thread per point.  Where a window holds a dozen
+// candidates, sixteen lanes have little to share, and a thread per point
+// (predict_point_alone; the same value bitwise, so that the choice is free) is the better
+// form once the points fill the chip.  A thread's chain is its pencils' bounds and its
+// candidates; where the forms meet (thousands of rows) the rows are 2500 to 4000 times
+// that: one dimension 1 / 6 / 24 candidates 12 / 28 / 62, two 20 / 32 / 75, three 60 / 62 /
+// 110, two with a core kernel 23 / 50 / 180.  At two million rows, sixteen lanes -> a thread, us:
+// 327 -> 57, 344 -> 118, 403 -> 330; 454 -> 101, 458 -> 132, 469 -> 291; 517 -> 225, 560 -> 240, 572
+// -> 339; 48 candidates 520 -> 609, 521 -> 517, 604 -> 510 (10^5 training points; 10^6: 822 -> 899).
+// Without the packed data the forms meet earlier (three dimensions, 12 candidates: 10^5
+// points 623 -> 401, 10^6 0.88x).
+constexpr double kAloneCands = 30, kAlonePlain = 16;  // candidates of a mean window, packed and not
+constexpr double kAloneDense = 8;                     // times that: of a window of the fullest cells
+constexpr double kAloneRows = 2560;
+static_assert(kAloneCands * kAloneDense <= kCandList, "the list of such a window has one part");
+
+static bool alone(const gp_predictor* p, int64_t m) {
+  const gp_dataset* ds = p->ds;
+  double cells = 1.0, pencils = 1.0;  // of a window inside the grid
+  for (int k = 0; k < ds->d; ++k) {
+    const double w = std::min(2.0 * p->grid.R[k] + 1.0, static_cast<double>(ds->g[k]));
+    cells *= w;
+    if (k > 0) pencils *= w;
+  }
+  const double cands = cells * static_cast<double>(ds->n) / static_cast<double>(ds->ncells);
+  if (cands > (p->pack ? kAloneCands : kAlonePlain) || cells * ds->max_cell > kAloneCands * kAloneDense) return false;
+  const double chain = 2.0 * pencils + (p->kt.core.kind != GP_CORE_NONE ? 2.0 : 1.0) * cands;
+  return static_cast<double>(m) >= kAloneRows * chain;
+}
+
 void predict(gp_ctx* c, const gp_predictor* p, int64_t m, const double* xs, int prec, double* out) {
   if (m == 0) return;
   const gp_dataset* ds = p->ds;
   const PredArgs a = pred_args(p);
   const dim3 B(kThreads);
+  const bool one = alone(p, m);
   ProfScope ps(c, prec == GP_MIXED ? "predict_f32" : "predict_f64");
   auto go = [&](auto DD) {
     constexpr int D = decltype(DD)::value;
@@ -629,11 +748,14 @@ void predict(gp_ctx* c, const gp_predictor* p, int64_t m, const double* xs, int 
       constexpr int CK = decltype(CC)::value;
       for (int64_t t0 = 0; t0 < m; t0 += kLaunchRows) {
         const int64_t t1 = std::min(m, t0 + kLaunchRows);
-        const dim3 G(grid_for(t1 - t0, kPointsPerBlock));
+        const dim3 G(grid_for(t1 - t0, one ? kThreads : kPointsPerBlock));
+        auto rows = [&](auto kernel) {
+          hipLaunchKernelGGL(kernel, G, B, 0, c->stream, a, p->cb, t0, t1, xs, out);
+        };
         if (prec == GP_MIXED)
-          hipLaunchKernelGGL((k_predict<D, true, CK>), G, B, 0, c->stream, a, p->cb, t0, t1, xs, out);
+          rows(one ? k_predict_alone<D, true, CK> : k_predict<D, true, CK>);
         else
-          hipLaunchKernelGGL((k_predict<D, false, CK>), G, B, 0, c->stream, a, p->cb, t0, t1, xs, out);
+          rows(one ? k_predict_alone<D, false, CK> : k_predict<D, false, CK>);
         if constexpr (CK != 0) {
           if (p->nm > 0)
             hipLaunchKernelGGL((k_predict_groups<D, CK>), dim3(grid_for((t1 - t0) * kWave, kThreads)), B, 0,
@@ -678,8 +800,11 @@ void predict_batch(gp_ctx* c, int32_t nreq, const gp_predictor* const* preds, co
   }
   const int d = uniq[0]->ds->d;
   const int ck = uniq[0]->kt.core.kind;
-  bool any_nm = false;
-  for (const gp_predictor* p : uniq) any_nm = any_nm || p->nm > 0;
+  bool any_nm = false, one = true;
+  for (const gp_predictor* p : uniq) {
+    any_nm = any_nm || p->nm > 0;
+    one = one && alone(p, m);
+  }
   const size_t np = uniq.size();
   const size_t b_args = sizeof(PredArgs) * np, b_cb = sizeof(CoreBasis) * np;
   const size_t b_req = sizeof(int32_t) * nreq, b_off = sizeof(int64_t) * (nreq + 1);
@@ -708,13 +833,14 @@ void predict_batch(gp_ctx* c, int32_t nreq, const gp_predictor* const* preds, co
       constexpr int CK = decltype(CC)::value;
       for (int64_t t0 = 0; t0 < m; t0 += kLaunchRows) {
         const int64_t t1 = std::min(m, t0 + kLaunchRows);
-        const dim3 G(grid_for(t1 - t0, kPointsPerBlock));
+        const dim3 G(grid_for(t1 - t0, one ? kThreads : kPointsPerBlock));
+        auto rows = [&](auto kernel) {
+          hipLaunchKernelGGL(kernel, G, B, 0, c->stream, da, dc, dreq, droff, nreq, t0, t1, xs, out);
+        };
         if (prec == GP_MIXED)
-          hipLaunchKernelGGL((k_predict_batch<D, true, CK>), G, B, 0, c->stream, da, dc, dreq, droff, nreq, t0, t1, xs,
-                             out);
+          rows(one ? k_predict_batch_alone<D, true, CK> : k_predict_batch<D, true, CK>);
         else
-          hipLaunchKernelGGL((k_predict_batch<D, false, CK>), G, B, 0, c->stream, da, dc, dreq, droff, nreq, t0, t1,
-                             xs, out);
+          rows(one ? k_predict_batch_alone<D, false, CK> : k_predict_batch<D, false, CK>);
         if constexpr (CK != 0) {
           if (any_nm)
             hipLaunchKernelGGL((k_predict_groups_batch<D, CK>), dim3(grid_for((t1 - t0) * kWave, kThreads)), B, 0,
