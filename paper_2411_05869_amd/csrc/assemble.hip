@@ -482,7 +482,17 @@ __global__ void __launch_bounds__(kThreads) k_local_rows_split(AsmArgs a) {
 //                   fill: 183.8 -> 32.7, 230.9 -> 72.5, 354.6 -> 259.3 (uniform n = 300,000 63.5 -> 62.6)
 //   d = 3, count: n = 60,000 39.4 -> 30.1, 109,500 71.8 -> 75.9, 365,000 111.5 -> 212.9
 //          fill: 64.5 -> 38.3, 111.6 -> 85.7, 240.9 -> 252.2
-constexpr int64_t split_rows(int d, bool fill) { return int64_t(d == 3 ? 65536 : 131072) << (fill ? 1 : 0); }
+// Those pencils hold 8 candidates and more.  Shorter ones leave lanes of a row idle, and
+// the limit falls with them (uniform points, count / fill):
+//   d = 2, pencils of 1.5: n = 100,003 9.1 -> 13.4 / 15.0 -> 16.2; fill of 250,007 20.8 -> 31.6
+//                 4: 10.8 -> 14.1 / 19.6 -> 18.0; 27.3 -> 32.7;  10: 14.1 -> 14.0 / 29.6 -> 20.9; 39.7 -> 39.5
+//   d = 3, pencils of 0.5: n = 60,013 16.2 -> 21.8 / 20.2 -> 24.4; fill of 100,003 23.0 -> 34.5
+//                 4: 21.5 -> 23.2 / 33.9 -> 27.0; 36.1 -> 37.6;  10: 27.3 -> 22.9 / 51.9 -> 32.2; 57.4 -> 44.6
+bool split_rows(const gp_dataset* ds, const Grid& g, bool fill) {
+  const double pencil = std::min(2.0 * g.R[0] + 1.0, static_cast<double>(g.g[0])) * ds->mates;  // about
+  const double limit = (ds->d == 3 ? 65536.0 : 131072.0) * (fill ? 2.0 : 1.0);
+  return static_cast<double>(ds->n) <= limit * std::min(1.0, pencil / 8.0);
+}
 
 // Rows with a group bit: |U_M| group entries come first in the row.
 __global__ void __launch_bounds__(kThreads) k_group_counts(int64_t nm, const int32_t* __restrict__ mlist,
@@ -974,7 +984,7 @@ gp_matrix* assemble(gp_ctx* c, const gp_dataset* ds, const gp_theta* th, int pre
   dispatch_d(d, [&](auto DD) {
     constexpr int D = decltype(DD)::value;
     ProfScope ps(c, "asm_count_local");
-    if (n <= split_rows(D, false))
+    if (split_rows(ds, grid, false))
       hipLaunchKernelGGL((k_local_rows_split<D, false, double>), dim3(grid_for(n * kSplit, kThreads)), dim3(kThreads),
                          0, c->stream, a);
     else
@@ -1184,7 +1194,7 @@ gp_matrix* assemble(gp_ctx* c, const gp_dataset* ds, const gp_theta* th, int pre
         constexpr int CK = decltype(CC)::value;
         {
           ProfScope ps(c, "asm_fill_local");
-          if (n <= split_rows(D, true))
+          if (split_rows(ds, grid, true))
             hipLaunchKernelGGL((k_local_rows_split<D, true, VT, CK>), dim3(grid_for(n * kSplit, kThreads)),
                                dim3(kThreads), 0, c->stream, a);
           else

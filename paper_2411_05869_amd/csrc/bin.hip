@@ -114,13 +114,29 @@ __global__ void k_gather(const double* __restrict__ x, int64_t n, int d, const i
   key[i] = key_orig[o];
 }
 
-__global__ void k_max_count(const int32_t* __restrict__ count, int64_t ncells, int32_t* __restrict__ out) {
+// the fullest cell, and the ordered pairs of points that share a cell
+struct CellStats {
+  unsigned long long pairs;
+  int32_t most, pad;
+};
+
+__global__ void k_cell_stats(const int32_t* __restrict__ count, int64_t ncells, CellStats* __restrict__ out) {
   int32_t m = 0;
+  unsigned long long s = 0;
   for (int64_t i = blockIdx.x * static_cast<int64_t>(kThreads) + threadIdx.x; i < ncells;
-       i += static_cast<int64_t>(gridDim.x) * kThreads)
-    m = max(m, count[i]);
-  for (int off = kWave / 2; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off, kWave));
-  if (lane_id() == 0) atomicMax(out, m);
+       i += static_cast<int64_t>(gridDim.x) * kThreads) {
+    const int32_t c = count[i];
+    m = max(m, c);
+    s += static_cast<unsigned long long>(c) * static_cast<unsigned long long>(max(c - 1, 0));
+  }
+  for (int off = kWave / 2; off > 0; off >>= 1) {
+    m = max(m, __shfl_xor(m, off, kWave));
+    s += __shfl_xor(s, off, kWave);
+  }
+  if (lane_id() == 0) {
+    atomicMax(&out->most, m);
+    if (s) atomicAdd(&out->pairs, s);
+  }
 }
 
 }  // namespace
@@ -198,16 +214,16 @@ void bin_dataset(gp_ctx* c, gp_dataset* ds, const double* x_dev, const double* c
   TmpBuf key_orig(c, sizeof(int32_t) * n);
   TmpBuf count(c, sizeof(int32_t) * ncells);
   TmpBuf tmp(c, sizeof(int32_t) * n);
-  TmpBuf mx(c, sizeof(int32_t));
+  TmpBuf stats(c, sizeof(CellStats));
   GPS_HIP(hipMemsetAsync(count.p, 0, sizeof(int32_t) * ncells, c->stream));
-  GPS_HIP(hipMemsetAsync(mx.p, 0, sizeof(int32_t), c->stream));
+  GPS_HIP(hipMemsetAsync(stats.p, 0, sizeof(CellStats), c->stream));
   hipLaunchKernelGGL(k_keys_hist, dim3(grid_for(n, kThreads)), dim3(kThreads), 0, c->stream, x_dev, n, d, bg,
                      key_orig.as<int32_t>(), count.as<int32_t>());
   check_launch("keys");
   scan_i32_to_i32(c, count.as<int32_t>(), ds->cell_start, ncells);
-  hipLaunchKernelGGL(k_max_count, dim3(std::min<int64_t>(grid_for(ncells, kThreads), 1024)), dim3(kThreads), 0,
-                     c->stream, count.as<int32_t>(), ncells, mx.as<int32_t>());
-  check_launch("max count");
+  hipLaunchKernelGGL(k_cell_stats, dim3(std::min<int64_t>(grid_for(ncells, kThreads), 1024)), dim3(kThreads), 0,
+                     c->stream, count.as<int32_t>(), ncells, stats.as<CellStats>());
+  check_launch("cell stats");
   GPS_HIP(hipMemsetAsync(count.p, 0, sizeof(int32_t) * ncells, c->stream));
   hipLaunchKernelGGL(k_scatter, dim3(grid_for(n, kThreads)), dim3(kThreads), 0, c->stream, key_orig.as<int32_t>(),
                      n, ds->cell_start, count.as<int32_t>(), ds->perm);
@@ -219,10 +235,11 @@ void bin_dataset(gp_ctx* c, gp_dataset* ds, const double* x_dev, const double* c
   hipLaunchKernelGGL(k_gather, dim3(grid_for(n, kThreads)), dim3(kThreads), 0, c->stream, x_dev, n, d, ds->perm,
                      key_orig.as<int32_t>(), ds->xb, ds->iperm, ds->key);
   check_launch("gather");
-  int32_t* h = static_cast<int32_t*>(pinned(c, sizeof(int32_t)));
-  GPS_HIP(hipMemcpyAsync(h, mx.p, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
+  CellStats* h = static_cast<CellStats*>(pinned(c, sizeof(CellStats)));
+  GPS_HIP(hipMemcpyAsync(h, stats.p, sizeof(CellStats), hipMemcpyDeviceToHost, c->stream));
   sync(c);
-  ds->max_cell = *h;
+  ds->max_cell = h->most;
+  ds->mates = static_cast<double>(h->pairs) / static_cast<double>(n);
 }
 
 }  // namespace gps

@@ -124,6 +124,7 @@ struct gp_dataset {
   int32_t* key = nullptr;       // cell key of each binned point
   int32_t* cell_start = nullptr;// ncells + 1
   int32_t max_cell = 0;         // most points in one cell
+  double mates = 0;             // other points in a point's cell, on average
   size_t bytes = 0;
 };
 

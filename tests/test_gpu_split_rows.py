@@ -44,3 +44,11 @@ def test_window_sizes(d, n, r0, cell, core):
         p.theta.core = random_core(core, d, 2)
     for prec in (0, 1):
         _check(p, prec, np.full(d, r0 * cell))
+
+
+# pencils of 9 to 10 candidates: the limits themselves and one row past them
+@pytest.mark.parametrize("d,n,r0", [(2, 131072, 4.3e-3), (2, 131073, 4.3e-3), (2, 262144, 3e-3), (2, 262145, 3e-3),
+                                    (3, 65536, 0.032), (3, 65537, 0.032), (3, 131072, 0.0253)])
+def test_long_pencils_at_the_limits(d, n, r0):
+    p = uniform_problem(n, d, 5 + d, r0=r0, n1=2, n2=1, bump_radius=2 * r0)
+    _check(p, n % 2, p.cell)
