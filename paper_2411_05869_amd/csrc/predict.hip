@@ -85,15 +85,17 @@ __global__ void __launch_bounds__(kThreads) k_pack(int64_t n, int d, const doubl
 // Member lists of the bump groups, one block per group i: the masked points
 // with bit i, ascending.  FILL = false: their number into off[i + 1];
 // FILL = true: the lists, from off[i] on.
+constexpr int kListThreads = 1024;
+
 template <bool FILL>
-__global__ void __launch_bounds__(kThreads) k_group_members(int64_t nm, const uint64_t* __restrict__ mmask,
+__global__ void __launch_bounds__(kListThreads) k_group_members(int64_t nm, const uint64_t* __restrict__ mmask,
                                                             const int32_t* __restrict__ mlist,
                                                             int32_t* __restrict__ off, int32_t* __restrict__ gk,
                                                             int32_t* __restrict__ gq, uint64_t* __restrict__ gmask) {
-  __shared__ int32_t wcount[kThreads / kWave];
+  __shared__ int32_t wcount[kListThreads / kWave];
   const int i = blockIdx.x, w = threadIdx.x / kWave;
   int32_t running = FILL ? off[i] : 0;
-  for (int64_t b = 0; b < nm; b += kThreads) {
+  for (int64_t b = 0; b < nm; b += kListThreads) {
     const int64_t k = b + threadIdx.x;
     const uint64_t mk = k < nm ? mmask[k] : 0;
     const bool hit = (mk >> i) & 1;
@@ -101,7 +103,7 @@ __global__ void __launch_bounds__(kThreads) k_group_members(int64_t nm, const ui
     if (lane_id() == 0) wcount[w] = __popcll(bal);
     __syncthreads();
     int32_t before = 0, total = 0;
-    for (int j = 0; j < kThreads / kWave; ++j) {
+    for (int j = 0; j < kListThreads / kWave; ++j) {
       if (j < w) before += wcount[j];
       total += wcount[j];
     }
@@ -562,42 +564,48 @@ static T* cache_new(gp_ctx* c, int64_t count) {
   }
 }
 
+// the lists in one allocation: masks, then indices, ids and offsets
+static size_t member_words(const gp_predictor* p) {
+  return static_cast<size_t>(p->nlist) * 2 + (p->kt.n1 + 2) / 2;
+}
+
 static void free_member_lists(gp_ctx* c, gp_predictor* p) {
-  if (p->goff) dev_free(c, p->goff, sizeof(int32_t) * (p->kt.n1 + 1));
-  if (p->gk) dev_free(c, p->gk, sizeof(int32_t) * p->nlist);
-  if (p->gq) dev_free(c, p->gq, sizeof(int32_t) * p->nlist);
-  if (p->gmask) dev_free(c, p->gmask, sizeof(uint64_t) * p->nlist);
+  if (p->gmask) dev_free(c, p->gmask, sizeof(uint64_t) * member_words(p));
   p->goff = p->gk = p->gq = nullptr;
   p->gmask = nullptr;
 }
 
+// Masked points from which on the lists are made: they cost gp_predictor_create 45 - 60 us
+// (a read-back, an allocation, two passes), which a few thousand masks tested by a wave
+// do not.  Create, 1, 1009 and 100,003 sites without -> with, us (mixture, Matern core):
+//   2858 masked 90 -> 137, 22 -> 22, 68 -> 59, 233 -> 195
+//   4787        95 -> 139, 40 -> 28, 88 -> 87, 277 -> 249
+//   26,644     140 -> 199, 30 -> 29, 259 -> 250, 1666 -> 1268
+constexpr int64_t kListMembers = 4096;
+
 // Member lists of the groups from the predictor's masked points (nm > 0).
 static void make_member_lists(gp_ctx* c, gp_predictor* p, int n1) {
-  p->goff = cache_new<int32_t>(c, n1 + 1);
-  if (!p->goff) return;
-  hipLaunchKernelGGL((k_group_members<false>), dim3(n1), dim3(kThreads), 0, c->stream, p->nm, p->mmask, p->mlist,
-                     p->goff, nullptr, nullptr, nullptr);
+  int32_t* size = static_cast<int32_t*>(workspace(c, 122, sizeof(int32_t) * (kMaxGroups + 1)));
+  hipLaunchKernelGGL((k_group_members<false>), dim3(n1), dim3(kListThreads), 0, c->stream, p->nm, p->mmask, p->mlist,
+                     size, nullptr, nullptr, nullptr);
   check_launch("group sizes");
   int32_t* h = static_cast<int32_t*>(pinned_for_write(c, sizeof(int32_t) * (n1 + 1)));
-  GPS_HIP(hipMemcpyAsync(h, p->goff, sizeof(int32_t) * (n1 + 1), hipMemcpyDeviceToHost, c->stream));
+  GPS_HIP(hipMemcpyAsync(h, size, sizeof(int32_t) * (n1 + 1), hipMemcpyDeviceToHost, c->stream));
   sync(c);
   int64_t total = 0;
   for (int i = 0; i <= n1; ++i) {
     if (i > 0) total += h[i];
     h[i] = static_cast<int32_t>(total);
   }
-  if (total < (int64_t(1) << 31)) {
-    p->nlist = total;  // > 0: every masked point is in a group
-    p->gk = cache_new<int32_t>(c, total);
-    p->gq = cache_new<int32_t>(c, total);
-    p->gmask = cache_new<uint64_t>(c, total);
-  }
-  if (!p->gk || !p->gq || !p->gmask) {
-    free_member_lists(c, p);
-    return;
-  }
+  if (total >= (int64_t(1) << 31)) return;
+  p->nlist = total;  // > 0: every masked point is in a group
+  p->gmask = cache_new<uint64_t>(c, static_cast<int64_t>(member_words(p)));
+  if (!p->gmask) return;
+  p->gk = reinterpret_cast<int32_t*>(p->gmask + total);
+  p->gq = p->gk + total;
+  p->goff = p->gq + total;
   h2d_async(c, p->goff, h, sizeof(int32_t) * (n1 + 1));
-  hipLaunchKernelGGL((k_group_members<true>), dim3(n1), dim3(kThreads), 0, c->stream, p->nm, p->mmask, p->mlist,
+  hipLaunchKernelGGL((k_group_members<true>), dim3(n1), dim3(kListThreads), 0, c->stream, p->nm, p->mmask, p->mlist,
                      p->goff, p->gk, p->gq, p->gmask);
   check_launch("group members");
 }
@@ -656,7 +664,7 @@ gp_predictor* make_predictor(gp_ctx* c, const gp_dataset* ds, const gp_theta* th
       hipLaunchKernelGGL(k_pack, dim3(grid_for(n, kThreads)), dim3(kThreads), 0, c->stream, n, ds->d, ds->xb,
                          p->alpha_b, p->pack);
     check_launch("pack training data");
-    if (p->nm > 0) make_member_lists(c, p.get(), th->n1);
+    if (p->nm >= kListMembers) make_member_lists(c, p.get(), th->n1);
   }
   sync(c);
   return p.release();
