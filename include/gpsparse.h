@@ -475,13 +475,18 @@ GP_API gp_status gp_mean_residual(gp_ctx* ctx, int64_t n, int32_t p, const doubl
  * into var_dev (m float64, device).  K must have been assembled with theta
  * (checked against a fingerprint of every hyper-parameter except tau2, which
  * enters K only and is not read here).  The test points
- * (xstar_dev: m x d row-major float64, device) are taken 32 at a time: their
- * cross-covariance columns are formed on the device and K W = C is solved by
- * 32 preconditioned conjugate-gradient recurrences in lockstep (one sparse
- * product with 32 columns per step, float64 vectors, the matrix's stored
- * values; opts->precond: block Jacobi, the default, or Jacobi), each stopping
- * when |c_s - K w_s| <= opts->rtol |c_s|; a float64 true residual is taken at
- * the end.  opts may be NULL (defaults; rtol, max_iter and precond are used).
+ * (xstar_dev: m x d row-major float64, device) are taken 32 at a time, the last
+ * of a request in the narrowest block of 1, 8, 16 or 32 columns that holds them:
+ * their cross-covariance columns are formed on the device and K W = C is solved
+ * by as many preconditioned conjugate-gradient recurrences in lockstep (one
+ * sparse product with the block's columns per step, float64 vectors, the
+ * matrix's stored values; opts->precond: block Jacobi, the default, or Jacobi),
+ * each stopping when |c_s - K w_s| <= opts->rtol |c_s|; a float64 true residual
+ * is taken at the end.  The same request gives the same bits every time; a
+ * point's variance may differ at rounding level between requests that put it
+ * into blocks of different width (the products and reductions of each width
+ * add in an order of their own).  A block of one column uses the one-column
+ * product and its int16 offsets (see gp_matvec).  opts may be NULL (defaults; rtol, max_iter and precond are used).
  * Work space: six n x 32 float64 blocks (n x 16, 8 or 1 for requests of so few points).
  * out (may be NULL) receives iteration counts and the largest final relative
  * residual.

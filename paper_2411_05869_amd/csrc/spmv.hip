@@ -627,7 +627,8 @@ __global__ void __launch_bounds__(kThreads) k_col16(int64_t n, const int64_t* __
 // 13.7 -> 9.6, 5.0M 21.4 -> 16.2, 42M 52.5 -> 49.0 and 87.5 -> 79.2 (FP64).  At 87M
 // entries the CSR rows want the waves that the tile code's registers cost them:
 // FP64 239 -> 243 us (gp_matvec); mixed (6 waves, see one_waves) 183 -> 180, but a
-// likelihood with the log det's products beside it 114.6 -> 116.6 ms.
+// likelihood with the log det's products beside it 114.6 -> 116.6 ms; one limit holds
+// for both.
 constexpr int64_t kOneLaunchEntries = int64_t(64) << 20;
 
 // Waves per SIMD the one-launch product is compiled for.  The tile code is at its
