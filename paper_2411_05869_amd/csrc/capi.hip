@@ -721,8 +721,9 @@ gp_status gp_loglik_batch(gp_ctx* c, int32_t nreq, const gp_matrix* const* K, co
   for (int r = 0; r < nreq; ++r)
     if (!K[r] || !y[r]) return GP_EINVAL;
   std::memset(out, 0, sizeof(gp_loglik_result) * nreq);
-  const gp_solve_opts o = fill_opts(opts);
+  gp_solve_opts o;
   gp_status st = guarded(c, [&] {
+    o = fill_opts(opts);
     GPS_REQUIRE(o.solver == GP_SOLVER_CG || o.solver == GP_SOLVER_AUTO, GP_EINVAL,
                 "gp_loglik_batch: the solver must be GP_SOLVER_CG or GP_SOLVER_AUTO");
     GPS_REQUIRE(o.logdet_mode == GP_LOGDET_SLQ || o.logdet_mode == GP_LOGDET_NONE, GP_EINVAL,
